@@ -391,9 +391,13 @@ gevp_status copy_ct(gevp_ctx* c, int64_t m, int64_t k, const zd* in, int64_t ldi
 // stream applies the panel first to the next panel's columns, after which
 // the panel stream may factor that panel, then to the rest of the lower
 // triangle, which overlaps the factorisation.
+namespace {
+constexpr int64_t IPW = 6 * NB;
+inline int64_t outer_panel(int64_t n) { return n >= 6144 ? 1024 : n >= 3072 ? 768 : IPW; }
+}  // namespace
 gevp_status chol_lower(gevp_ctx* c, int64_t n, zd* M, int64_t ldm, zd* Dinv, int64_t ldi,
                        int* info_dev, hipEvent_t midpoint, zd* R, int64_t ldr, int64_t m) {
-  constexpr int64_t PW = 6 * NB;  // measured at n = 8192: 30 ms; 128: 31, 256: 32, 512: 33
+  const int64_t PW = outer_panel(n);
   if (n <= 0) {
     if (midpoint) GEVP_HIP_TRY(hipEventRecord(midpoint, c->stream));
     return GEVP_OK;
@@ -420,20 +424,29 @@ gevp_status chol_lower(gevp_ctx* c, int64_t n, zd* M, int64_t ldm, zd* Dinv, int
     }
     for (int64_t p0 = 0; p0 < n; p0 += PW) {
       const int64_t pw = std::min<int64_t>(PW, n - p0), pend = p0 + pw;
-      // factor the panel (columns p0 .. pend-1, all rows below p0)
-      for (int64_t r0 = p0; r0 < pend; r0 += NB) {
-        const int64_t kb = std::min<int64_t>(NB, pend - r0), below = n - r0 - kb;
-        zd* Mkk = M + r0 + r0 * ldm;
-        GEVP_TRY(potrf_leaf(pc, kb, Mkk, ldm, Dinv + r0, ldi, info_dev, r0));
-        if (below <= 0) continue;
-        zd* L21 = Mkk + kb;
-        GEVP_TRY(launch_zgemm(pc, 0, 1, below, kb, kb, 1.0, L21, ldm, Dinv + r0, ldi, 0.0, nullptr,
-                              0, 0.0, nullptr, 0, nullptr, L21, ldm));
-        const int64_t w = pend - r0 - kb;  // panel columns right of this block
-        if (w > 0) {
-          zd* A2 = M + (r0 + kb) + (r0 + kb) * ldm;
-          GEVP_TRY(launch_zgemm(pc, 0, 1, below, w, kb, -1.0, L21, ldm, L21, ldm, 1.0, A2, ldm, 0.0,
-                                nullptr, 0, nullptr, A2, ldm));
+      // factor the panel (columns p0 .. pend-1, all rows below p0) in inner panels
+      for (int64_t q0 = p0; q0 < pend; q0 += IPW) {
+        const int64_t qend = std::min<int64_t>(q0 + IPW, pend);
+        for (int64_t r0 = q0; r0 < qend; r0 += NB) {
+          const int64_t kb = std::min<int64_t>(NB, qend - r0), below = n - r0 - kb;
+          zd* Mkk = M + r0 + r0 * ldm;
+          GEVP_TRY(potrf_leaf(pc, kb, Mkk, ldm, Dinv + r0, ldi, info_dev, r0));
+          if (below <= 0) continue;
+          zd* L21 = Mkk + kb;
+          GEVP_TRY(launch_zgemm(pc, 0, 1, below, kb, kb, 1.0, L21, ldm, Dinv + r0, ldi, 0.0, nullptr,
+                                0, 0.0, nullptr, 0, nullptr, L21, ldm));
+          const int64_t w = qend - r0 - kb;  // inner panel columns right of this block
+          if (w > 0) {
+            zd* A2 = M + (r0 + kb) + (r0 + kb) * ldm;
+            GEVP_TRY(launch_zgemm(pc, 0, 1, below, w, kb, -1.0, L21, ldm, L21, ldm, 1.0, A2, ldm, 0.0,
+                                  nullptr, 0, nullptr, A2, ldm));
+          }
+        }
+        if (qend < pend) {  // the panel's columns right of the inner panel
+          const zd* Lq = M + qend + q0 * ldm;
+          zd* A2 = M + qend + qend * ldm;
+          GEVP_TRY(launch_zgemm(pc, 0, 1, n - qend, pend - qend, qend - q0, -1.0, Lq, ldm, Lq, ldm, 1.0,
+                                A2, ldm, 0.0, nullptr, 0, nullptr, A2, ldm));
         }
       }
       const int64_t rest = n - pend;

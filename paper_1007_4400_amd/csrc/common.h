@@ -94,6 +94,16 @@ struct gevp_ctx {
   // set for the duration of a call that must not allocate: launch_zgemm then
   // never splits K (which needs the split-K buffer)
   bool no_split = false;
+  // scratch of the residue-arithmetic products (zgemm_mod.hip): library-owned,
+  // grown on demand and freed by destroy; in a caller-owned workspace the part
+  // of ws beyond ws_used serves instead.  no_mod: keep to the FP64 kernels
+  // (calls that must not allocate, and after a failed allocation).
+  char* mod = nullptr;
+  size_t mod_bytes = 0;
+  bool mod_borrowed = false;  // mod points into the caller-owned workspace
+  bool no_mod = false;
+  hipStream_t mod_stream = nullptr;  // stream of the last product that used mod, done at mod_done
+  hipEvent_t mod_done = nullptr;
   // split-K cost models count the compute units divided by this (a batched
   // worker shares the GPU with the other streams)
   int cu_div = 1;
@@ -122,6 +132,14 @@ gevp_status ws_reserve(gevp_ctx* c, size_t bytes);
 void* ws_take(gevp_ctx* c, size_t bytes);
 inline size_t ws_round(size_t b) { return (b + 255) & ~size_t(255); }
 
+struct ModPrepared {  // a left operand converted once for several products
+  void* planes = nullptr;
+  int* ex = nullptr;
+  const double* ks = nullptr;  // balancing scales for the right operands
+  int* flag = nullptr;
+  int64_t m = 0, k = 0;
+};
+
 // ---- kernel launchers (host functions, asynchronous on c->stream)
 
 // D = alpha op(A) op(B) + beta Cm + gamma diag(gcol) E   (FP64 MFMA, complex128)
@@ -139,7 +157,32 @@ gevp_status launch_zgemm(gevp_ctx* c, int opA, int opB, int64_t m, int64_t n, in
                          double beta, const zd* Cm, int64_t ldc, double gamma, const zd* E,
                          int64_t lde, const double* gcol, zd* D, int64_t ldd,
                          const double* coef = nullptr, int lower = 0, int upperA = 0,
-                         int64_t m1 = 0, const zd* A2 = nullptr);
+                         int64_t m1 = 0, const zd* A2 = nullptr,
+                         const ModPrepared* prepared = nullptr);
+
+// Residue-arithmetic products on the INT8 matrix cores (zgemm_mod.hip); used by
+// launch_zgemm where mod_gemm_pays and scratch is available.
+struct ModGemmCall {
+  int opA, opB, lower, upperA;
+  int64_t m, n, k, m1;
+  const zd *A, *A2, *B, *Cm, *E;
+  int64_t lda, ldb, ldc, lde, ldd;
+  double alpha, beta, gamma;
+  const double *gcol, *coef;
+  zd* D;
+  const ModPrepared* prepared;
+};
+bool mod_gemm_pays(int opA, int opB, int64_t m, int64_t n, int64_t k, int lower, int upperA, bool prepared);
+size_t mod_gemm_bytes(int64_t m, int64_t n, int64_t k);
+size_t mod_prepared_bytes(int64_t m, int64_t k);
+gevp_status mod_prepare(gevp_ctx* c, int64_t m, int64_t k, int opA, const zd* A, int64_t lda, void* buf,
+                        ModPrepared* out);
+// scratch >= mod_gemm_bytes; *flag1, *flag2 (the latter may be null): device
+// flags, raised when the product was left to the FP64 kernels
+gevp_status launch_mod_gemm(gevp_ctx* c, const ModGemmCall& g, void* scratch, const int** flag1,
+                            const int** flag2);
+// scratch of at least `bytes` for the next product on c's stream, or null
+void* mod_scratch(gevp_ctx* c, size_t bytes);
 
 // Blocked Cholesky of the lower triangle; Dinv (n x 64 column-major, ld =
 // ldi) receives the inverses of the 64 x 64 diagonal blocks; *info_dev

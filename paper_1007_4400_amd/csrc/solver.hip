@@ -229,6 +229,24 @@ size_t solve_ws_bytes_max(const Opts& o, int64_t n, int64_t nev) {
   return b;
 }
 
+// Residue-arithmetic products of a solve (zgemm_mod.hip): the reduced matrix
+// converted once, and the scratch of the largest product on the main and on
+// the second stream.  Optional: where the memory is not there the FP64 kernels
+// do these products.  Below n = 640 none of them pays.
+struct ModBytes {
+  size_t prepared = 0, main = 0, second = 0;
+  size_t total() const { return ws_round(prepared) + ws_round(main) + ws_round(second); }
+};
+ModBytes solve_mod_bytes(int64_t n, int64_t nb, bool second) {
+  ModBytes b;
+  if (n < 640) return b;
+  if (mod_gemm_pays(0, 0, n, nb, n, 0, 0, true)) b.prepared = mod_prepared_bytes(n, n);
+  const int64_t w = std::min<int64_t>(n, 1024), h = (n / 2 + 63) / 64 * 64;
+  b.main = std::max(std::max(mod_gemm_bytes(n, nb, n), mod_gemm_bytes(n, n, w)), mod_gemm_bytes(h, h, h));
+  if (second) b.second = mod_gemm_bytes(n, nb, n);
+  return b;
+}
+
 struct Timer {
   gevp_ctx* c;
   hipEvent_t ev[2];
@@ -446,6 +464,8 @@ void gevp_destroy(gevp_handle h) {
   if (h->owns_stream) (void)hipStreamDestroy(h->stream);
   if (h->ws && !h->ext) (void)hipFree(h->ws);
   if (h->skw && !h->ext) (void)hipFree(h->skw);
+  if (h->mod && !h->mod_borrowed) (void)hipFree(h->mod);
+  if (h->mod_done) (void)hipEventDestroy(h->mod_done);
   for (int i = 0; i < h->fev_cap; ++i) (void)hipEventDestroy(h->fev[i]);
   delete[] h->fev;
   for (int i = 0; i < h->gev_cap; ++i) (void)hipEventDestroy(h->gev[i]);
@@ -463,7 +483,8 @@ gevp_status gevp_workspace_size(gevp_handle h, const gevp_opts* opts, int64_t n,
   (void)h;  // the size depends on the arguments only
   if (!bytes || n < 1 || nev < 1 || nev > n) return GEVP_ERR_INVALID;
   const Opts o = resolve(opts, nev);
-  *bytes = solve_ws_bytes_max(o, n, nev) + (size_t)EXT_SLOTS * SKW_BYTES;
+  *bytes = solve_ws_bytes_max(o, n, nev) + solve_mod_bytes(n, block_of(o, n, nev), true).total() +
+           (size_t)EXT_SLOTS * SKW_BYTES;
   return GEVP_OK;
 }
 
@@ -488,7 +509,9 @@ gevp_status gevp_workspace_size_batched(gevp_handle h, const gevp_opts* opts, in
   size_t per = 0;
   for (int i = 0; i < count; ++i) {
     if (n[i] < 1 || nev[i] < 1 || nev[i] > n[i]) return GEVP_ERR_INVALID;
-    per = std::max(per, solve_ws_bytes_max(resolve(opts, nev[i]), n[i], nev[i]));
+    const Opts o = resolve(opts, nev[i]);
+    per = std::max(per, solve_ws_bytes_max(o, n[i], nev[i]) +
+                            solve_mod_bytes(n[i], block_of(o, n[i], nev[i]), false).total());
   }
   per = ws_round(per + SKW_BYTES);
   const size_t total = per * (size_t)batch_stream_count(opts, count);
@@ -513,6 +536,10 @@ gevp_status gevp_set_workspace(gevp_handle h, void* dev_ptr, size_t bytes) {
       if (c->ws) (void)hipFree(c->ws);
       if (c->skw) (void)hipFree(c->skw);
     }
+    if (c->mod && !c->mod_borrowed) (void)hipFree(c->mod);
+    c->mod = nullptr;
+    c->mod_bytes = 0;
+    c->mod_borrowed = c->no_mod = false;
     c->ws = nullptr;
     c->ws_bytes = 0;
     c->ws_used = 0;
@@ -627,7 +654,27 @@ gevp_status gevp_solve(gevp_handle h, const gevp_opts* opts, int64_t n, const vo
   const int lz = o.lanczos;
   const size_t lp_elem = 8;                              // complex64
   const size_t need = solve_ws_bytes(o, n, nb, contour, c32, lp, bf16);
-  GEVP_TRY(ws_reserve(c, need));
+  const bool full_seed = seeded && k0 >= nb;
+  const bool spec = full_seed && c->inner_streams;
+  ModBytes mb = solve_mod_bytes(n, nb, spec);
+  if (c->no_mod) mb = ModBytes();
+  if (c->ext) {  // whatever the caller's buffer has beyond the solve's own needs
+    GEVP_TRY(ws_reserve(c, need));
+    size_t left = c->ws_bytes - need;
+    if (left < ws_round(mb.main)) mb = ModBytes();
+    left -= ws_round(mb.main);
+    if (left < ws_round(mb.prepared)) mb.prepared = 0;
+    left -= ws_round(mb.prepared);
+    if (left < ws_round(mb.second)) mb.second = 0;
+  } else {
+    gevp_status rs = ws_reserve(c, need + ws_round(mb.prepared));
+    if (rs == GEVP_ERR_ALLOC && mb.prepared) {
+      mb = ModBytes();
+      rs = ws_reserve(c, need);
+    }
+    GEVP_TRY(rs);
+    if (mb.main) (void)mod_scratch(c, mb.main);  // one allocation for all products
+  }
   zd* Af = (zd*)ws_take(c, sizeof(zd) * nn);
   zd* Bf = (zd*)ws_take(c, sizeof(zd) * nn);
   zd* L = (zd*)ws_take(c, sizeof(zd) * nn);
@@ -685,6 +732,11 @@ gevp_status gevp_solve(gevp_handle h, const gevp_opts* opts, int64_t n, const vo
     coef2 = (double*)ws_take(c, sizeof(double) * 4 * nb * (o.deg_reach + 2));
   }
 
+  void* mod_c = mb.prepared ? ws_take(c, mb.prepared) : nullptr;
+  void* mod_second = (c->ext && mb.second) ? ws_take(c, mb.second) : nullptr;
+  ModPrepared prepared;
+  const ModPrepared* pC = nullptr;  // C in residues, once it is formed
+
   Timer tm(c);
   // flags[0]: nonfinite input, flags[1]: Cholesky pivot of B, flags[2]: QR flag
   int init_flags[4] = {0, 0x7fffffff, 0x7fffffff, 0};
@@ -708,8 +760,6 @@ gevp_status gevp_solve(gevp_handle h, const gevp_opts* opts, int64_t n, const vo
   // path runs otherwise).  The second stream writes only T, Hs, Zs, theta,
   // norms, its Lanczos workspace and the eigensolver workspace, none of
   // which the main stream touches before the join.
-  const bool full_seed = seeded && k0 >= nb;
-  const bool spec = full_seed && c->inner_streams;
   const int lzn = lz > 12 ? 12 : lz;  // norm estimates need fewer steps than the filter bound
   const double frac = std::min(1.0, (double)nb / (double)n);
   EventPair evs;
@@ -719,6 +769,11 @@ gevp_status gevp_solve(gevp_handle h, const gevp_opts* opts, int64_t n, const vo
     ax->profiling = c->profiling & 4;
     ax->gev_used = 0;
     ax->gev_flops = 0.0;
+    if (c->ext) {
+      ax->mod = (char*)mod_second;
+      ax->mod_bytes = mod_second ? mb.second : 0;
+      ax->mod_borrowed = true;
+    }
     GEVP_HIP_TRY(hipEventCreateWithFlags(&evs.fork, hipEventDisableTiming));
     GEVP_HIP_TRY(hipEventCreateWithFlags(&evs.mid, hipEventDisableTiming));
     GEVP_HIP_TRY(hipEventCreateWithFlags(&evs.join, hipEventDisableTiming));
@@ -787,6 +842,10 @@ gevp_status gevp_solve(gevp_handle h, const gevp_opts* opts, int64_t n, const vo
   // only its lower triangle is formed, then mirrored
   GEVP_TRY(trsm_right_lower_c_lowerpart(c, n, L, n, Dinv, n, C, n, 1));
   GEVP_TRY(launch_mirror_lower(c, n, C, n, C, n, flags + 3));
+  if (mod_c) {
+    GEVP_TRY(mod_prepare(c, n, n, 0, C, n, mod_c, &prepared));
+    pC = &prepared;
+  }
   if (lp && bf16) GEVP_TRY(launch_split_rows_bf16(c, n, C, n, Clp));
   if (lp && !bf16) GEVP_TRY(launch_to_c32(c, n, n, C, n, Clp, n));
   tm.stop(info, GEVP_STAGE_REDUCE);
@@ -855,10 +914,10 @@ gevp_status gevp_solve(gevp_handle h, const gevp_opts* opts, int64_t n, const vo
       GEVP_TRY(fev_mark(c));
       if (j == 1)
         GEVP_TRY(launch_zgemm(c, 0, 0, n, cols, n, 0.0, C, n, src + s0 * n, n, 0.0, src + s0 * n, n,
-                              0.0, nullptr, 0, nullptr, dst + s0 * n, n, cf));
+                              0.0, nullptr, 0, nullptr, dst + s0 * n, n, cf, 0, 0, 0, nullptr, pC));
       else
         GEVP_TRY(launch_zgemm(c, 0, 0, n, cols, n, 0.0, C, n, src + s0 * n, n, 0.0, src + s0 * n, n,
-                              0.0, dst + s0 * n, n, nullptr, dst + s0 * n, n, cf));
+                              0.0, dst + s0 * n, n, nullptr, dst + s0 * n, n, cf, 0, 0, 0, nullptr, pC));
       GEVP_TRY(fev_mark(c));
     }
     std::swap(P0, P1);
@@ -945,7 +1004,7 @@ gevp_status gevp_solve(gevp_handle h, const gevp_opts* opts, int64_t n, const vo
       // Rayleigh-Ritz of the active columns; the locked ones are copied over
       zd* Wa = W + l0 * n;
       GEVP_TRY(launch_zgemm(c, 0, 0, n, na, n, 1.0, C, n, Pa, n, 0.0, nullptr, 0, 0.0, nullptr, 0,
-                            nullptr, Wa, n));
+                            nullptr, Wa, n, nullptr, 0, 0, 0, nullptr, pC));
       GEVP_TRY(launch_zgemm(c, 1, 0, na, na, n, 1.0, Pa, n, Wa, n, 0.0, nullptr, 0, 0.0, nullptr, 0,
                             nullptr, Hs, na, nullptr, 1));
       GEVP_TRY(launch_mirror_lower(c, na, Hs, na, Hs, na, nullptr));
@@ -961,10 +1020,10 @@ gevp_status gevp_solve(gevp_handle h, const gevp_opts* opts, int64_t n, const vo
       GEVP_TRY(launch_zgemm(c, 0, 0, n, nb, nb, 1.0, P0, n, Zs, nb, 0.0, nullptr, 0, 0.0, nullptr,
                             0, nullptr, P1, n));
       GEVP_TRY(launch_zgemm(c, 0, 0, n, nb, n, 1.0, C, n, P1, n, 0.0, nullptr, 0, 0.0, nullptr, 0,
-                            nullptr, T, n));
+                            nullptr, T, n, nullptr, 0, 0, 0, nullptr, pC));
     } else {
       GEVP_TRY(launch_zgemm(c, 0, 0, n, nb, n, 1.0, C, n, P0, n, 0.0, nullptr, 0, 0.0, nullptr, 0,
-                            nullptr, W, n));
+                            nullptr, W, n, nullptr, 0, 0, 0, nullptr, pC));
       GEVP_TRY(launch_zgemm(c, 1, 0, nb, nb, n, 1.0, P0, n, W, n, 0.0, nullptr, 0, 0.0, nullptr, 0,
                             nullptr, Hs, nb, nullptr, 1));
       GEVP_TRY(launch_mirror_lower(c, nb, Hs, nb, Hs, nb, nullptr));
@@ -1096,8 +1155,16 @@ gevp_status gevp_solve(gevp_handle h, const gevp_opts* opts, int64_t n, const vo
     // tiles fill the compute units' rounds better than two n-row products),
     // then the column norms of the top half minus the scaled bottom half
     const int64_t kr = resid_out ? kx : nev;
-    GEVP_TRY(launch_zgemm(c, 0, 0, 2 * n, kr, n, 1.0, Af, n, X, ldx, 0.0, nullptr, 0, 0.0, nullptr, 0,
-                          nullptr, WT, 2 * n, nullptr, 0, 0, n, Bf));
+    // (in residue arithmetic the two products need no such filling)
+    if (mb.main) {
+      GEVP_TRY(launch_zgemm(c, 0, 0, n, kr, n, 1.0, Af, n, X, ldx, 0.0, nullptr, 0, 0.0, nullptr, 0,
+                            nullptr, WT, 2 * n));
+      GEVP_TRY(launch_zgemm(c, 0, 0, n, kr, n, 1.0, Bf, n, X, ldx, 0.0, nullptr, 0, 0.0, nullptr, 0,
+                            nullptr, WT + n, 2 * n));
+    } else {
+      GEVP_TRY(launch_zgemm(c, 0, 0, 2 * n, kr, n, 1.0, Af, n, X, ldx, 0.0, nullptr, 0, 0.0, nullptr, 0,
+                            nullptr, WT, 2 * n, nullptr, 0, 0, n, Bf));
+    }
     GEVP_TRY(launch_resid_cols(c, n, kr, WT, 2 * n, WT + n, 2 * n, theta, fres));
     if (resid_out) GEVP_TRY(launch_copy_real(c, kx, fres, resid_out));
     std::vector<double> hr(kr);
@@ -1169,9 +1236,10 @@ gevp_status gevp_backward_noalloc(gevp_handle h, int64_t n, int64_t nev, const v
   const zd* X = (const zd*)X_;
   zd* Xw = (zd*)sp;  // n x nev scaled columns, in the scratch array
   // no split-K buffer and no profiling events for the duration of the call
-  const bool ns = c->no_split;
+  const bool ns = c->no_split, nm = c->no_mod;
   const int prof = c->profiling;
   c->no_split = true;
+  c->no_mod = true;
   c->profiling = 0;
   gevp_status st = GEVP_OK;
   if (dA_) {
@@ -1188,6 +1256,7 @@ gevp_status gevp_backward_noalloc(gevp_handle h, int64_t n, int64_t nev, const v
                         nullptr, (zd*)dB_, lddb);
   }
   c->no_split = ns;
+  c->no_mod = nm;
   c->profiling = prof;
   return st;
 }

@@ -83,6 +83,10 @@ struct ZgemmParams {
   zd* part;         // splits > 1: raw partial tiles [split][tile][col][row]
   const zd* A2;     // op(A) = 'N' only: rows >= M1 of op(A) are rows - M1 of A2 (same lda)
   int M1;
+  // k_zgemm_after: the product was done in residue arithmetic unless one of
+  // these flags is up (flag2 may be null)
+  const int* flag1;
+  const int* flag2;
 };
 
 __device__ __forceinline__ zd zconj(zd a) { return make_double2(a.x, -a.y); }
@@ -321,6 +325,16 @@ __global__ __launch_bounds__(NTHR, 2) void k_zgemm_nc(ZgemmParams p) { zgemm_til
 __global__ __launch_bounds__(NTHR, 2) void k_zgemm_cn(ZgemmParams p) { zgemm_tile<1, 0>(p); }
 __global__ __launch_bounds__(NTHR, 2) void k_zgemm_cc(ZgemmParams p) { zgemm_tile<1, 1>(p); }
 
+// Behind a product in residue arithmetic (zgemm_mod.hip): the whole product
+// where an operand could not be scaled, nothing otherwise.  Kernels of their
+// own: the two flag loads ahead of every work-group's first slice cost the
+// plain ones 7 per cent at K = 256.
+template <int OPA, int OPB>
+__global__ __launch_bounds__(NTHR, 2) void k_zgemm_after(ZgemmParams p) {
+  if (*p.flag1 == 0 && (p.flag2 == nullptr || *p.flag2 == 0)) return;
+  zgemm_tile<OPA, OPB>(p);
+}
+
 // Skinny tiles for products with at most 64 rows (TALL: 64 x 16 output
 // tiles) or at most 64 columns (16 x 64 tiles) and a short K: the base cases
 // and 64-wide updates of the triangular solves and the panel products of the
@@ -496,15 +510,52 @@ int zgemm_splits(int64_t T, int nk, int64_t slots, int64_t max_parts) {
 }
 }  // namespace
 
+void* mod_scratch(gevp_ctx* c, size_t bytes) {
+  // under capture nothing may be allocated and no event of this handle may be
+  // tied to the graph: the FP64 kernels alone
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(c->stream, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) {
+    (void)hipGetLastError();
+    return nullptr;
+  }
+  // a caller that moves the handle to another stream: that stream's first
+  // product waits for the last one that used this scratch
+  if (c->mod_done && c->mod_stream != c->stream &&
+      hipStreamWaitEvent(c->stream, c->mod_done, 0) != hipSuccess)
+    return nullptr;
+  if (c->ext && !c->mod_borrowed) {  // what the caller's workspace has left
+    const size_t used = ws_round(c->ws_used);
+    return (c->ws && used + bytes <= c->ws_bytes) ? c->ws + used : nullptr;
+  }
+  if (bytes <= c->mod_bytes) return c->mod;
+  if (c->ext || bytes > ((size_t)16 << 30)) return nullptr;
+  if (c->mod) {
+    if (hipStreamSynchronize(c->stream) != hipSuccess) return nullptr;  // earlier launches may still read it
+    (void)hipFree(c->mod);
+    c->mod = nullptr;
+    c->mod_bytes = 0;
+  }
+  if (hipMalloc((void**)&c->mod, bytes) != hipSuccess) {
+    c->mod = nullptr;
+    c->no_mod = true;  // no memory to spare: stay with the FP64 kernels
+    (void)hipGetLastError();
+    return nullptr;
+  }
+  c->mod_bytes = bytes;
+  return c->mod;
+}
+
 gevp_status launch_zgemm(gevp_ctx* c, int opA, int opB, int64_t m, int64_t n, int64_t k,
                          double alpha, const zd* A, int64_t lda, const zd* B, int64_t ldb,
                          double beta, const zd* Cm, int64_t ldc, double gamma, const zd* E,
                          int64_t lde, const double* gcol, zd* D, int64_t ldd,
-                         const double* coef, int lower, int upperA, int64_t m1, const zd* A2) {
+                         const double* coef, int lower, int upperA, int64_t m1, const zd* A2,
+                         const ModPrepared* prepared) {
   if (m <= 0 || n <= 0) return GEVP_OK;
   // a stacked left operand [A; A2]: plain 'N' form only
   if (A2 && (opA != 0 || lower || upperA || coef || m1 <= 0 || m1 >= m)) return GEVP_ERR_INVALID;
   if (m > INT32_MAX || n > INT32_MAX || k > INT32_MAX) return GEVP_ERR_INVALID;
+  if (prepared && (prepared->m != m || prepared->k != k || upperA || A2)) return GEVP_ERR_INVALID;
   ZgemmParams p;
   p.M = (int)m;
   p.N = (int)n;
@@ -551,7 +602,22 @@ gevp_status launch_zgemm(gevp_ctx* c, int opA, int opB, int64_t m, int64_t n, in
   }
   const int nk = (p.K + KT - 1) / KT;
   p.upperA = upperA;
-  int s = (c->no_split || skinny)
+  // FP64 GEMM timing (profiling bit 4): not the FP64 filter (coef), which is
+  // timed as a filter product by the caller
+  const bool timed = (coef == nullptr) && (c->profiling & 4);
+  p.flag1 = p.flag2 = nullptr;
+  bool mod = false;
+  if (!skinny && !c->no_mod &&
+      mod_gemm_pays(opA, opB, m, n, k, lower, upperA, prepared != nullptr)) {
+    if (void* sc = mod_scratch(c, mod_gemm_bytes(m, n, k))) {
+      const ModGemmCall g{opA, opB, lower, upperA, m, n, k, m1, A, A2, B, Cm, E, lda, ldb, ldc, lde, ldd,
+                          alpha, beta, gamma, gcol, coef, D, prepared};
+      if (timed) GEVP_TRY(gev_begin(c));
+      GEVP_TRY(launch_mod_gemm(c, g, sc, &p.flag1, &p.flag2));
+      mod = true;
+    }
+  }
+  int s = (c->no_split || skinny || mod)
               ? 1
               : zgemm_splits(total, nk,
                              std::max<int64_t>(1, 2 * (int64_t)gevp_device_cus(c->device) / std::max(1, c->cu_div)),
@@ -588,9 +654,6 @@ gevp_status launch_zgemm(gevp_ctx* c, int opA, int opB, int64_t m, int64_t n, in
   // eighth tile, heavy rows first.
   p.remap = (!upperA && blocks % 8 == 0 && blocks >= 64) ? 1 : 0;
   const dim3 grid((unsigned)blocks), thr(NTHR);
-  // FP64 GEMM timing (profiling bit 4): not the FP64 filter (coef), which is
-  // timed as a filter product by the caller
-  const bool timed = (coef == nullptr) && (c->profiling & 4);
   if (skinny) {
     const int64_t sm = skinny == 1 ? 64 : 16, sn = skinny == 1 ? 16 : 64;
     const int64_t sk_tiles = ((m + sm - 1) / sm) * ((n + sn - 1) / sn);
@@ -614,8 +677,13 @@ gevp_status launch_zgemm(gevp_ctx* c, int opA, int opB, int64_t m, int64_t n, in
     }
     return GEVP_OK;
   }
-  if (timed) GEVP_TRY(gev_begin(c));
-  if (opA == 0 && opB == 0) {
+  if (timed && !mod) GEVP_TRY(gev_begin(c));
+  if (mod) {
+    if (opA == 0 && opB == 0) hipLaunchKernelGGL((k_zgemm_after<0, 0>), grid, thr, 0, c->stream, p);
+    else if (opA == 0) hipLaunchKernelGGL((k_zgemm_after<0, 1>), grid, thr, 0, c->stream, p);
+    else if (opB == 0) hipLaunchKernelGGL((k_zgemm_after<1, 0>), grid, thr, 0, c->stream, p);
+    else hipLaunchKernelGGL((k_zgemm_after<1, 1>), grid, thr, 0, c->stream, p);
+  } else if (opA == 0 && opB == 0) {
     if (coef)
       hipLaunchKernelGGL(k_zgemm<1>, grid, thr, 0, c->stream, p);
     else
@@ -633,6 +701,11 @@ gevp_status launch_zgemm(gevp_ctx* c, int opA, int opB, int64_t m, int64_t n, in
     hipLaunchKernelGGL(k_zgemm_splitk_reduce, dim3((unsigned)((elems + 255) / 256)), dim3(256), 0,
                        c->stream, p);
     GEVP_HIP_TRY(hipGetLastError());
+  }
+  if (mod) {
+    if (!c->mod_done) GEVP_HIP_TRY(hipEventCreateWithFlags(&c->mod_done, hipEventDisableTiming));
+    GEVP_HIP_TRY(hipEventRecord(c->mod_done, c->stream));
+    c->mod_stream = c->stream;
   }
   if (timed) {
     // algorithmic flops: 8 per complex multiply-add of the product as
