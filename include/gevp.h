@@ -219,8 +219,11 @@ gevp_status gevp_workspace_size_batched(gevp_handle h, const gevp_opts* opts, in
  * at its top end), owned by the caller and left valid until the handle is
  * destroyed or the workspace replaced.  The handle then calls no hipMalloc
  * or hipFree for device memory; a call that needs more than the buffer
- * returns GEVP_ERR_WORKSPACE before launching anything.  Memory the handle
- * had allocated itself is freed here.  dev_ptr = NULL returns to
+ * returns GEVP_ERR_WORKSPACE before launching anything.  What the buffer has
+ * beyond a call's needs serves as scratch of the large products on the INT8
+ * matrix cores (at n = 8192, nev = 820 about 8 GiB let a solve use them
+ * throughout); without it the FP64 matrix cores do these products.  Memory the
+ * handle had allocated itself is freed here.  dev_ptr = NULL returns to
  * library-managed memory.  Waits for the handle's streams.  Calls that share
  * a handle must not overlap (one handle per stream, as always). */
 gevp_status gevp_set_workspace(gevp_handle h, void* dev_ptr, size_t bytes);
@@ -356,10 +359,16 @@ gevp_status gevp_backward_noalloc(gevp_handle h, int64_t n, int64_t nev, const v
 /* ---- kernel-level entry points (the building blocks, exposed for tests) ---- */
 
 /*
- * D = alpha op(A) op(B) + beta Cm + gamma diag-scaled E on FP64 MFMA, complex128.
+ * D = alpha op(A) op(B) + beta Cm + gamma diag-scaled E on the matrix cores, complex128.
  *   opA, opB: 'N' or 'C' (conjugate transpose).  op(A) is m x k, op(B) k x n.
  *   Cm may alias D; Cm / E may be NULL (term dropped).  gcol (device float64[n])
  *   scales the E term per column when non-NULL.  Asynchronous.
+ * Large products run in residue arithmetic on the INT8 matrix cores (see
+ * zgemm_mod.hip): after an exact power-of-two balancing along k, an entry's
+ * error is at most about sqrt(k) 2^-57 ||op(A)(i, :)|| ||op(B)(:, j)|| and a few
+ * roundings of the entry itself.  The handle keeps their scratch (up to 16 GiB,
+ * the largest product's); under stream capture, or where the memory is not to
+ * be had, the FP64 matrix cores do every product.
  */
 gevp_status gevp_k_zgemm(gevp_handle h, char opA, char opB, int64_t m, int64_t n, int64_t k,
                          double alpha, const void* A, int64_t lda, const void* B, int64_t ldb,

@@ -231,11 +231,11 @@ size_t solve_ws_bytes_max(const Opts& o, int64_t n, int64_t nev) {
 
 // Residue-arithmetic products of a solve (zgemm_mod.hip): the reduced matrix
 // converted once, and the scratch of the largest product on the main and on
-// the second stream.  Optional: where the memory is not there the FP64 kernels
-// do these products.  Below n = 640 none of them pays.
+// the second stream.  Optional, and no part of gevp_workspace_size: where the
+// memory is not there the FP64 kernels do these products.  Below n = 640 none
+// of them pays.
 struct ModBytes {
   size_t prepared = 0, main = 0, second = 0;
-  size_t total() const { return ws_round(prepared) + ws_round(main) + ws_round(second); }
 };
 ModBytes solve_mod_bytes(int64_t n, int64_t nb, bool second) {
   ModBytes b;
@@ -483,8 +483,7 @@ gevp_status gevp_workspace_size(gevp_handle h, const gevp_opts* opts, int64_t n,
   (void)h;  // the size depends on the arguments only
   if (!bytes || n < 1 || nev < 1 || nev > n) return GEVP_ERR_INVALID;
   const Opts o = resolve(opts, nev);
-  *bytes = solve_ws_bytes_max(o, n, nev) + solve_mod_bytes(n, block_of(o, n, nev), true).total() +
-           (size_t)EXT_SLOTS * SKW_BYTES;
+  *bytes = solve_ws_bytes_max(o, n, nev) + (size_t)EXT_SLOTS * SKW_BYTES;
   return GEVP_OK;
 }
 
@@ -509,9 +508,7 @@ gevp_status gevp_workspace_size_batched(gevp_handle h, const gevp_opts* opts, in
   size_t per = 0;
   for (int i = 0; i < count; ++i) {
     if (n[i] < 1 || nev[i] < 1 || nev[i] > n[i]) return GEVP_ERR_INVALID;
-    const Opts o = resolve(opts, nev[i]);
-    per = std::max(per, solve_ws_bytes_max(o, n[i], nev[i]) +
-                            solve_mod_bytes(n[i], block_of(o, n[i], nev[i]), false).total());
+    per = std::max(per, solve_ws_bytes_max(resolve(opts, nev[i]), n[i], nev[i]));
   }
   per = ws_round(per + SKW_BYTES);
   const size_t total = per * (size_t)batch_stream_count(opts, count);
