@@ -8,6 +8,7 @@
 // matrix cores per level, and the base case applies a diagonal block's
 // inverse with a GEMM (in place: a 64-wide block fits one output tile of the
 // GEMM, so every tile reads its whole K range before it writes).
+#include <cfloat>
 #include <climits>
 
 #include "common.h"
@@ -15,293 +16,335 @@
 namespace {
 constexpr int NB = 64;
 
-// Register-resident 64 x 64 block algorithms.  Thread t owns row i = t % 64
-// and the 16 columns c = kq + 4m (kq = t / 64, m = 0..15), so the four waves
-// split the columns and a wave reads a broadcast buffer at a uniform index.
+typedef double d4 __attribute__((ext_vector_type(4)));
 
-__device__ __forceinline__ zd zmul(zd a, zd b) {
-  return make_double2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
-}
-
-// X = inv(L) for the lower-triangular n x n L held in S[col][row], by
-// right-looking forward substitution on L X = I: row k of X is finished at
-// step k and broadcast through a double-buffered row buffer (one barrier per
-// step).  X is written to Dinv (zeros above the diagonal).
-__device__ void reg_inverse_to(zd (*S)[NB], zd (*xrow)[NB], int n, zd* Dinv, int64_t ldi) {
-  const int tid = threadIdx.x, i = tid & 63, kq = tid >> 6;
-  zd b[16];
-#pragma unroll
-  for (int m = 0; m < 16; ++m) b[m] = make_double2((kq + 4 * m == i) ? 1.0 : 0.0, 0.0);
-  for (int k = 0; k < n; ++k) {
-    zd* xr = xrow[k & 1];
-    if (i == k) {
-      const zd lkk = S[k][k];
-      const double dd = lkk.x * lkk.x + lkk.y * lkk.y;
-      const zd r = make_double2(lkk.x / dd, -lkk.y / dd);  // 1 / l_kk
-#pragma unroll
-      for (int m = 0; m < 16; ++m) {
-        b[m] = zmul(b[m], r);
-        xr[kq + 4 * m] = b[m];
-      }
-    }
-    __syncthreads();
-    // rows i > k subtract l_ik * x_k; every load is unconditional (valid
-    // addresses) and a 0/1 factor masks the update, so no branch splits the
-    // batch of LDS reads
-    const double fk = (i > k && i < n) ? 1.0 : 0.0;
-    zd lik = S[k][i];
-    lik.x *= fk;
-    lik.y *= fk;
-    zd xv[16];
-#pragma unroll
-    for (int m = 0; m < 16; ++m) xv[m] = xr[kq + 4 * m];
-#pragma unroll
-    for (int m = 0; m < 16; ++m) {
-      const zd t = zmul(lik, xv[m]);
-      b[m].x -= t.x;
-      b[m].y -= t.y;
-    }
-  }
-  if (i < n) {
-#pragma unroll
-    for (int m = 0; m < 16; ++m) {
-      const int c = kq + 4 * m;
-      if (c < n) Dinv[i + (int64_t)c * ldi] = (c <= i) ? b[m] : make_double2(0.0, 0.0);
-    }
-  }
-}
-
-// Factor the n x n (n <= 64) diagonal block at M (lower triangle read), write
-// L back (upper part of the block zeroed) and inv(L) to Dinv.
-//
-// Blocked right-looking in LDS with 16-wide panels.  Per panel: one wave
-// factors the 16 x 16 diagonal block and inverts it (lanes own a row and
-// four columns; a wave's LDS accesses are ordered, so no barrier is needed
-// inside), then all threads form the panel below as A21 inv(L11)^H and
-// update the trailing lower triangle.  inv(L) is then assembled block row by
-// block row from the diagonal inverses: X_IJ = -X_II sum_{K=J}^{I-1} L_IK X_KJ.
-// Entries past n are the identity, so a ragged block needs no special case.
-// A non-positive or non-finite pivot is recorded in *info (atomic min of the
-// 1-based global index) and replaced by 1 so the kernel always finishes.
 constexpr int PB = 16;       // panel width
 constexpr int SLD = NB + 1;  // LDS column stride in complex entries (odd: rows spread over banks)
 // L and inv(L) share one array: L in the lower triangle (column-major,
 // S[c * SLD + r], r >= c), the strict lower triangle of inv(L) transposed into
 // the upper one (X(i, j), i > j, at S[i * SLD + j]), inv(L)'s diagonal in a
-// separate vector.  66.5 KB of LDS instead of 133 KB, so the factor fits on a
-// compute unit next to one work-group of the trailing-update GEMM (which holds
-// 66.5 KB) instead of waiting for a unit with both of its GEMM work-groups
-// gone.
-constexpr size_t POTRF_LDS = sizeof(zd) * (NB * SLD + NB);
+// separate vector: 75 KB of LDS, so the factor fits on a compute unit next to
+// one work-group of the FP64 trailing-update GEMM.
+constexpr int TLD = 33;
+struct Block64 {
+  zd S[NB * SLD];
+  zd Xd[NB];        // diagonal of inv(L)
+  zd T[PB * TLD];   // the inverting wave's copy of a panel's columns
+};
 
-__device__ __forceinline__ zd zmulc(zd a, zd b) {  // a * conj(b)
-  return make_double2(a.x * b.x + a.y * b.y, a.y * b.x - a.x * b.y);
+__device__ __forceinline__ double lane_value(double v, int lane) {
+  const unsigned long long u = __double_as_longlong(v);
+  const unsigned lo = __builtin_amdgcn_readlane((unsigned)u, lane);
+  const unsigned hi = __builtin_amdgcn_readlane((unsigned)(u >> 32), lane);
+  return __longlong_as_double(((unsigned long long)hi << 32) | lo);
 }
 
+// s = sqrt(d) and il = 1 / s for finite d > 0, each to about one unit in the
+// last place: the hardware estimate (24 bits) and one third-order step, a chain
+// of five operations where the library's square root and division take over
+// thirty (no product leaves the range for any d, subnormal ones included)
+__device__ __forceinline__ void sqrt_and_inverse(double d, double& s, double& il) {
+  const double y = __builtin_amdgcn_rsq(d);
+  const double e = fma(-(d * y), y, 1.0);
+  il = fma(y * e, fma(e, 0.375, 0.5), y);
+  const double t = d * il;
+  s = fma(fma(-t, t, d), 0.5 * il, t);
+}
+// by value: a conditional between lvalues would be a choice of addresses, with
+// the operands put in memory for it
+__device__ __forceinline__ zd pick(bool c, zd a, zd b) {
+  return make_double2(c ? a.x : b.x, c ? a.y : b.y);
+}
+// a - b conj(s), a - b s
+__device__ __forceinline__ zd sub_mulc(zd a, zd b, zd s) {
+  return make_double2(fma(-b.y, s.y, fma(-b.x, s.x, a.x)), fma(b.x, s.y, fma(-b.y, s.x, a.y)));
+}
+__device__ __forceinline__ zd sub_mul(zd a, zd b, zd s) {
+  return make_double2(fma(b.y, s.y, fma(-b.x, s.x, a.x)), fma(-b.y, s.x, fma(-b.x, s.y, a.y)));
+}
+
+// A wave's part of a 16-column panel whose diagonal block starts at lane d0: a
+// lane holds its row's 16 entries in registers, so a column is finished by
+// every row at once, without a barrier.  The chain from pivot to pivot is what
+// counts: the next two columns get their multipliers straight from the lanes
+// that hold them; those of the others go through the LDS (broadcast reads of
+// the finished columns in buf) and are applied one column later, beside the
+// next pivot's chain.  Entries above the diagonal carry values no other row
+// reads.  Returns the first failing pivot of the panel, or INT_MAX.
+__device__ __forceinline__ int panel16(zd (&a)[PB], int d0, zd* buf, int ld, int slot) {
+  const int lane = threadIdx.x & 63;
+  zd f[2][PB];  // multipliers of this and the previous column
+  double ljj, il;
+  int bad = INT_MAX;
+  auto pivot = [&](int j) {
+    const double d = lane_value(a[j].x, d0 + j);
+    const bool ok = d > 0.0 && d <= DBL_MAX;
+    bad = ok ? bad : min(bad, j);
+    sqrt_and_inverse(d, ljj, il);
+    ljj = ok ? ljj : 1.0;
+    il = ok ? il : 1.0;
+  };
+  pivot(0);
+#pragma unroll
+  for (int j = 0; j < PB; ++j) {
+    a[j] = (lane == d0 + j) ? make_double2(ljj, 0.0) : make_double2(a[j].x * il, a[j].y * il);
+    zd* col = buf + j * ld;
+    col[slot] = a[j];
+#pragma unroll
+    for (int c = j + 3; c < PB; ++c) f[j & 1][c] = col[d0 + c];
+#pragma unroll
+    for (int c = j + 1; c < PB && c <= j + 2; ++c) {
+      a[c] = sub_mulc(a[c], a[j], make_double2(lane_value(a[j].x, d0 + c), lane_value(a[j].y, d0 + c)));
+      if (c == j + 1) pivot(c);
+    }
+    if (j > 0) {
+#pragma unroll
+      for (int c = j + 2; c < PB; ++c) a[c] = sub_mulc(a[c], a[j - 1], f[(j - 1) & 1][c]);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  return bad;
+}
+
+// Block (I, J) of the trailing matrix: A_IJ -= L_Ip L_Jp^H by one wave on the
+// matrix cores (above the diagonal of a diagonal block: values nobody reads)
+__device__ __forceinline__ void update16(Block64& m, int I, int J, int p) {
+  const int l16 = threadIdx.x & 15, lg = (threadIdx.x >> 4) & 3;
+  zd* col = m.S + (J * PB + l16) * SLD + I * PB + lg;
+  d4 re, im, re2 = {0, 0, 0, 0}, im2 = {0, 0, 0, 0};  // four chains: an MFMA's result takes two slots
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    re[r] = col[4 * r].x;
+    im[r] = col[4 * r].y;
+  }
+#pragma unroll
+  for (int t = 0; t < 4; ++t) {
+    const zd* k = m.S + (p * PB + 4 * t + lg) * SLD + l16;
+    const zd a = k[I * PB], b = k[J * PB];
+    re = __builtin_amdgcn_mfma_f64_16x16x4f64(-a.x, b.x, re, 0, 0, 0);
+    im = __builtin_amdgcn_mfma_f64_16x16x4f64(-a.y, b.x, im, 0, 0, 0);
+    re2 = __builtin_amdgcn_mfma_f64_16x16x4f64(-a.y, b.y, re2, 0, 0, 0);
+    im2 = __builtin_amdgcn_mfma_f64_16x16x4f64(a.x, b.y, im2, 0, 0, 0);
+  }
+#pragma unroll
+  for (int r = 0; r < 4; ++r) col[4 * r] = make_double2(re[r] + re2[r], im[r] + im2[r]);
+}
+
+// Inverse of diagonal block p by one wave, rd the reciprocals of L's diagonal:
+// lane c % 16 substitutes forward for column c, columns of L being broadcast
+// reads.
+__device__ __forceinline__ void invert16(Block64& m, const zd* rd, int p) {
+  const int lane = threadIdx.x & 63, c = lane & 15, p0 = p * PB;
+  zd x[PB];
+#pragma unroll
+  for (int r = 0; r < PB; ++r) x[r] = make_double2(r == c ? 1.0 : 0.0, 0.0);
+  int o = 0;
+#pragma unroll
+  for (int k = 0; k < PB; ++k) {
+    const zd d = rd[p0 + k], t = x[k];
+    x[k] = make_double2(t.x * d.x - t.y * d.y, t.x * d.y + t.y * d.x);
+    // the reads' address waits for the step before: all of them at once would
+    // not fit the registers
+    if (k > 0) asm volatile("" : "+v"(o) : "v"(__double2loint(x[k - 1].x)));
+    const zd* col = m.S + (p0 + k) * SLD + p0 + o;
+#pragma unroll
+    for (int r = k + 1; r < PB; ++r) {
+      x[r] = sub_mul(x[r], x[k], col[r]);
+    }
+  }
+  if (lane < 16) {
+#pragma unroll
+    for (int r = 0; r < PB; ++r) {
+      if (r > c) m.S[(p0 + r) * SLD + p0 + c] = x[r];
+      if (r == c) m.Xd[p0 + c] = x[r];
+    }
+  }
+}
+
+// Block (I, J), I > J, of inv(L) by one wave: X_IJ = -X_II sum_{K=J}^{I-1} L_IK
+// X_KJ.  The matrix cores leave the sum in the layout their next product takes
+// as its right operand, so it never leaves the registers.
+struct Sum16 {
+  d4 re, im;
+};
+__device__ __forceinline__ Sum16 offdiag_sum(const Block64& m, int I, int J) {
+  const int l16 = threadIdx.x & 15, lg = (threadIdx.x >> 4) & 3;
+  const zd zero = make_double2(0.0, 0.0);
+  d4 tr = {0, 0, 0, 0}, ti = {0, 0, 0, 0}, t2 = {0, 0, 0, 0}, t3 = {0, 0, 0, 0};
+  for (int K = J; K < I; ++K) {
+    zd a[4], b[4];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      const int k = 4 * t + lg;
+      a[t] = m.S[(K * PB + k) * SLD + I * PB + l16];
+      b[t] = m.S[(K * PB + k) * SLD + J * PB + l16];
+      if (K == J) b[t] = pick(k == l16, m.Xd[J * PB + k], pick(k > l16, b[t], zero));
+    }
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      tr = __builtin_amdgcn_mfma_f64_16x16x4f64(a[t].x, b[t].x, tr, 0, 0, 0);
+      ti = __builtin_amdgcn_mfma_f64_16x16x4f64(a[t].x, b[t].y, ti, 0, 0, 0);
+      t2 = __builtin_amdgcn_mfma_f64_16x16x4f64(-a[t].y, b[t].y, t2, 0, 0, 0);
+      t3 = __builtin_amdgcn_mfma_f64_16x16x4f64(a[t].y, b[t].x, t3, 0, 0, 0);
+    }
+  }
+  return {tr + t2, ti + t3};
+}
+__device__ __forceinline__ void offdiag_finish(Block64& m, int I, int J, const Sum16& s) {
+  const int l16 = threadIdx.x & 15, lg = (threadIdx.x >> 4) & 3;
+  const zd zero = make_double2(0.0, 0.0);
+  d4 xr = {0, 0, 0, 0}, xi = {0, 0, 0, 0}, x2 = {0, 0, 0, 0}, x3 = {0, 0, 0, 0};
+  zd a[4];
+#pragma unroll
+  for (int t = 0; t < 4; ++t) {
+    const int k = 4 * t + lg;
+    a[t] = m.S[(I * PB + l16) * SLD + I * PB + k];
+    a[t] = pick(k == l16, m.Xd[I * PB + k], pick(k < l16, a[t], zero));
+  }
+#pragma unroll
+  for (int t = 0; t < 4; ++t) {
+    xr = __builtin_amdgcn_mfma_f64_16x16x4f64(-a[t].x, s.re[t], xr, 0, 0, 0);
+    xi = __builtin_amdgcn_mfma_f64_16x16x4f64(-a[t].x, s.im[t], xi, 0, 0, 0);
+    x2 = __builtin_amdgcn_mfma_f64_16x16x4f64(a[t].y, s.im[t], x2, 0, 0, 0);
+    x3 = __builtin_amdgcn_mfma_f64_16x16x4f64(-a[t].y, s.re[t], x3, 0, 0, 0);
+  }
+#pragma unroll
+  for (int r = 0; r < 4; ++r)
+    m.S[(I * PB + lg + 4 * r) * SLD + J * PB + l16] = make_double2(xr[r] + x2[r], xi[r] + x3[r]);
+}
+
+// lower triangle of the n x n block at A (padded with the identity) into LDS,
+// all loads in flight before the first store; zeros above the diagonal
+__device__ __forceinline__ void load_lower(Block64& m, const zd* A, int64_t lda, int n) {
+  zd v[NB * NB / 256];
+#pragma unroll
+  for (int q = 0; q < NB * NB / 256; ++q) {
+    const int e = threadIdx.x + 256 * q, r = e & (NB - 1), c = e >> 6;
+    v[q] = make_double2((r == c && r >= n) ? 1.0 : 0.0, 0.0);
+    if (r < n && c < n && r >= c) v[q] = A[r + (int64_t)c * lda];
+  }
+#pragma unroll
+  for (int q = 0; q < NB * NB / 256; ++q) {
+    const int e = threadIdx.x + 256 * q, r = e & (NB - 1), c = e >> 6;
+    m.S[c * SLD + r] = v[q];
+  }
+}
+__device__ __forceinline__ void store_inverse(const Block64& m, int n, zd* Dinv, int64_t ldi) {
+  for (int e = threadIdx.x; e < NB * NB; e += 256) {
+    const int r = e & (NB - 1), c = e >> 6;
+    if (r < n && c < n)
+      Dinv[r + (int64_t)c * ldi] =
+          pick(r > c, m.S[r * SLD + c], pick(r == c, m.Xd[r], make_double2(0.0, 0.0)));
+  }
+}
+
+// Factor the n x n (n <= 64) diagonal block at M (lower triangle read), write
+// L back (upper part of the block zeroed) and inv(L) to Dinv.  A chain of 64
+// columns, bound by its latency: wave 0 factors 16-wide panels of all rows in
+// registers; wave 1 runs the same chain on the panel's diagonal block and, below
+// it, on the rows of the unit matrix, which become the block's inverse
+// (conjugate-transposed); waves 2 and 3 meanwhile apply the previous panel
+// beyond the next one and build inv(L)'s blocks below the diagonal on the
+// matrix cores as their parts become known.  27-30 us, 11.8 of them the four
+// panels' vector instructions (76-81 us when one wave went through the LDS for
+// every column and the panels below and the inverse followed in turn); 3001 x
+// 3001 factorisation 5.8 -> 3.5 ms.
+// Entries past n are the identity, so a ragged block needs no special case.
+// A non-positive or non-finite pivot is recorded in *info (atomic min of the
+// 1-based global index) and replaced by 1 so the kernel always finishes.
 __global__ __launch_bounds__(256) void k_potrf_block(zd* M, int64_t ldm, int n, zd* Dinv,
                                                      int64_t ldi, int* info, int goff) {
-  extern __shared__ double potrf_lds[];
-  zd* S = reinterpret_cast<zd*>(potrf_lds);  // L, S[c * SLD + r], r >= c
-  zd* Xd = S + NB * SLD;                     // diagonal of inv(L)
-  // entry (i, j), i >= j, of inv(L)
-  auto X = [&](int i, int j) -> zd& { return (i == j) ? Xd[i] : S[i * SLD + j]; };
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  {
-    // all sixteen loads in flight before the first LDS store
-    zd v[NB * NB / 256];
-#pragma unroll
-    for (int q = 0; q < NB * NB / 256; ++q) {
-      const int e = tid + 256 * q, r = e & (NB - 1), c = e >> 6;
-      v[q] = make_double2((r == c && (r >= n || c >= n)) ? 1.0 : 0.0, 0.0);
-      if (r < n && c < n && r >= c) v[q] = M[r + (int64_t)c * ldm];
-    }
-#pragma unroll
-    for (int q = 0; q < NB * NB / 256; ++q) {
-      const int e = tid + 256 * q, r = e & (NB - 1), c = e >> 6;
-      S[c * SLD + r] = v[q];  // zeros above the diagonal: inv(L)'s entries go there later
-    }
-  }
+  extern __shared__ double block_lds[];
+  Block64& m = *reinterpret_cast<Block64*>(block_lds);
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  load_lower(m, M, ldm, n);
   __syncthreads();
-  for (int p0 = 0; p0 < NB; p0 += PB) {
-    if (wave == 0) {
-      // lane: row r of the diagonal block, columns cg + 4m (m = 0..3)
-      const int r = lane & 15, cg = lane >> 4;
-      for (int j = 0; j < PB; ++j) {
-        const int gj = p0 + j;
-        zd* colj = S + gj * SLD + p0;
-        double d = colj[j].x;
-        const bool bad = !(d > 0.0) || !isfinite(d);
-        if (bad) d = 1.0;
-        if (lane == 0 && bad && gj < n) atomicMin(info, goff + gj + 1);
-        const double ljj = sqrt(d), il = 1.0 / ljj;
-        if (cg == (j & 3)) {
-          if (r == j) {
-            colj[r] = make_double2(ljj, 0.0);
-          } else if (r > j) {
-            const zd v = colj[r];
-            colj[r] = make_double2(v.x * il, v.y * il);
-          }
-        }
-        __builtin_amdgcn_wave_barrier();
-        const zd lr = colj[r];  // L(r, j)
+  Sum16 s30 = {}, s31 = {};
+  for (int p = 0; p < 4; ++p) {
+    const int p0 = p * PB;
+    zd a[PB];
+    const int i = lane - PB;  // wave 1: row of the unit matrix
+    if (wave < 2) {
+      const int row = wave == 0 ? lane : p0 + (lane & 15);
 #pragma unroll
-        for (int m = 0; m < 4; ++m) {
-          const int c = cg + 4 * m;
-          if (c > j && c <= r) {
-            const zd t = zmulc(lr, colj[c]);
-            zd* a = S + (p0 + c) * SLD + p0 + r;
-            const zd v = *a;
-            *a = make_double2(v.x - t.x, v.y - t.y);
-          }
-        }
-        __builtin_amdgcn_wave_barrier();
-      }
-      // inverse of the diagonal block: right-looking forward substitution on
-      // L11 X = I for the lane's four columns
-      zd x[4];
-#pragma unroll
-      for (int m = 0; m < 4; ++m) x[m] = make_double2((cg + 4 * m == r) ? 1.0 : 0.0, 0.0);
-      for (int k = 0; k < PB; ++k) {
-        zd* colk = S + (p0 + k) * SLD + p0;
-        if (r == k) {
-          const double il = 1.0 / colk[k].x;
-#pragma unroll
-          for (int m = 0; m < 4; ++m) {
-            x[m] = make_double2(x[m].x * il, x[m].y * il);
-            if (cg + 4 * m <= k) X(p0 + k, p0 + cg + 4 * m) = x[m];  // row k, lower part
-          }
-        }
-        __builtin_amdgcn_wave_barrier();
-        if (r > k) {
-          const zd lrk = colk[r];
-#pragma unroll
-          for (int m = 0; m < 4; ++m) {
-            const zd xk = (cg + 4 * m <= k) ? X(p0 + k, p0 + cg + 4 * m) : make_double2(0.0, 0.0);
-            const zd t = make_double2(lrk.x * xk.x - lrk.y * xk.y, lrk.x * xk.y + lrk.y * xk.x);
-            x[m] = make_double2(x[m].x - t.x, x[m].y - t.y);
-          }
-        }
-        __builtin_amdgcn_wave_barrier();
+      for (int c = 0; c < PB; ++c) {
+        a[c] = pick(wave == 1 && i >= 0, make_double2(c == i ? 1.0 : 0.0, 0.0), m.S[(p0 + c) * SLD + row]);
       }
     }
     __syncthreads();
-    const int R = NB - p0 - PB;  // rows below the panel
-    if (R > 0) {
-      // L21 = A21 inv(L11)^H: entry (row, c) = sum_{k <= c} A21(row, k) conj(X11(c, k))
-      zd v[3];
+    if (wave < 2) {
+      const int bad = panel16(a, wave == 0 ? p0 : 0, wave == 0 ? m.S + p0 * SLD : m.T, wave == 0 ? SLD : TLD,
+                              wave == 0 ? lane : min(lane, TLD - 1));
+      if (threadIdx.x == 0 && bad != INT_MAX && p0 + bad < n) atomicMin(info, goff + p0 + bad + 1);
+    } else if (p == 1) {  // blocks right of panel 1 by panel 0
+      update16(m, wave, 2, 0);
+      if (wave == 3) update16(m, 3, 3, 0);
+    } else if (p == 2) {
+      if (wave == 2) update16(m, 3, 3, 1);
+      else offdiag_finish(m, 1, 0, offdiag_sum(m, 1, 0));
+    } else if (p == 3) {
+      const int J = wave - 2;
+      offdiag_finish(m, 2, J, offdiag_sum(m, 2, J));
+      if (wave == 2) s30 = offdiag_sum(m, 3, 0);
+      else s31 = offdiag_sum(m, 3, 1);
+    }
+    __syncthreads();
+    if (wave == 1 && i >= 0 && i < PB) {  // X(c, i) = conj of entry c of row i
 #pragma unroll
-      for (int q = 0; q < 3; ++q) {
-        const int e = tid + 256 * q;
-        v[q] = make_double2(0.0, 0.0);
-        if (e < R * PB) {
-          const int row = p0 + PB + e % R, c = e / R;
-          for (int k = 0; k <= c; ++k) {
-            const zd t = zmulc(S[(p0 + k) * SLD + row], X(p0 + c, p0 + k));
-            v[q].x += t.x;
-            v[q].y += t.y;
-          }
-        }
+      for (int c = 0; c < PB; ++c) {
+        const zd x = make_double2(a[c].x, -a[c].y);
+        if (c > i) m.S[(p0 + c) * SLD + p0 + i] = x;
+        if (c == i) m.Xd[p0 + c] = x;
       }
-      __syncthreads();
-#pragma unroll
-      for (int q = 0; q < 3; ++q) {
-        const int e = tid + 256 * q;
-        if (e < R * PB) S[(p0 + e / R) * SLD + p0 + PB + e % R] = v[q];
-      }
-      __syncthreads();
-      // trailing lower triangle: A22 -= L21 L21^H
-      for (int e = tid; e < R * R; e += 256) {
-        const int rr = p0 + PB + e % R, cc = p0 + PB + e / R;
-        if (rr < cc) continue;
-        zd acc = S[cc * SLD + rr];
+    }
+    if (p < 3 && wave != 1) {  // the next panel's columns: three, two, one blocks
+      const int I = p + 1 + (wave == 0 ? 0 : wave - 1);
+      if (I < 4) update16(m, I, p + 1, p);
+    }
+    __syncthreads();
+  }
+  if (wave == 2) offdiag_finish(m, 3, 0, s30);
+  else if (wave == 3) offdiag_finish(m, 3, 1, s31);
+  else if (wave == 0) offdiag_finish(m, 3, 2, offdiag_sum(m, 3, 2));
+  __syncthreads();
+  // L and inv(L), both from the LDS
 #pragma unroll 4
-        for (int k = 0; k < PB; ++k) {
-          const zd t = zmulc(S[(p0 + k) * SLD + rr], S[(p0 + k) * SLD + cc]);
-          acc.x -= t.x;
-          acc.y -= t.y;
-        }
-        S[cc * SLD + rr] = acc;
-      }
-      __syncthreads();
-    }
-  }
-  // off-diagonal blocks of inv(L), block row I = 1..3
-  for (int I = 1; I < NB / PB; ++I) {
-    // T_IJ = sum_{K=J}^{I-1} L_IK X_KJ, into X's block (I, J)
-    zd v[3];
-#pragma unroll
-    for (int q = 0; q < 3; ++q) {
-      const int e = tid + 256 * q;
-      v[q] = make_double2(0.0, 0.0);
-      if (e < I * PB * PB) {
-        const int J = e >> 8, r = e & 15, c = (e >> 4) & 15;
-        const int row = I * PB + r, col = J * PB + c;
-        for (int k = J * PB + c; k < I * PB; ++k) {  // X(k, col) = 0 for k < col
-          const zd l = S[k * SLD + row], xk = X(k, col);
-          v[q].x += l.x * xk.x - l.y * xk.y;
-          v[q].y += l.x * xk.y + l.y * xk.x;
-        }
-      }
-    }
-#pragma unroll
-    for (int q = 0; q < 3; ++q) {
-      const int e = tid + 256 * q;
-      if (e < I * PB * PB) {
-        const int J = e >> 8, r = e & 15, c = (e >> 4) & 15;
-        X(I * PB + r, J * PB + c) = v[q];
-      }
-    }
-    __syncthreads();
-    // X_IJ = -X_II T_IJ (X_II lower triangular)
-#pragma unroll
-    for (int q = 0; q < 3; ++q) {
-      const int e = tid + 256 * q;
-      v[q] = make_double2(0.0, 0.0);
-      if (e < I * PB * PB) {
-        const int J = e >> 8, r = e & 15, c = (e >> 4) & 15;
-        const int row = I * PB + r, col = J * PB + c;
-        for (int k = 0; k <= r; ++k) {
-          const zd xi = X(row, I * PB + k), t = X(I * PB + k, col);
-          v[q].x -= xi.x * t.x - xi.y * t.y;
-          v[q].y -= xi.x * t.y + xi.y * t.x;
-        }
-      }
-    }
-    __syncthreads();
-#pragma unroll
-    for (int q = 0; q < 3; ++q) {
-      const int e = tid + 256 * q;
-      if (e < I * PB * PB) {
-        const int J = e >> 8, r = e & 15, c = (e >> 4) & 15;
-        X(I * PB + r, J * PB + c) = v[q];
-      }
-    }
-    __syncthreads();
-  }
-  for (int e = tid; e < NB * NB; e += 256) {
-    const int r = e & (NB - 1), c = e >> 6;
+  for (int q = 0; q < NB * NB / 256; ++q) {
+    const int e = threadIdx.x + 256 * q, r = e & (NB - 1), c = e >> 6;
+    const zd zero = make_double2(0.0, 0.0);
+    const zd l = pick(r >= c, m.S[c * SLD + r], zero);
+    const zd x = pick(r > c, m.S[r * SLD + c], pick(r == c, m.Xd[r], zero));
     if (r < n && c < n) {
-      M[r + (int64_t)c * ldm] = (r >= c) ? S[c * SLD + r] : make_double2(0.0, 0.0);
-      Dinv[r + (int64_t)c * ldi] = (r >= c) ? X(r, c) : make_double2(0.0, 0.0);
+      M[r + (int64_t)c * ldm] = l;
+      Dinv[r + (int64_t)c * ldi] = x;
     }
   }
 }
 
-// inverse of the n x n (n <= 64) lower-triangular block at L into Dinv
-__global__ __launch_bounds__(256) void k_trtri_block(const zd* L, int64_t ldl, int64_t ntot, zd* Dinv,
+// inverse of the lower-triangular 64 x 64 diagonal blocks of L (the last one
+// ragged) into Dinv, one work-group each: the four 16 x 16 diagonal blocks at
+// once, then the blocks below them (a barrier per column before: 85 us at 15
+// blocks).
+__global__ __launch_bounds__(256, 2) void k_trtri_block(const zd* L, int64_t ldl, int64_t ntot, zd* Dinv,
                                                      int64_t ldi) {
-  __shared__ zd S[NB][NB];
-  __shared__ zd xr[2][NB];
-  const int tid = threadIdx.x;
+  extern __shared__ double block_lds[];
+  Block64& m = *reinterpret_cast<Block64*>(block_lds);
+  const int wave = threadIdx.x >> 6;
   const int64_t off = (int64_t)blockIdx.x * NB;
   const int n = (int)((ntot - off) < NB ? (ntot - off) : NB);
-  const zd* Lb = L + off + off * ldl;
-  for (int e = tid; e < NB * NB; e += 256) {
-    const int i = e & (NB - 1), j = e >> 6;
-    S[j][i] = (i < n && j < n && i >= j) ? Lb[i + (int64_t)j * ldl] : make_double2(0.0, 0.0);
+  load_lower(m, L + off + off * ldl, ldl, n);
+  __syncthreads();
+  if (threadIdx.x < NB) {
+    const zd d = m.S[threadIdx.x * SLD + threadIdx.x];
+    const double q = d.x * d.x + d.y * d.y;
+    m.T[threadIdx.x] = make_double2(d.x / q, -d.y / q);
   }
   __syncthreads();
-  reg_inverse_to(S, xr, n, Dinv + off, ldi);
+  invert16(m, m.T, wave);
+  __syncthreads();
+  for (int I = wave + 1; I < 4; ++I) offdiag_finish(m, I, wave, offdiag_sum(m, I, wave));
+  __syncthreads();
+  store_inverse(m, n, Dinv + off, ldi);
 }
 
 __global__ void k_zero_upper(zd* M, int64_t ldm, int64_t n) {
@@ -338,11 +381,11 @@ gevp_status potrf_leaf(gevp_ctx* c, int64_t n, zd* M, int64_t ldm, zd* Dinv, int
                        int64_t goff) {
   static const bool attr = [] {
     (void)hipFuncSetAttribute((const void*)k_potrf_block, hipFuncAttributeMaxDynamicSharedMemorySize,
-                              (int)POTRF_LDS);
+                              (int)sizeof(Block64));
     return true;
   }();
   (void)attr;
-  hipLaunchKernelGGL(k_potrf_block, dim3(1), dim3(256), POTRF_LDS, c->stream, M, ldm, (int)n, Dinv,
+  hipLaunchKernelGGL(k_potrf_block, dim3(1), dim3(256), sizeof(Block64), c->stream, M, ldm, (int)n, Dinv,
                      ldi, info, (int)goff);
   GEVP_HIP_TRY(hipGetLastError());
   return GEVP_OK;
@@ -500,7 +543,13 @@ gevp_status chol_lower(gevp_ctx* c, int64_t n, zd* M, int64_t ldm, zd* Dinv, int
 gevp_status diag_block_inverses(gevp_ctx* c, int64_t n, const zd* L, int64_t ldl, zd* Dinv,
                                 int64_t ldi) {
   if (n <= 0) return GEVP_OK;
-  hipLaunchKernelGGL(k_trtri_block, dim3((unsigned)((n + NB - 1) / NB)), dim3(256), 0, c->stream, L,
+  static const bool attr = [] {
+    (void)hipFuncSetAttribute((const void*)k_trtri_block, hipFuncAttributeMaxDynamicSharedMemorySize,
+                              (int)sizeof(Block64));
+    return true;
+  }();
+  (void)attr;
+  hipLaunchKernelGGL(k_trtri_block, dim3((unsigned)((n + NB - 1) / NB)), dim3(256), sizeof(Block64), c->stream, L,
                      ldl, n, Dinv, ldi);
   GEVP_HIP_TRY(hipGetLastError());
   return GEVP_OK;
