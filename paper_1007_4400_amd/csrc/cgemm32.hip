@@ -11,6 +11,10 @@
 // LDS staging, XCD-aware tile order and three-real-product complex form
 // (P1 = Ar Gr, P2 = Ai Gi, P3 = (Ar + Ai)(Gr + Gi); Re = P1 - P2,
 // Im = P3 - P1 - P2) as the FP64 kernel; the accumulators are FP32.
+//
+// Split-K: with few output tiles the K range is cut over several work-groups
+// (split32), each writes its raw partial tile to the stream's split-K buffer
+// and a second kernel sums them in a fixed order and applies the epilogue.
 #include "common.h"
 
 typedef float f4 __attribute__((ext_vector_type(4)));
@@ -37,7 +41,32 @@ struct CgemmParams {
   const double* gamma;
   const double* delta;
   int tiles_n, total, remap;
+  int tiles, nks;  // output tiles; K slices per part
+  zf* part;        // split-K partial tiles [part][tile][col][row], or null
 };
+
+// D entry from its product, FP32 as the accumulators
+__device__ __forceinline__ void epilogue(const CgemmParams& p, int row, int col, float pr, float pi) {
+  const float al = (float)p.alpha[col], be = (float)p.beta[col];
+  const float ga = (float)p.gamma[col], de = (float)p.delta[col];
+  float vr = al * pr, vi = al * pi;
+  if (be != 0.f) {  // G(row, col) exists only for square products (the filter's)
+    const zf g = p.B[row + (int64_t)col * p.ldb];
+    vr += be * g.x;
+    vi += be * g.y;
+  }
+  if (ga != 0.f) {
+    const zf q = p.P[row + (int64_t)col * p.ldp];
+    vr += ga * q.x;
+    vi += ga * q.y;
+  }
+  if (de != 0.f) {
+    const zf q = p.R[row + (int64_t)col * p.ldr];
+    vr += de * q.x;
+    vi += de * q.y;
+  }
+  p.D[row + (int64_t)col * p.ldd] = make_float2(vr, vi);
+}
 
 __global__ __launch_bounds__(NTHR, 2) void k_cgemm32_filter(CgemmParams p) {
   __shared__ zf As[2][KT][PADA];
@@ -48,7 +77,8 @@ __global__ __launch_bounds__(NTHR, 2) void k_cgemm32_filter(CgemmParams p) {
     const int per = p.total >> 3;
     L = (L & 7) * per + (L >> 3);
   }
-  const int tm = L / p.tiles_n, tn = L - tm * p.tiles_n;
+  const int kc = L / p.tiles, tile = L - kc * p.tiles;
+  const int tm = tile / p.tiles_n, tn = tile - tm * p.tiles_n;
   const int row0 = tm * BM, col0 = tn * BN;
   const int lane = tid & 63, wave = tid >> 6;
   const int wr = wave >> 1, wc = wave & 1;
@@ -87,14 +117,15 @@ __global__ __launch_bounds__(NTHR, 2) void k_cgemm32_filter(CgemmParams p) {
     for (int i = 0; i < 4; ++i) Bs[buf][k][(tid >> 4) + 16 * i] = rb[i];
   };
   const int nk = (p.K + KT - 1) / KT;
-  if (nk > 0) {
-    load(0);
+  const int t0 = kc * p.nks, t1 = min(nk, t0 + p.nks);
+  if (t0 < t1) {
+    load(t0 * KT);
     store(0);
   }
   __syncthreads();
-  for (int t = 0; t < nk; ++t) {
-    const int cur = t & 1;
-    if (t + 1 < nk) load((t + 1) * KT);
+  for (int t = t0; t < t1; ++t) {
+    const int cur = (t - t0) & 1;
+    if (t + 1 < t1) load((t + 1) * KT);
 #pragma unroll
     for (int ks = 0; ks < KT / 4; ++ks) {
       const int kk = ks * 4 + lg;
@@ -126,7 +157,7 @@ __global__ __launch_bounds__(NTHR, 2) void k_cgemm32_filter(CgemmParams p) {
         for (int j = 0; j < 2; ++j)
           acc3[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(sa[i], sb[j], acc3[i][j], 0, 0, 0);
     }
-    if (t + 1 < nk) store(cur ^ 1);
+    if (t + 1 < t1) store(cur ^ 1);
     __syncthreads();
   }
   f4 accR[2][2], accI[2][2];  // the complex result of the three products
@@ -138,37 +169,72 @@ __global__ __launch_bounds__(NTHR, 2) void k_cgemm32_filter(CgemmParams p) {
       accI[i][j] = acc3[i][j] - acc1[i][j] - acc2[i][j];
     }
   // D layout of v_mfma_f32_16x16x4f32: lane l, register r -> row 4 (l/16) + r, col l%16
+  if (p.part) {
+    zf* pt = p.part + ((int64_t)kc * p.tiles + tile) * (BM * BN);
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          pt[(wc * 32 + j * 16 + l16) * BM + wr * 32 + i * 16 + 4 * lg + r] =
+              make_float2(accR[i][j][r], accI[i][j][r]);
+    return;
+  }
 #pragma unroll
   for (int i = 0; i < 2; ++i)
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
       const int col = col0 + wc * 32 + j * 16 + l16;
       if (col >= p.N) continue;
-      const float al = (float)p.alpha[col], be = (float)p.beta[col];
-      const float ga = (float)p.gamma[col], de = (float)p.delta[col];
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int row = row0 + wr * 32 + i * 16 + 4 * lg + r;
-        if (row >= p.M) continue;
-        float vr = al * accR[i][j][r], vi = al * accI[i][j][r];
-        if (be != 0.f) {  // G(row, col) exists only for square products (the filter's)
-          const zf g = p.B[row + (int64_t)col * p.ldb];
-          vr += be * g.x;
-          vi += be * g.y;
-        }
-        if (ga != 0.f) {
-          const zf q = p.P[row + (int64_t)col * p.ldp];
-          vr += ga * q.x;
-          vi += ga * q.y;
-        }
-        if (de != 0.f) {
-          const zf q = p.R[row + (int64_t)col * p.ldr];
-          vr += de * q.x;
-          vi += de * q.y;
-        }
-        p.D[row + (int64_t)col * p.ldd] = make_float2(vr, vi);
+        if (row < p.M) epilogue(p, row, col, accR[i][j][r], accI[i][j][r]);
       }
     }
+}
+
+// sum of the partial tiles in part order, then the epilogue; one thread per
+// entry, consecutive threads on consecutive rows
+__global__ __launch_bounds__(256) void k_cgemm32_reduce(CgemmParams p, int parts) {
+  const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  constexpr int PER = BM * BN;
+  if (e >= (int64_t)p.tiles * PER) return;
+  const int tile = (int)(e / PER), w = (int)(e - (int64_t)tile * PER);
+  const int tm = tile / p.tiles_n, tn = tile - tm * p.tiles_n;
+  const int row = tm * BM + (w & (BM - 1)), col = tn * BN + w / BM;
+  if (row >= p.M || col >= p.N) return;
+  const zf* src = p.part + e;
+  const int64_t st = (int64_t)p.tiles * PER;
+  float sr = 0.f, si = 0.f;
+  for (int q = 0; q < parts; ++q) {
+    const zf v = src[q * st];
+    sr += v.x;
+    si += v.y;
+  }
+  epilogue(p, row, col, sr, si);
+}
+
+// Parts of nk K-slices for T tiles when `slots` work-groups run at once: a
+// slice costs 1, the second kernel 3 and its reads 0.005 a partial tile; at
+// least four slices a part.  Measured at 1001 x 116 x 1001 (32 tiles, 63
+// slices): one work-group per tile 92 us, cut 14.5 + 7 us.
+inline int split32(int64_t T, int nk, int64_t slots, int64_t max_parts) {
+  int best = 1;
+  double cost = (double)((T + slots - 1) / slots) * nk;
+  for (int s = 2; s <= 16; ++s) {
+    const int nks = (nk + s - 1) / s;
+    if (nks < 4) break;
+    const int se = (nk + nks - 1) / nks;
+    if (T * se > max_parts) break;
+    const double c = (double)((T * se + slots - 1) / slots) * nks + 3.0 + 0.005 * (double)(T * se);
+    if (c < 0.95 * cost) {
+      best = se;
+      cost = c;
+    }
+  }
+  return best;
 }
 
 // FP64 complex -> FP32 complex copy of an n x n matrix (column-major)
@@ -244,9 +310,27 @@ gevp_status launch_cgemm32_filter(gevp_ctx* c, int64_t m, int64_t n, int64_t k, 
   p.delta = de;
   p.tiles_n = (int)((n + BN - 1) / BN);
   const int64_t total = ((m + BM - 1) / BM) * p.tiles_n;
-  p.total = (int)total;
-  p.remap = (total % 8 == 0 && total >= 64) ? 1 : 0;
-  hipLaunchKernelGGL(k_cgemm32_filter, dim3((unsigned)total), dim3(NTHR), 0, c->stream, p);
+  const int nk = (p.K + KT - 1) / KT;
+  constexpr int64_t MAX_PARTS = (int64_t)(SKW_BYTES / (sizeof(zf) * BM * BN));
+  int parts = c->no_split ? 1
+                          : split32(total, nk, std::max<int64_t>(1, 2 * (int64_t)gevp_device_cus(c->device) /
+                                                                        std::max(1, c->cu_div)),
+                                    MAX_PARTS);
+  p.part = nullptr;
+  if (parts > 1) {
+    void* buf = nullptr;
+    GEVP_TRY(splitk_buffer(c, (size_t)parts * total * BM * BN * sizeof(zf), &buf));
+    p.part = (zf*)buf;
+  }
+  p.tiles = (int)total;
+  p.nks = nk > 0 ? (nk + parts - 1) / parts : 1;
+  const int64_t blocks = total * parts;
+  p.total = (int)blocks;
+  p.remap = (blocks % 8 == 0 && blocks >= 64) ? 1 : 0;
+  hipLaunchKernelGGL(k_cgemm32_filter, dim3((unsigned)blocks), dim3(NTHR), 0, c->stream, p);
+  if (parts > 1)
+    hipLaunchKernelGGL(k_cgemm32_reduce, dim3((unsigned)(total * BM * BN / 256)), dim3(256), 0, c->stream, p,
+                       parts);
   GEVP_HIP_TRY(hipGetLastError());
   return GEVP_OK;
 }

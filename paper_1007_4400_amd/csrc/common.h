@@ -181,6 +181,8 @@ gevp_status mod_prepare(gevp_ctx* c, int64_t m, int64_t k, int opA, const zd* A,
 // flags, raised when the product was left to the FP64 kernels
 gevp_status launch_mod_gemm(gevp_ctx* c, const ModGemmCall& g, void* scratch, const int** flag1,
                             const int** flag2);
+// the stream's split-K buffer (SKW_BYTES, allocated on first use)
+gevp_status splitk_buffer(gevp_ctx* c, size_t need, void** out);
 // scratch of at least `bytes` for the next product on c's stream, or null
 void* mod_scratch(gevp_ctx* c, size_t bytes);
 

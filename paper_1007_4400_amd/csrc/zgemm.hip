@@ -510,6 +510,25 @@ int zgemm_splits(int64_t T, int nk, int64_t slots, int64_t max_parts) {
 }
 }  // namespace
 
+gevp_status splitk_buffer(gevp_ctx* c, size_t need, void** out) {
+  if (need > c->skw_bytes) {
+    if (c->ext) return GEVP_ERR_WORKSPACE;  // caller-owned memory is never reallocated
+    if (c->skw) {
+      GEVP_HIP_TRY(hipStreamSynchronize(c->stream));  // earlier launches may still read it
+      GEVP_HIP_TRY(hipFree(c->skw));
+      c->skw = nullptr;
+      c->skw_bytes = 0;
+    }
+    if (need > SKW_BYTES || hipMalloc(&c->skw, SKW_BYTES) != hipSuccess) {
+      c->skw = nullptr;
+      return GEVP_ERR_ALLOC;
+    }
+    c->skw_bytes = SKW_BYTES;
+  }
+  *out = c->skw;
+  return GEVP_OK;
+}
+
 void* mod_scratch(gevp_ctx* c, size_t bytes) {
   // under capture nothing may be allocated and no event of this handle may be
   // tied to the graph: the FP64 kernels alone
@@ -626,23 +645,9 @@ gevp_status launch_zgemm(gevp_ctx* c, int opA, int opB, int64_t m, int64_t n, in
   p.splits = nk > 0 ? (nk + p.nks - 1) / p.nks : 1;
   p.part = nullptr;
   if (p.splits > 1) {
-    const size_t need = (size_t)p.splits * total * BM * BN * sizeof(zd);
-    if (need > c->skw_bytes) {
-      if (c->ext) return GEVP_ERR_WORKSPACE;  // caller-owned memory is never reallocated
-      if (c->skw) {
-        GEVP_HIP_TRY(hipStreamSynchronize(c->stream));  // earlier launches may still read it
-        GEVP_HIP_TRY(hipFree(c->skw));
-        c->skw = nullptr;
-        c->skw_bytes = 0;
-      }
-      const size_t cap = (size_t)SPLIT_TILES_MAX * BM * BN * sizeof(zd);
-      if (hipMalloc(&c->skw, cap) != hipSuccess) {
-        c->skw = nullptr;
-        return GEVP_ERR_ALLOC;
-      }
-      c->skw_bytes = cap;
-    }
-    p.part = (zd*)c->skw;
+    void* buf = nullptr;
+    GEVP_TRY(splitk_buffer(c, (size_t)p.splits * total * BM * BN * sizeof(zd), &buf));
+    p.part = (zd*)buf;
   }
   const int64_t blocks = total * p.splits;
   p.total = (int)blocks;
