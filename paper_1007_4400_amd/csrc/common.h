@@ -77,6 +77,9 @@ struct gevp_ctx {
   // false for the worker contexts of gevp_solve_batched: problems already run
   // concurrently there, so a solve keeps all its work on its own stream
   bool inner_streams = true;
+  // other work shares the GPU with this stream (batched workers, the second
+  // stream): no launch that must have all its work-groups resident at once
+  bool shared_gpu = false;
   // panel stream of the Cholesky factorisation and its two events (on demand)
   gevp_ctx* panel = nullptr;
   hipEvent_t pev[2] = {nullptr, nullptr};

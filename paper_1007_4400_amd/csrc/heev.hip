@@ -1,8 +1,8 @@
 // Small dense Hermitian eigensolver for the Rayleigh-Ritz step (n up to a few
 // thousand), all on the GPU in FP64:
 //
-//  1. Householder tridiagonalisation H = U T U^H, one fused kernel per
-//     reflector.  Kernel s finishes the rank-2 update of reflector s-1 on the
+//  1. Householder tridiagonalisation H = U T U^H, whole in one launch that
+//     keeps H in registers, or one fused kernel per reflector.  Step s finishes the rank-2 update of reflector s-1 on the
 //     columns it owns, forms reflector s from column s (which every
 //     work-group reconstructs redundantly from the old column and the
 //     previous reflector, so no extra grid-wide barrier is needed), and
@@ -18,6 +18,7 @@
 //     diag(1/tau) plus the strict upper triangle of V^H V, so Z <- Z - V (T
 //     (V^H Z)) is a Gram product, a triangular solve and two products on the
 //     FP64 matrix cores.
+#include <atomic>
 #include <cfloat>
 
 #include "common.h"
@@ -219,6 +220,465 @@ __global__ __launch_bounds__(HT) void k_hetrd_step(TrdArgs a, int s) {
   __shared__ double sh[8];
   __shared__ zd bc[4];
   hetrd_body(a, s, reinterpret_cast<zd*>(sm), sh, bc);
+}
+
+// ---- the whole tridiagonalisation in one launch
+//
+// A wave owns whole columns of H and keeps them in registers (lane l holds rows
+// l, l + 64, ...), so H is read once and never written.  What a step exchanges
+// is small: every column's owner publishes p_s(j), and the owner of column s +
+// 1 that column as it stands, which is all a wave needs to form the next
+// reflector by itself, exactly as every other wave forms it (the same operations
+// in the same order).  One exchange per reflector, no other communication.
+
+// sum over the wave, the same in every lane: within rows of 16 lanes, then
+// across the rows, by lane shifts of the vector unit
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_move(double v) {
+  const unsigned long long u = __double_as_longlong(v);
+  const unsigned lo = __builtin_amdgcn_update_dpp(0, (unsigned)u, CTRL, ROWS, 0xf, true);
+  const unsigned hi = __builtin_amdgcn_update_dpp(0, (unsigned)(u >> 32), CTRL, ROWS, 0xf, true);
+  return __longlong_as_double(((unsigned long long)hi << 32) | lo);
+}
+__device__ __forceinline__ double wave_total(double v) {
+  v += dpp_move<0x111, 0xf>(v);  // row_shr 1, 2, 4, 8
+  v += dpp_move<0x112, 0xf>(v);
+  v += dpp_move<0x114, 0xf>(v);
+  v += dpp_move<0x118, 0xf>(v);
+  v += dpp_move<0x142, 0xa>(v);  // lane 15 of rows 0 and 2 to the next row
+  v += dpp_move<0x143, 0xc>(v);  // lane 31 to the upper half
+  const unsigned long long u = __double_as_longlong(v);
+  const unsigned lo = __builtin_amdgcn_readlane((unsigned)u, 63);
+  const unsigned hi = __builtin_amdgcn_readlane((unsigned)(u >> 32), 63);
+  return __longlong_as_double(((unsigned long long)hi << 32) | lo);
+}
+
+struct Reflector {
+  zd tau, scal, K, wps;  // K of the previous reflector and w_{s-1}(s)
+  double d, beta;
+};
+// Reflector s from column s as published (updated through reflector s - 2), p of
+// reflector s - 1 (rows >= s) and v_{s-1}, one row a lane: c becomes v_s, w
+// becomes w_{s-1}.
+__device__ __forceinline__ Reflector reflect(int s, int n, const zd* C, const zd* P, const zd* V, zd taup,
+                                             zd& c, zd& w) {
+  const int lane = threadIdx.x & 63;
+  const zd zero = make_double2(0.0, 0.0);
+  Reflector f;
+  f.K = f.wps = c = w = zero;
+  if (lane >= s && lane < n) c = C[lane];
+  zd cs = C[s], ca = zero;  // rows s and s + 1
+  if (s + 1 < n) ca = C[s + 1];
+  if (s > 0) {
+    zd v = zero;
+    if (lane >= s && lane < n) {
+      v = V[lane];
+      w = P[lane];
+    }
+    const double kr = v.x * w.x + v.y * w.y, ki = v.x * w.y - v.y * w.x;  // conj(v) p
+    const zd k2 = cmul(cconj(taup), make_double2(wave_total(kr), wave_total(ki)));
+    f.K = make_double2(0.5 * k2.x, 0.5 * k2.y);
+    // v_{s-1}(s) = 1
+    f.wps = make_double2(P[s].x - f.K.x, P[s].y - f.K.y);
+    const zd kv = cmul(f.K, v), t = cmul(v, cconj(f.wps));
+    w = make_double2(w.x - kv.x, w.y - kv.y);
+    c = make_double2(c.x - (t.x + w.x), c.y - (t.y + w.y));
+    cs.x -= 2.0 * f.wps.x;
+    if (s + 1 < n) {
+      const zd va = V[s + 1], ka = cmul(f.K, va), ta = cmul(va, cconj(f.wps));
+      ca.x -= ta.x + (P[s + 1].x - ka.x);
+      ca.y -= ta.y + (P[s + 1].y - ka.y);
+    }
+  }
+  f.d = cs.x;
+  const double sig = wave_total(lane >= s + 2 ? c.x * c.x + c.y * c.y : 0.0);
+  f.tau = f.scal = zero;
+  if (sig == 0.0 && ca.y == 0.0) {
+    f.beta = ca.x;
+  } else {
+    const double nrm = sqrt(ca.x * ca.x + ca.y * ca.y + sig);
+    f.beta = (ca.x >= 0.0) ? -nrm : nrm;
+    f.tau = make_double2((f.beta - ca.x) / f.beta, -ca.y / f.beta);
+    const zd den = make_double2(ca.x - f.beta, ca.y);  // scal = 1 / den
+    const double dd = den.x * den.x + den.y * den.y;
+    f.scal = make_double2(den.x / dd, -den.y / dd);
+  }
+  const zd x = cmul(c, f.scal);
+  c = make_double2(lane == s + 1 ? 1.0 : lane > s + 1 ? x.x : 0.0, lane > s + 1 ? x.y : 0.0);
+  return f;
+}
+
+// p_s(j) of one column h (row of the lane), after its update by reflector s - 1
+__device__ __forceinline__ zd column_step(int s, int j, const Reflector& f, const zd* P, const zd* V, zd vs,
+                                          zd w, zd& h) {
+  const int lane = threadIdx.x & 63;
+  if (s > 0) {
+    const zd vj = V[j], kv = cmul(f.K, vj), wj = make_double2(P[j].x - kv.x, P[j].y - kv.y);
+    const zd t1 = cmul(V[lane], cconj(wj)), t2 = cmul(w, cconj(vj));
+    if (lane >= s) h = make_double2(h.x - (t1.x + t2.x), h.y - (t1.y + t2.y));
+  }
+  // conj(h) v_s
+  return cmul(f.tau, make_double2(wave_total(h.x * vs.x + h.y * vs.y), wave_total(h.x * vs.y - h.y * vs.x)));
+}
+
+// n <= 60: one work-group of 16 waves, up to four columns a wave, the exchange
+// through the LDS and one barrier per reflector.
+constexpr int TRD1_MAX = 60;
+__global__ __launch_bounds__(1024) void k_hetrd_one(TrdArgs a) {
+  __shared__ zd P[2][64], C[2][64], V[2][64];
+  const int n = a.n, lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const zd zero = make_double2(0.0, 0.0);
+  zd h[4];
+#pragma unroll
+  for (int m = 0; m < 4; ++m) {
+    const int j = wave + 16 * m;
+    h[m] = zero;
+    if (lane < n && j < n) h[m] = a.H[lane + (int64_t)j * a.ldh];
+  }
+  if (threadIdx.x < 64) {
+    V[0][threadIdx.x] = V[1][threadIdx.x] = zero;
+    if ((int)threadIdx.x < n) C[0][threadIdx.x] = a.H[threadIdx.x];
+  }
+  __syncthreads();
+  zd taup = zero;
+  for (int s = 0; s < n; ++s) {
+    const int b = s & 1;
+    zd c, w;
+    const Reflector f = reflect(s, n, C[b], P[b], V[b], taup, c, w);
+    if (wave == 0) {
+      if (lane == 0) {
+        a.d[s] = f.d;
+        if (s < n - 1) {
+          a.tau[s] = f.tau;
+          a.e[s] = f.beta;
+        }
+      }
+      V[b ^ 1][lane] = c;
+      if (lane < n && s < n - 1) a.V[lane + (int64_t)s * a.ldv] = c;
+    }
+    if (s == n - 1) break;
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+      const int j = wave + 16 * m;
+      if (j <= s || j >= n) continue;
+      const zd p = column_step(s, j, f, P[b], V[b], c, w, h[m]);
+      if (lane == 0) P[b ^ 1][j] = p;
+      if (j == s + 1) C[b ^ 1][lane] = h[m];
+    }
+    taup = f.tau;
+    __syncthreads();
+  }
+}
+
+// 60 < n <= 2048: eight columns a work-group, a row of each in every thread (R
+// rows when there are more than threads), one launch.  The exchange
+// goes through device memory with accesses that are coherent over the XCDs by
+// themselves (agent-scope atomics of 8 bytes), every step into fresh memory that
+// was filled with a value no arithmetic produces: a reader polls the entries it
+// needs until they differ from it, so a step costs one trip from writer to reader
+// and no cache is written back or invalidated.  A work-group publishes its eight
+// p as one line of 128 bytes.  A wait that exceeds its bound raises *err and ends
+// the work-group (and with it, in time, the others); the host then takes the
+// launch per reflector.
+// Latency bounds it: of the 4.4 us a step takes at n = 948 about half is the way
+// of p through memory, the rest three sums over the work-group and eight columns
+// of FP64 arithmetic.  Measured whole, n = 256, 512, 948: 0.71, 1.82, 4.18 ms,
+// against 1.9, 4.1 and 8.8 ms for the launches per reflector.  One column a wave
+// and the reflector formed by every wave took 10 us a step at n = 948 (the reads
+// of p by 237 work-groups queue up); 256 threads instead of 512 4.9 us.
+constexpr int TRDM_MAX = 2048;
+constexpr unsigned long long HOLE = 0x7ff8a5c35a3cf00dull;  // a NaN with a payload of its own
+struct TrdExchange {
+  // step t: p_t, then column t + 1, each as n real and n imaginary parts (a wave's
+  // read is one contiguous piece) of ld entries
+  unsigned long long* x;
+  int64_t ld;
+  int* err;
+  int spin;               // polls before a wait gives up
+};
+__device__ __forceinline__ void publish(unsigned long long* dst, double v) {
+  unsigned long long u = __double_as_longlong(v);
+  u = u == HOLE ? 0x7ff8000000000000ull : u;
+  __hip_atomic_store(dst, u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ unsigned long long peek(const unsigned long long* src) {
+  return __hip_atomic_load(src, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__global__ __launch_bounds__(256) void k_trd_holes(unsigned long long* x, int64_t words, int* err) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i == 0) *err = 0;
+  for (int64_t k = i; k < words; k += (int64_t)gridDim.x * 256) x[k] = HOLE;
+}
+// Sums over the wave of 16 values a lane: the lane returns the total of value
+// 4 * (lane / 16) + (lane & 3).  The first two levels exchange halves of the
+// values as they add them, the last two rotate within rows of 16 lanes.
+__device__ __forceinline__ double2 swap_halves32(double a, double b) {
+  const unsigned long long ua = __double_as_longlong(a), ub = __double_as_longlong(b);
+  const auto lo = __builtin_amdgcn_permlane32_swap((unsigned)ua, (unsigned)ub, false, false);
+  const auto hi = __builtin_amdgcn_permlane32_swap((unsigned)(ua >> 32), (unsigned)(ub >> 32), false, false);
+  return make_double2(__longlong_as_double(((unsigned long long)hi[0] << 32) | lo[0]),
+                      __longlong_as_double(((unsigned long long)hi[1] << 32) | lo[1]));
+}
+__device__ __forceinline__ double2 swap_halves16(double a, double b) {
+  const unsigned long long ua = __double_as_longlong(a), ub = __double_as_longlong(b);
+  const auto lo = __builtin_amdgcn_permlane16_swap((unsigned)ua, (unsigned)ub, false, false);
+  const auto hi = __builtin_amdgcn_permlane16_swap((unsigned)(ua >> 32), (unsigned)(ub >> 32), false, false);
+  return make_double2(__longlong_as_double(((unsigned long long)hi[0] << 32) | lo[0]),
+                      __longlong_as_double(((unsigned long long)hi[1] << 32) | lo[1]));
+}
+__device__ __forceinline__ double wave_totals16(const double (&v)[16]) {
+  double a[8], b[4];
+#pragma unroll
+  for (int k = 0; k < 8; ++k) {
+    const double2 t = swap_halves32(v[k], v[k + 8]);
+    a[k] = t.x + t.y;
+  }
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const double2 t = swap_halves16(a[k], a[k + 4]);
+    b[k] = t.x + t.y;
+    b[k] += dpp_move<0x128, 0xf>(b[k]);  // row_ror 8, 4, 2, 1
+    b[k] += dpp_move<0x124, 0xf>(b[k]);
+    b[k] += dpp_move<0x122, 0xf>(b[k]);
+    b[k] += dpp_move<0x121, 0xf>(b[k]);
+  }
+  const int l = threadIdx.x & 3;
+  const double x = l & 1 ? b[1] : b[0], y = l & 1 ? b[3] : b[2];
+  return l & 2 ? y : x;
+}
+
+constexpr int TRD_COLS = 8;
+template <int T, int R>
+__global__ __launch_bounds__(T) void k_hetrd_all(TrdArgs a, TrdExchange e) {
+  constexpr int K = TRD_COLS, W = T / 64;
+  __shared__ zd P[T * R + 1], V[2][T * R + 1];
+  __shared__ double sums[2 * W], sigs[W], dots[W][2 * K];
+  __shared__ zd head[2];  // rows s and s + 1 of column s
+  __shared__ int fail;
+  const int n = a.n, tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int j0 = blockIdx.x * K, last = min(n, j0 + K) - 1;  // done after step `last`
+  const zd zero = make_double2(0.0, 0.0);
+  zd h[K][R], v[R];
+#pragma unroll
+  for (int q = 0; q < R; ++q) {
+    const int i = tid + T * q;
+    v[q] = V[0][i] = V[1][i] = P[i] = zero;
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      h[k][q] = zero;
+      if (i < n && j0 + k < n) h[k][q] = a.H[i + (int64_t)(j0 + k) * a.ldh];
+    }
+  }
+  if (tid == 0) {
+    fail = 0;
+    P[T * R] = V[0][T * R] = V[1][T * R] = head[1] = zero;
+  }
+  __syncthreads();
+  zd taup = zero;
+  for (int s = 0; s <= last; ++s) {
+    // p of reflector s - 1 and column s, rows >= s
+    zd p[R], c[R];
+#pragma unroll
+    for (int q = 0; q < R; ++q) p[q] = c[q] = zero;
+    if (s == 0) {
+#pragma unroll
+      for (int q = 0; q < R; ++q)
+        if (tid + T * q < n) c[q] = a.H[tid + T * q];
+    } else {
+      const unsigned long long* x = e.x + (s - 1) * 4 * e.ld;
+      unsigned long long g[R][4];
+#pragma unroll
+      for (int q = 0; q < R; ++q)
+#pragma unroll
+        for (int u = 0; u < 4; ++u) g[q][u] = HOLE;
+      bool miss = true;
+      for (int spin = 0; miss && spin < e.spin; ++spin) {
+        miss = false;
+#pragma unroll
+        for (int q = 0; q < R; ++q) {
+          const int i = tid + T * q;
+          if (i >= s && i < n && (g[q][0] == HOLE || g[q][1] == HOLE)) {
+            g[q][0] = peek(x + i);
+            g[q][1] = peek(x + e.ld + i);
+          }
+          if (i >= s && i < n && (g[q][2] == HOLE || g[q][3] == HOLE)) {
+            g[q][2] = peek(x + 2 * e.ld + i);
+            g[q][3] = peek(x + 3 * e.ld + i);
+          }
+        }
+#pragma unroll
+        for (int q = 0; q < R; ++q) {
+          const int i = tid + T * q;
+          if (i >= s && i < n)
+            miss |= g[q][0] == HOLE || g[q][1] == HOLE || g[q][2] == HOLE || g[q][3] == HOLE;
+        }
+      }
+      if (miss) fail = 1;
+#pragma unroll
+      for (int q = 0; q < R; ++q)
+        if (tid + T * q >= s && tid + T * q < n) {
+          p[q] = make_double2(__longlong_as_double(g[q][0]), __longlong_as_double(g[q][1]));
+          c[q] = make_double2(__longlong_as_double(g[q][2]), __longlong_as_double(g[q][3]));
+        }
+    }
+    // K = conj(tau) / 2 * v^H p
+    double kr = 0.0, ki = 0.0;
+#pragma unroll
+    for (int q = 0; q < R; ++q) {
+      const int i = tid + T * q;
+      P[i] = p[q];
+      if (i == s) head[0] = c[q];
+      if (i == s + 1) head[1] = c[q];
+      kr += v[q].x * p[q].x + v[q].y * p[q].y;
+      ki += v[q].x * p[q].y - v[q].y * p[q].x;
+    }
+    kr = wave_total(kr);
+    ki = wave_total(ki);
+    if (lane == 0) {
+      sums[2 * wave] = kr;
+      sums[2 * wave + 1] = ki;
+    }
+    __syncthreads();
+    if (fail) {
+      if (tid == 0) __hip_atomic_store(e.err, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      return;
+    }
+    const zd* Vp = V[s & 1];
+    kr = ki = 0.0;
+#pragma unroll
+    for (int u = 0; u < W; ++u) {
+      kr += sums[2 * u];
+      ki += sums[2 * u + 1];
+    }
+    const zd k2 = cmul(cconj(taup), make_double2(0.5 * kr, 0.5 * ki));
+    // w = p - K v; column s: c - (v conj(w(s)) + w conj(v(s))), v(s) = 1
+    const zd ps = P[s], wps = make_double2(ps.x - k2.x, ps.y - k2.y);
+    zd cs = head[0], ca = head[1];
+    if (s > 0) {
+      cs.x -= 2.0 * wps.x;
+      const zd va = Vp[s + 1], pa = P[s + 1], kv = cmul(k2, va), t = cmul(va, cconj(wps));
+      ca.x -= t.x + (pa.x - kv.x);
+      ca.y -= t.y + (pa.y - kv.y);
+    }
+    double sig = 0.0;
+#pragma unroll
+    for (int q = 0; q < R; ++q) {
+      const zd kv = cmul(k2, v[q]), t = cmul(v[q], cconj(wps));
+      p[q] = make_double2(p[q].x - kv.x, p[q].y - kv.y);  // w from here on
+      c[q] = make_double2(c[q].x - (t.x + p[q].x), c[q].y - (t.y + p[q].y));
+      if (tid + T * q >= s + 2) sig += c[q].x * c[q].x + c[q].y * c[q].y;
+    }
+    sig = wave_total(sig);
+    if (lane == 0) sigs[wave] = sig;
+    __syncthreads();
+    sig = 0.0;
+#pragma unroll
+    for (int u = 0; u < W; ++u) sig += sigs[u];
+    zd tau = zero, scal = zero;
+    double beta = ca.x;
+    if (sig != 0.0 || ca.y != 0.0) {
+      const double nrm = sqrt(ca.x * ca.x + ca.y * ca.y + sig);
+      beta = (ca.x >= 0.0) ? -nrm : nrm;
+      tau = make_double2((beta - ca.x) / beta, -ca.y / beta);
+      const zd den = make_double2(ca.x - beta, ca.y);  // scal = 1 / den
+      const double dd = den.x * den.x + den.y * den.y;
+      scal = make_double2(den.x / dd, -den.y / dd);
+    }
+#pragma unroll
+    for (int q = 0; q < R; ++q) {  // v_s
+      const int i = tid + T * q;
+      const zd t = cmul(c[q], scal);
+      c[q] = make_double2(i == s + 1 ? 1.0 : i > s + 1 ? t.x : 0.0, i > s + 1 ? t.y : 0.0);
+      V[(s & 1) ^ 1][i] = c[q];
+    }
+    if (s >= j0) {  // this work-group's column: the reflector goes out
+      if (tid == 0) {
+        a.d[s] = cs.x;
+        if (s < n - 1) {
+          a.tau[s] = tau;
+          a.e[s] = beta;
+        }
+      }
+      if (s < n - 1) {
+#pragma unroll
+        for (int q = 0; q < R; ++q)
+          if (tid + T * q < n) a.V[tid + T * q + (int64_t)s * a.ldv] = c[q];
+      }
+    }
+    if (s == last) break;
+    // the columns' update by reflector s - 1, then conj(h) v_s
+    // (a wave's 64 rows that lie above row s are zero in v, w and v_s)
+    double dot[2 * K];
+    constexpr int KB = R > 2 ? K / 2 : K;  // columns at a time, by the registers left
+#pragma unroll
+    for (int kb = 0; kb < K; kb += KB) {
+      zd vj[KB], wj[KB];
+#pragma unroll
+      for (int k = 0; k < KB; ++k) {
+        const int j = min(j0 + kb + k, n - 1);
+        vj[k] = Vp[j];
+        const zd kv = cmul(k2, vj[k]);
+        wj[k] = make_double2(P[j].x - kv.x, P[j].y - kv.y);
+        dot[2 * (kb + k)] = dot[2 * (kb + k) + 1] = 0.0;
+      }
+#pragma unroll
+      for (int q = 0; q < R; ++q) {
+        if (64 * wave + T * q + 63 < s) continue;
+#pragma unroll
+        for (int k = 0; k < KB; ++k) {
+          double x = h[kb + k][q].x, y = h[kb + k][q].y;
+          x = fma(-v[q].x, wj[k].x, x);  // - v conj(w(j)) - w conj(v(j))
+          y = fma(-v[q].y, wj[k].x, y);
+          x = fma(-v[q].y, wj[k].y, x);
+          y = fma(v[q].x, wj[k].y, y);
+          x = fma(-p[q].x, vj[k].x, x);
+          y = fma(-p[q].y, vj[k].x, y);
+          x = fma(-p[q].y, vj[k].y, x);
+          y = fma(p[q].x, vj[k].y, y);
+          h[kb + k][q] = make_double2(x, y);
+          dot[2 * (kb + k)] += x * c[q].x + y * c[q].y;
+          dot[2 * (kb + k) + 1] += x * c[q].y - y * c[q].x;
+        }
+      }
+    }
+    unsigned long long* x = e.x + s * 4 * e.ld;
+    if (s + 1 >= j0) {  // column s + 1 (s < last: it is one of these)
+      const int kc = s + 1 - j0;
+#pragma unroll
+      for (int q = 0; q < R; ++q) {
+        const int i = tid + T * q;
+        zd t = h[0][q];
+#pragma unroll
+        for (int k = 1; k < K; ++k) {
+          t.x = kc == k ? h[k][q].x : t.x;
+          t.y = kc == k ? h[k][q].y : t.y;
+        }
+        if (i > s && i < n) {
+          publish(x + 2 * e.ld + i, t.x);
+          publish(x + 3 * e.ld + i, t.y);
+        }
+      }
+    }
+    const double total = wave_totals16(dot);
+    if ((lane & 15) < 4) dots[wave][4 * (lane >> 4) + (lane & 3)] = total;
+    __syncthreads();
+    if (tid < 2 * K) {
+      const int k = tid >> 1, j = j0 + k;
+      double dr = 0.0, di = 0.0;
+#pragma unroll
+      for (int u = 0; u < W; ++u) {
+        dr += dots[u][2 * k];
+        di += dots[u][2 * k + 1];
+      }
+      const zd pk = cmul(tau, make_double2(dr, di));
+      if (j > s && j < n) publish(x + (tid & 1 ? e.ld : 0) + j, tid & 1 ? pk.y : pk.x);
+    }
+#pragma unroll
+    for (int q = 0; q < R; ++q) v[q] = c[q];
+    taup = tau;
+  }
 }
 
 // Sturm count: number of eigenvalues of T smaller than x.
@@ -591,9 +1051,10 @@ size_t heev_work_bytes(int64_t n) {
   return b;
 }
 
-// One launch per reflector: the kernel boundary is the grid-wide barrier (a
-// cooperative single launch with explicit barriers measured slower, because
-// each barrier must write back and invalidate the XCD caches).  Issued one by
+// One launch per reflector, for streams that share the GPU, under capture and
+// where the single launch gave up: the kernel boundary is the grid-wide barrier (a cooperative single launch with
+// explicit barriers measured slower, because each barrier must write back and
+// invalidate the XCD caches).  Issued one by
 // one, the launches cost the host about 4.4 us each at n = 948, more than the
 // later, shorter steps take on the GPU; so the sequence is captured once per
 // argument set into a graph and replayed (the first call also pays the
@@ -650,6 +1111,71 @@ gevp_status hetrd_launches(gevp_ctx* c, const TrdArgs& a, int G, size_t sh3) {
 }
 }  // namespace
 
+namespace {
+constexpr int TRD_SPINS = 1 << 18;  // some tenths of a second
+
+// one single-launch tridiagonalisation at a time per device and process: two of
+// them, each with a part of its work-groups resident, would wait for the other's
+// compute units
+struct TrdTurn {
+  std::atomic<bool>* busy = nullptr;
+  explicit TrdTurn(int device) {
+    static std::atomic<bool> taken[64];
+    if (device >= 0 && device < 64 && !taken[device].exchange(true)) busy = &taken[device];
+  }
+  ~TrdTurn() {
+    if (busy) busy->store(false);
+  }
+};
+
+// The tridiagonalisation in one launch; *done = false when it may not run, could
+// not be launched or gave up, H being unchanged.  An ordinary launch: kernels of
+// other streams end by themselves, so its work-groups, no more than fit the GPU
+// at once, all become resident.  (A cooperative launch gives the process one more
+// hardware queue for good, which slowed batches on eight streams from 94 to 139
+// ms.)  A handle whose launch gave up once (its stream may be confined to some of
+// the compute units) does not try again.
+gevp_status hetrd_all(gevp_ctx* c, const TrdArgs& a, TrdExchange x, bool* done) {
+  *done = false;
+  // the outcome is read back, which a capture cannot hold
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(c->stream, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) {
+    (void)hipGetLastError();
+    return GEVP_OK;
+  }
+  const int n = a.n;
+  auto* f = n <= 256    ? k_hetrd_all<256, 1>
+            : n <= 512  ? k_hetrd_all<512, 1>
+            : n <= 1024 ? k_hetrd_all<512, 2>
+            : n <= 1536 ? k_hetrd_all<512, 3>
+                        : k_hetrd_all<512, 4>;
+  const int threads = n <= 256 ? 256 : 512, groups = (n + TRD_COLS - 1) / TRD_COLS;
+  int per_cu = 0, cus = 0;
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, f, threads, 0) != hipSuccess ||
+      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device) != hipSuccess) {
+    (void)hipGetLastError();
+    return GEVP_OK;
+  }
+  if (per_cu * cus < groups) return GEVP_OK;
+  TrdTurn turn(c->device);
+  if (!turn.busy) return GEVP_OK;
+  x.ld = (n + 15) / 16 * 16;
+  const int64_t words = (int64_t)n * 4 * x.ld;
+  hipLaunchKernelGGL(k_trd_holes, dim3((unsigned)std::min<int64_t>((words + 255) / 256, 4096)), dim3(256), 0,
+                     c->stream, x.x, words, x.err);
+  GEVP_HIP_TRY(hipGetLastError());
+  hipLaunchKernelGGL(f, dim3((unsigned)groups), dim3((unsigned)threads), 0, c->stream, a, x);
+  const hipError_t launched = hipGetLastError();
+  int err = 1;
+  GEVP_HIP_TRY(hipMemcpyAsync(&err, x.err, sizeof(int), hipMemcpyDeviceToHost, c->stream));
+  GEVP_HIP_TRY(hipStreamSynchronize(c->stream));
+  GEVP_HIP_TRY(launched);
+  *done = err == 0;
+  if (err) c->shared_gpu = true;
+  return GEVP_OK;
+}
+}  // namespace
+
 gevp_status heev_small(gevp_ctx* c, int64_t n64, zd* H, int64_t ldh, double* theta, zd* Z,
                        int64_t ldz, void* work) {
   if (n64 <= 0) return GEVP_OK;
@@ -689,11 +1215,23 @@ gevp_status heev_small(gevp_ctx* c, int64_t n64, zd* H, int64_t ldh, double* the
     return true;
   }();
   (void)attr;
-  if (n == 1) {
-    hipLaunchKernelGGL(k_hetrd_step, dim3(1), dim3(HT), sh3, c->stream, a, 0);
+  // Many work-groups in one launch where they can be resident together; one
+  // work-group where the exchange through memory costs more than it spreads (the
+  // whole eigensolver at n = 32, 64, 116: 0.25, 0.47, 0.94 ms with one, 0.28,
+  // 0.45, 0.76 with many); a launch per reflector where other streams share the
+  // GPU.  The exchange lies in the tridiagonal solver's workspace, not
+  // in use yet (40 n^2 bytes against 32 n (n + 15): enough from n = 60).
+  bool done = false;
+  if (n > TRD1_MAX && n <= TRDM_MAX && !c->shared_gpu) {
+    TrdExchange x{(unsigned long long*)tw, 0, (int*)a.pb, TRD_SPINS};
+    GEVP_TRY(hetrd_all(c, a, x, &done));
+  }
+  if (n <= TRD1_MAX && !c->shared_gpu) {
+    hipLaunchKernelGGL(k_hetrd_one, dim3(1), dim3(1024), 0, c->stream, a);
     GEVP_HIP_TRY(hipGetLastError());
-    GEVP_HIP_TRY(hipMemsetAsync(a.tau, 0, sizeof(zd), c->stream));
-  } else {
+    done = true;
+  }
+  if (!done) {
     GEVP_HIP_TRY(hipMemsetAsync(a.tau, 0, sizeof(zd) * n, c->stream));
     GEVP_TRY(hetrd_launches(c, a, G, sh3));
   }

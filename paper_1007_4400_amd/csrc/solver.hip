@@ -573,6 +573,7 @@ gevp_status aux_ctx(gevp_ctx* c, gevp_ctx** out) {
       return GEVP_ERR_HIP;
     }
     w->owns_stream = true;
+    w->shared_gpu = true;
     c->aux = w;
     ext_assign(c, w, SLOT_AUX);
   }
@@ -1279,6 +1280,7 @@ gevp_status gevp_solve_batched(gevp_handle h, const gevp_opts* opts, int count, 
     }
     w->owns_stream = true;
     w->inner_streams = false;
+    w->shared_gpu = true;
     h->workers.push_back(w);
   }
   // event timing of the filter launches (profiling flag 2) carries over; the
