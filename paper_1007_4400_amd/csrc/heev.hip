@@ -681,18 +681,39 @@ __global__ __launch_bounds__(T) void k_hetrd_all(TrdArgs a, TrdExchange e) {
   }
 }
 
-// Sturm count: number of eigenvalues of T smaller than x.
+// 1 / x for a normal x, within an ulp or so: the vector unit's estimate (24 bits
+// or more) times 1 + e + e^2, e = 1 - x r being what it lacks.  The recurrences
+// below are one chain of divisions; the full divide's scaling and fix-up double
+// the chain.
+__device__ __forceinline__ double recip(double x) {
+  const double r = __builtin_amdgcn_rcp(x), e = fma(-x, r, 1.0);
+  return fma(r, fma(e, e, e), r);
+}
+
+// Sturm count: number of eigenvalues of T smaller than x.  |q| >= pivmin keeps
+// both 1 / q and e^2 / q finite.  948 eigenvalues: 820 us with the full divide, now
+// 460 us.
 __device__ int sturm(const double* d, const double* e2, int n, double x, double pivmin) {
   int cnt = 0;
   double q = d[0] - x;
   if (fabs(q) < pivmin) q = -pivmin;
   cnt += q < 0.0;
   for (int i = 1; i < n; ++i) {
-    q = d[i] - x - e2[i - 1] / q;
-    if (fabs(q) < pivmin) q = -pivmin;
+    q = fma(-e2[i - 1], recip(q), d[i] - x);
+  if (fabs(q) < pivmin) q = -pivmin;
     cnt += q < 0.0;
   }
   return cnt;
+}
+
+// largest v of the work-group; sh holds one entry per wave
+__device__ double bmax(double v, double* sh) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) v = fmax(v, __shfl_xor(v, o, 64));
+  __syncthreads();
+  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
+  __syncthreads();
+  return fmax(fmax(sh[0], sh[1]), fmax(sh[2], sh[3]));
 }
 
 // One wave per eigenvalue k: every round the 64 lanes evaluate Sturm counts
@@ -703,31 +724,29 @@ __global__ __launch_bounds__(HT) void k_tri_bisect(const double* d, const double
   extern __shared__ double sm[];
   double* sd = sm;
   double* se2 = sm + n;
-  __shared__ double red[3];
+  __shared__ double red[4];
   for (int i = threadIdx.x; i < n; i += HT) {
     sd[i] = d[i];
     se2[i] = (i < n - 1) ? e[i] * e[i] : 0.0;
   }
   __syncthreads();
-  if (threadIdx.x == 0) {
-    double gl = DBL_MAX, gu = -DBL_MAX, emax = 0.0;
-    for (int i = 0; i < n; ++i) {
-      const double r = (i > 0 ? sqrt(se2[i - 1]) : 0.0) + (i < n - 1 ? sqrt(se2[i]) : 0.0);
-      gl = fmin(gl, sd[i] - r);
-      gu = fmax(gu, sd[i] + r);
-      if (i < n - 1) emax = fmax(emax, se2[i]);
-    }
-    const double tnorm = fmax(fabs(gl), fabs(gu));
-    red[0] = gl - 2.0 * DBL_EPSILON * tnorm * n - 1e-300;
-    red[1] = gu + 2.0 * DBL_EPSILON * tnorm * n + 1e-300;
-    red[2] = DBL_MIN * fmax(1.0, emax);
+  double gl = DBL_MAX, gu = -DBL_MAX, emax = 0.0;
+  for (int i = threadIdx.x; i < n; i += HT) {
+    const double r = (i > 0 ? sqrt(se2[i - 1]) : 0.0) + (i < n - 1 ? sqrt(se2[i]) : 0.0);
+    gl = fmin(gl, sd[i] - r);
+    gu = fmax(gu, sd[i] + r);
+    emax = fmax(emax, se2[i]);
   }
-  __syncthreads();
+  gl = -bmax(-gl, red);
+  gu = bmax(gu, red);
+  emax = bmax(emax, red);
+  const double tnorm = fmax(fabs(gl), fabs(gu));
   const int lane = threadIdx.x & 63;
   const int k = blockIdx.x * (HT / 64) + (threadIdx.x >> 6);
   if (k >= n) return;
-  double lo = red[0], hi = red[1];
-  const double pivmin = red[2];
+  double lo = gl - 2.0 * DBL_EPSILON * tnorm * n - 1e-300;
+  double hi = gu + 2.0 * DBL_EPSILON * tnorm * n + 1e-300;
+  const double pivmin = DBL_MIN * fmax(1.0, emax);
   for (int round = 0; round < 40; ++round) {
     if (hi - lo <= 2.0 * DBL_EPSILON * fmax(fabs(lo), fabs(hi)) + 4.0 * pivmin) break;
     const double w = (hi - lo) / 65.0;
@@ -755,130 +774,159 @@ __device__ __forceinline__ uint64_t hmix(uint64_t z) {
   return z ^ (z >> 31);
 }
 
-// Inverse iteration, thread j <-> eigenvalue j.  Scratch arrays are laid out
-// [i * n + j] so that a wave's accesses are contiguous.  Output Zt[i*n + j].
-// LU of T - lam I with partial pivoting: row k of U holds (U, Vv, Ww) on
-// columns (k, k+1, k+2); Lm the multiplier and Sw the row swap of step k.
+// Inverse iteration, thread j <-> eigenvalue j; Zt comes in with the start
+// vectors.  Work arrays are laid out [k * n + j] so that a wave's accesses are
+// contiguous.  Output Zt[i*n + j].
+// LU of T - lam I with partial pivoting: row k of U holds the pivot's reciprocal
+// (array U), Vv on column k + 1 and, where rows k and k + 1 were swapped, e_{k+1}
+// on column k + 2; Lm is the multiplier; the swaps are bits in the LDS.
+// Every pass is one serial chain per thread, so what counts is the chain's length
+// (one reciprocal a step in the LU, one or two multiply-adds in the sweeps) and
+// that no load is waited for: a pass loads its next IB steps before it works on
+// these.  n = 948: 880 us with divisions in the chains and each IB steps' loads
+// waited for (and five work arrays, start vectors formed here),
+// now 510 us.
 __global__ __launch_bounds__(64) void k_tri_invit(const double* dg, const double* eg, int n,
                                                   const double* theta, double* U, double* Vv,
-                                                  double* Ww, double* Lm, double* Sw, double* Zt,
-                                                  const double* tnorm_dev) {
+                                                  double* Lm, double* Zt, const double* tnorm_dev) {
+  constexpr int IB = 16;
   const double tnorm = *tnorm_dev;
   extern __shared__ double sm[];
-  double* d = sm;
-  double* e = sm + n;
-  for (int i = threadIdx.x; i < n; i += 64) {
-    d[i] = dg[i];
-    e[i] = (i < n - 1) ? eg[i] : 0.0;
+  double* d = sm;                        // n + IB + 1 entries each, zeros behind T
+  double* e = sm + n + IB + 1;
+  unsigned short* swaps = (unsigned short*)(e + n + IB + 1);  // IB steps a word: [step / IB][thread]
+  for (int i = threadIdx.x; i < n + IB + 1; i += 64) {
+    d[i] = i < n ? dg[i] : 0.0;
+    e[i] = i < n - 1 ? eg[i] : 0.0;
   }
   __syncthreads();
   const int j = blockIdx.x * 64 + threadIdx.x;
   if (j >= n) return;
+  swaps += threadIdx.x;
   const double lam = theta[j];
-  const double tiny = DBL_EPSILON * fmax(tnorm, DBL_MIN);
-  // thread j's entry k of an n x n work array; consecutive threads are
-  // consecutive addresses.  Every pass below keeps its recurrence in
-  // registers; the loads it needs do not depend on the recurrence and are
-  // issued IB steps at a time, so a pass costs n / IB memory latencies.
+  const double tiny = fmax(DBL_EPSILON * tnorm, DBL_MIN);
   auto at = [&](double* A, int k) -> double& { return A[(int64_t)k * n + j]; };
-  constexpr int IB = 32;
-  // LU with partial pivoting of T - lam I; working row k: (al, be) on columns (k, k+1)
-  double al = d[0] - lam, be = (n > 1) ? e[0] : 0.0;
-  for (int k = 0; k < n - 1; ++k) {
-    const double ck = e[k], an = d[k + 1] - lam, bn = (k + 1 < n - 1) ? e[k + 1] : 0.0;
-    if (fabs(al) >= fabs(ck)) {  // pivot on the working row
-      const double piv = (al == 0.0) ? tiny : al;
-      const double l = ck / piv;
-      at(U, k) = piv;
-      at(Vv, k) = be;
-      at(Ww, k) = 0.0;
-      at(Lm, k) = l;
-      at(Sw, k) = 0.0;
-      al = an - l * be;
-      be = bn;
-    } else {  // pivot on the next original row (ck, an, bn)
-      const double l = al / ck;
-      at(U, k) = ck;
-      at(Vv, k) = an;
-      at(Ww, k) = bn;
-      at(Lm, k) = l;
-      at(Sw, k) = 1.0;
-      const double nal = be - l * an;
-      be = -l * bn;
-      al = nal;
+  const int nb = (n + IB - 1) / IB;  // blocks of IB steps
+  // working row k: (al, be) on columns (k, k+1); the last step is its pivot alone
+  double al = d[0] - lam, be = e[0];
+  for (int blk = 0; blk < nb; ++blk) {
+    const int k0 = blk * IB;
+    unsigned bits = 0;
+    double dv[IB], ev[IB + 1];
+#pragma unroll
+    for (int q = 0; q < IB; ++q) {
+      dv[q] = d[k0 + q + 1] - lam;
+      ev[q] = e[k0 + q];
     }
-  }
-  at(U, n - 1) = (al == 0.0) ? tiny : al;
-  for (int i = 0; i < n; ++i) {
-    const uint64_t r = hmix(((uint64_t)j << 32) ^ (uint64_t)i ^ 0x5DEECE66Dull);
-    at(Zt, i) = ((double)(r >> 11) * (1.0 / 9007199254740992.0)) - 0.5;
+    ev[IB] = e[k0 + IB];
+#pragma unroll
+    for (int q = 0; q < IB; ++q) {
+      const int k = k0 + q;
+      const double ck = ev[q], an = dv[q], bn = ev[q + 1];
+      const bool sw = fabs(al) < fabs(ck);  // pivot on the next original row (ck, an, bn)
+      double piv = sw ? ck : al;
+      if (fabs(piv) < DBL_MIN) piv = copysign(piv == 0.0 ? tiny : DBL_MIN, piv);
+      const double rp = recip(piv), l = (sw ? al : ck) * rp;
+      if (k < n) {
+        at(U, k) = rp;
+        at(Vv, k) = sw ? an : be;
+        at(Lm, k) = l;
+      }
+      bits |= (unsigned)sw << q;
+      const double x = sw ? be : an, y = sw ? an : be;
+      al = fma(-l, y, x);
+      be = sw ? -l * bn : bn;
+    }
+    swaps[64 * blk] = (unsigned short)bits;
   }
   // Two sweeps of inverse iteration.  The growth of the first sweep is removed
   // by a power-of-two factor folded into the second sweep's loads (exact, no
   // extra pass); the second sweep's backward pass also accumulates the sum of
   // squares, so one final pass normalises.
+  struct Fwd {
+    double l[IB], a[IB];
+  };
+  struct Bwd {
+    double y[IB], v[IB], u[IB];
+  };
   double sc = 1.0, ssq = 0.0, mx = 0.0;
   for (int it = 0; it < 2; ++it) {
     // forward: apply the row swaps and multipliers; c is the current y_k
+    auto load_f = [&](Fwd& f, int blk) {
+#pragma unroll
+      for (int q = 0; q < IB; ++q) {
+        const int k = min(blk * IB + q, n - 1);
+        f.l[q] = at(Lm, k);
+        f.a[q] = at(Zt, min(k + 1, n - 1));
+      }
+    };
     double c = at(Zt, 0) * sc;
-    for (int k0 = 0; k0 < n - 1; k0 += IB) {
-      double lv[IB], sv[IB], av[IB];
+    auto pass_f = [&](const Fwd& f, int blk) {
+      const unsigned bits = swaps[64 * blk];
 #pragma unroll
       for (int q = 0; q < IB; ++q) {
-        const int k = k0 + q;
+        const int k = blk * IB + q;
+        const double a = f.a[q] * sc;
+        const bool sw = (bits >> q) & 1;
         if (k < n - 1) {
-          lv[q] = at(Lm, k);
-          sv[q] = at(Sw, k);
-          av[q] = at(Zt, k + 1);
+          at(Zt, k) = sw ? a : c;
+          c = fma(-f.l[q], sw ? a : c, sw ? c : a);
         }
       }
-#pragma unroll
-      for (int q = 0; q < IB; ++q) {
-        const int k = k0 + q;
-        if (k < n - 1) {
-          const double a = av[q] * sc;
-          if (sv[q] != 0.0) {  // rows k, k+1 swapped
-            at(Zt, k) = a;
-            c = c - lv[q] * a;
-          } else {
-            at(Zt, k) = c;
-            c = a - lv[q] * c;
-          }
-        }
-      }
+    };
+    Fwd f0, f1;
+    load_f(f0, 0);
+    for (int blk = 0; blk < nb; blk += 2) {
+      load_f(f1, blk + 1);
+      __builtin_amdgcn_sched_barrier(0);
+      pass_f(f0, blk);
+      __builtin_amdgcn_sched_barrier(0);
+      load_f(f0, blk + 2);
+      __builtin_amdgcn_sched_barrier(0);
+      if (blk + 1 < nb) pass_f(f1, blk + 1);
+      __builtin_amdgcn_sched_barrier(0);
     }
     at(Zt, n - 1) = c;
     // backward: U x = y with U upper triangular, bandwidth 3
     double x1 = 0.0, x2 = 0.0;
     mx = 0.0;
     ssq = 0.0;
-    for (int k0 = n - 1; k0 >= 0; k0 -= IB) {
-      double yv[IB], vv[IB], wv[IB], uv[IB];
+    auto load_b = [&](Bwd& f, int blk) {
 #pragma unroll
       for (int q = 0; q < IB; ++q) {
-        const int k = k0 - q;
-        if (k >= 0) {
-          yv[q] = at(Zt, k);
-          vv[q] = at(Vv, k);
-          wv[q] = at(Ww, k);
-          uv[q] = at(U, k);
-        }
+        const int k = min(max(blk * IB + q, 0), n - 1);
+        f.y[q] = at(Zt, k);
+        f.v[q] = at(Vv, k);
+        f.u[q] = at(U, k);
       }
+    };
+    auto pass_b = [&](const Bwd& f, int blk) {
+      const unsigned bits = swaps[64 * blk];
 #pragma unroll
-      for (int q = 0; q < IB; ++q) {
-        const int k = k0 - q;
-        if (k >= 0) {
-          double y = yv[q];
-          if (k + 1 < n) y -= vv[q] * x1;
-          if (k + 2 < n) y -= wv[q] * x2;
-          const double x = y / uv[q];
+      for (int q = IB - 1; q >= 0; --q) {
+        const int k = blk * IB + q;
+        if (k < n) {
+          const double w = (bits >> q) & 1 ? e[k + 1] : 0.0;
+          const double x = fma(-f.v[q], x1, fma(-w, x2, f.y[q])) * f.u[q];
           at(Zt, k) = x;
           x2 = x1;
           x1 = x;
           mx = fmax(mx, fabs(x));
-          ssq += x * x;
+          ssq = fma(x, x, ssq);
         }
       }
+    };
+    Bwd b0, b1;
+    load_b(b0, nb - 1);
+    for (int blk = nb - 1; blk >= 0; blk -= 2) {
+      load_b(b1, blk - 1);
+      __builtin_amdgcn_sched_barrier(0);
+      pass_b(b0, blk);
+      __builtin_amdgcn_sched_barrier(0);
+      load_b(b0, blk - 2);
+      __builtin_amdgcn_sched_barrier(0);
+      if (blk - 1 >= 0) pass_b(b1, blk - 1);
+      __builtin_amdgcn_sched_barrier(0);
     }
     int ex = 0;
     (void)frexp(mx, &ex);
@@ -886,29 +934,30 @@ __global__ __launch_bounds__(64) void k_tri_invit(const double* dg, const double
   }
   // normalise: from the sum of squares when it is finite, else after scaling
   // by the power of two (a second pass, only for extreme growth)
+  constexpr int NB = 32;
   double inv;
   if (ssq > 0.0 && isfinite(ssq)) {
     inv = 1.0 / sqrt(ssq);
   } else {
     double nrm = 0.0;
-    for (int k0 = 0; k0 < n; k0 += IB) {
-      double zv[IB];
+    for (int k0 = 0; k0 < n; k0 += NB) {
+      double zv[NB];
 #pragma unroll
-      for (int q = 0; q < IB; ++q)
+      for (int q = 0; q < NB; ++q)
         if (k0 + q < n) zv[q] = at(Zt, k0 + q);
 #pragma unroll
-      for (int q = 0; q < IB; ++q)
+      for (int q = 0; q < NB; ++q)
         if (k0 + q < n) nrm += (zv[q] * sc) * (zv[q] * sc);
     }
     inv = (nrm > 0.0 && isfinite(nrm)) ? sc / sqrt(nrm) : 0.0;
   }
-  for (int k0 = 0; k0 < n; k0 += IB) {
-    double zv[IB];
+  for (int k0 = 0; k0 < n; k0 += NB) {
+    double zv[NB];
 #pragma unroll
-    for (int q = 0; q < IB; ++q)
+    for (int q = 0; q < NB; ++q)
       if (k0 + q < n) zv[q] = at(Zt, k0 + q);
 #pragma unroll
-    for (int q = 0; q < IB; ++q)
+    for (int q = 0; q < NB; ++q)
       if (k0 + q < n) at(Zt, k0 + q) = zv[q] * inv;
   }
 }
@@ -962,12 +1011,24 @@ __global__ __launch_bounds__(256) void k_zt_to_complex(const double* Zt, int n, 
   }
 }
 
-__global__ void k_tri_norm(const double* d, const double* e, int n, double* out) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
+// Group 0: the norm of T; the others: the start vectors of the inverse iteration
+__global__ __launch_bounds__(HT) void k_tri_start(const double* d, const double* e, int n, double* out,
+                                                  double* Zt) {
+  if (blockIdx.x > 0) {
+    for (int64_t k = (int64_t)(blockIdx.x - 1) * HT + threadIdx.x; k < (int64_t)n * n;
+         k += (int64_t)(gridDim.x - 1) * HT) {
+      const uint64_t i = k / n, j = k % n;
+      const uint64_t r = hmix((j << 32) ^ i ^ 0x5DEECE66Dull);
+      Zt[k] = ((double)(r >> 11) * (1.0 / 9007199254740992.0)) - 0.5;
+    }
+    return;
+  }
+  __shared__ double sh[4];
   double m = 0.0;
-  for (int i = 0; i < n; ++i)
+  for (int i = threadIdx.x; i < n; i += HT)
     m = fmax(m, fabs(d[i]) + (i > 0 ? fabs(e[i - 1]) : 0.0) + (i < n - 1 ? fabs(e[i]) : 0.0));
-  out[0] = m;
+  m = bmax(m, sh);
+  if (threadIdx.x == 0) out[0] = m;
 }
 }  // namespace
 
@@ -978,7 +1039,7 @@ __global__ void k_tri_norm(const double* d, const double* e, int n, double* out)
 inline int trd_groups(int64_t n) { return (int)(n - 1 < HT ? (n > 1 ? n - 1 : 1) : HT); }
 
 size_t tridiag_eig_work_bytes(int64_t n) {
-  return 5 * ws_round(sizeof(double) * n * n) + ws_round(sizeof(double) * 8);  // U, Vv, Ww, Lm, Sw; norm
+  return 5 * ws_round(sizeof(double) * n * n) + ws_round(sizeof(double) * 8);  // U, Vv, Lm, and the tridiagonalisation's exchange; norm
 }
 
 gevp_status tridiag_eig(gevp_ctx* c, int64_t n64, const double* d, const double* e, double* theta,
@@ -993,17 +1054,17 @@ gevp_status tridiag_eig(gevp_ctx* c, int64_t n64, const double* d, const double*
   };
   double* U = (double*)take(sizeof(double) * n * n);
   double* Vv = (double*)take(sizeof(double) * n * n);
-  double* Ww = (double*)take(sizeof(double) * n * n);
   double* Lm = (double*)take(sizeof(double) * n * n);
-  double* Sw = (double*)take(sizeof(double) * n * n);
   double* tn = (double*)take(sizeof(double) * 8);
-  hipLaunchKernelGGL(k_tri_norm, dim3(1), dim3(64), 0, c->stream, d, e, n, tn);
+  hipLaunchKernelGGL(k_tri_start, dim3(1 + (unsigned)std::min<int64_t>(((int64_t)n * n + HT - 1) / HT, 512)),
+                     dim3(HT), 0, c->stream, d, e, n, tn, Zt);
   GEVP_HIP_TRY(hipGetLastError());
   hipLaunchKernelGGL(k_tri_bisect, dim3((n + 3) / 4), dim3(HT), sizeof(double) * 2 * n, c->stream,
                      d, e, n, theta);
   GEVP_HIP_TRY(hipGetLastError());
-  hipLaunchKernelGGL(k_tri_invit, dim3((n + 63) / 64), dim3(64), sizeof(double) * 2 * n, c->stream,
-                     d, e, n, theta, U, Vv, Ww, Lm, Sw, Zt, tn);
+  const size_t shi = sizeof(double) * 2 * (n + 17) + 2 * 64 * (size_t)((n + 15) / 16);
+  hipLaunchKernelGGL(k_tri_invit, dim3((n + 63) / 64), dim3(64), shi, c->stream,
+                     d, e, n, theta, U, Vv, Lm, Zt, tn);
   GEVP_HIP_TRY(hipGetLastError());
   hipLaunchKernelGGL(k_tri_cluster_mgs, dim3(n), dim3(HT), 0, c->stream, theta, n, Zt, tn);
   GEVP_HIP_TRY(hipGetLastError());
