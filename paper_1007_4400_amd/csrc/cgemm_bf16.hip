@@ -430,26 +430,47 @@ __global__ __launch_bounds__(256) void k_split_cols_bf16(int k, int KG, int cols
 
 // Planes of the rows of the Hermitian C: row i, k-group g holds
 // C(i, 8g .. 8g+7) = conj(C_st(8g .. 8g+7, i)), split into re hi/lo, im hi/lo.
-__global__ void k_split_rows_bf16(int64_t n, int KG, const zd* C, int64_t ldc, uint4* planes) {
-  const int64_t i = blockIdx.y;
+// Memory bound (16 bytes read and 8 written per element).  A wave takes 512
+// elements of a column at a time, consecutive lanes on consecutive elements in the
+// loads and on consecutive 16-byte chunks in the stores, and turns one order into
+// the other in its own 4 KB of LDS (a group's 64 bytes rotated by 16 bytes every
+// four groups, against bank conflicts).  n = 8192: 0.28 ms (5.7 TB/s; 1.0 ms
+// with eight elements a thread, whose loads and stores are 128 and 64 bytes apart).
+constexpr int SPLIT_ELEMS = 512;
+__global__ __launch_bounds__(256) void k_split_rows_bf16(int64_t n, int KG, const zd* C, int64_t ldc,
+                                                         uint4* planes) {
+  __shared__ uint4 sh[4][SPLIT_ELEMS / 2];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int64_t i = blockIdx.y, k0 = ((int64_t)blockIdx.x * 4 + wave) * SPLIT_ELEMS;
+  if (k0 >= (int64_t)KG * 8) return;
   const zd* col = C + i * ldc;
-  for (int g = blockIdx.x * blockDim.x + threadIdx.x; g < KG; g += gridDim.x * blockDim.x) {
-    float re[8], im[8];
+  zd v[8];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const int64_t k = (int64_t)g * 8 + e;
-      const zd v = (k < n) ? col[k] : make_double2(0.0, 0.0);
-      re[e] = (float)v.x;
-      im[e] = (float)(-v.y);
-    }
-    uint4 rh, rl, ih, il;
-    split8(re, rh, rl);
-    split8(im, ih, il);
-    uint4* o = planes + (i * KG + g) * 4;
-    o[0] = rh;
-    o[1] = rl;
-    o[2] = ih;
-    o[3] = il;
+  for (int q = 0; q < 8; ++q) {
+    const int64_t k = k0 + 64 * q + lane;
+    v[q] = make_double2(0.0, 0.0);
+    if (k < n) v[q] = col[k];
+  }
+  unsigned short* s = (unsigned short*)sh[wave];
+#pragma unroll
+  for (int q = 0; q < 8; ++q) {
+    const int g = 8 * q + (lane >> 3), e = lane & 7;
+    const float re = (float)v[q].x, im = (float)(-v[q].y);
+    const unsigned short rh = bf16_rne(re), ih = bf16_rne(im);
+    const unsigned short rl = bf16_rne(re - bf16_f(rh)), il = bf16_rne(im - bf16_f(ih));
+    s[(4 * g + ((0 + (g >> 2)) & 3)) * 8 + e] = rh;
+    s[(4 * g + ((1 + (g >> 2)) & 3)) * 8 + e] = rl;
+    s[(4 * g + ((2 + (g >> 2)) & 3)) * 8 + e] = ih;
+    s[(4 * g + ((3 + (g >> 2)) & 3)) * 8 + e] = il;
+  }
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  uint4* o = planes + i * KG * 4;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int c = 64 * q + lane, g = c >> 2;  // chunk c: plane c % 4 of group g
+    const int64_t dst = k0 / 2 + c;
+    if (dst < (int64_t)KG * 4) o[dst] = sh[wave][4 * g + (((c & 3) + (g >> 2)) & 3)];
   }
 }
 }  // namespace
@@ -462,7 +483,7 @@ size_t bf16_planes_bytes(int64_t n) {
 gevp_status launch_split_rows_bf16(gevp_ctx* c, int64_t n, const zd* C, int64_t ldc, void* planes) {
   if (n <= 0) return GEVP_OK;
   const int KG = (int)(((n + 31) / 32) * 4);
-  const unsigned gxs = (unsigned)((KG + 255) / 256);
+  const unsigned gxs = (unsigned)((KG * 8 + 4 * SPLIT_ELEMS - 1) / (4 * SPLIT_ELEMS));
   hipLaunchKernelGGL(k_split_rows_bf16, dim3(gxs, (unsigned)n), dim3(256), 0, c->stream, n, KG, C, ldc,
                      (uint4*)planes);
   GEVP_HIP_TRY(hipGetLastError());
