@@ -15,6 +15,9 @@
 // Split-K: with few output tiles the K range is cut over several work-groups
 // (split32), each writes its raw partial tile to the stream's split-K buffer
 // and a second kernel sums them in a fixed order and applies the epilogue.
+//
+// A batch of products of one shape, each operand at a constant stride (the
+// contour filter's nodes), is one launch.
 #include "common.h"
 
 typedef float f4 __attribute__((ext_vector_type(4)));
@@ -41,9 +44,21 @@ struct CgemmParams {
   const double* gamma;
   const double* delta;
   int tiles_n, total, remap;
-  int tiles, nks;  // output tiles; K slices per part
+  int tiles, nks;  // output tiles (of the whole batch); K slices per part
+  // a batch of products: tiles of one, element strides of A, B and D (P, R as D)
+  int tiles1;
+  int64_t sA, sB, sD;
   zf* part;        // split-K partial tiles [part][tile][col][row], or null
 };
+
+// the parameters of product b of a batch
+__device__ __forceinline__ void select(CgemmParams& p, int b) {
+  p.A += b * p.sA;
+  p.B += b * p.sB;
+  p.P += b * p.sD;
+  p.R += b * p.sD;
+  p.D += b * p.sD;
+}
 
 // D entry from its product, FP32 as the accumulators
 __device__ __forceinline__ void epilogue(const CgemmParams& p, int row, int col, float pr, float pi) {
@@ -78,7 +93,9 @@ __global__ __launch_bounds__(NTHR, 2) void k_cgemm32_filter(CgemmParams p) {
     L = (L & 7) * per + (L >> 3);
   }
   const int kc = L / p.tiles, tile = L - kc * p.tiles;
-  const int tm = tile / p.tiles_n, tn = tile - tm * p.tiles_n;
+  const int bt = tile / p.tiles1, tile1 = tile - bt * p.tiles1;
+  select(p, bt);
+  const int tm = tile1 / p.tiles_n, tn = tile1 - tm * p.tiles_n;
   const int row0 = tm * BM, col0 = tn * BN;
   const int lane = tid & 63, wave = tid >> 6;
   const int wr = wave >> 1, wc = wave & 1;
@@ -202,7 +219,9 @@ __global__ __launch_bounds__(256) void k_cgemm32_reduce(CgemmParams p, int parts
   constexpr int PER = BM * BN;
   if (e >= (int64_t)p.tiles * PER) return;
   const int tile = (int)(e / PER), w = (int)(e - (int64_t)tile * PER);
-  const int tm = tile / p.tiles_n, tn = tile - tm * p.tiles_n;
+  const int bt = tile / p.tiles1, tile1 = tile - bt * p.tiles1;
+  select(p, bt);
+  const int tm = tile1 / p.tiles_n, tn = tile1 - tm * p.tiles_n;
   const int row = tm * BM + (w & (BM - 1)), col = tn * BN + w / BM;
   if (row >= p.M || col >= p.N) return;
   const zf* src = p.part + e;
@@ -288,8 +307,8 @@ gevp_status launch_cgemm32_filter(gevp_ctx* c, int64_t m, int64_t n, int64_t k, 
                                   int64_t lda, const void* G, int64_t ldg, const void* P,
                                   int64_t ldp, const void* R, int64_t ldr, void* D, int64_t ldd,
                                   const double* al, const double* be, const double* ga,
-                                  const double* de) {
-  if (m <= 0 || n <= 0) return GEVP_OK;
+                                  const double* de, int batch, int64_t sA, int64_t sG, int64_t sD) {
+  if (m <= 0 || n <= 0 || batch <= 0) return GEVP_OK;
   CgemmParams p;
   p.M = (int)m;
   p.N = (int)n;
@@ -309,7 +328,11 @@ gevp_status launch_cgemm32_filter(gevp_ctx* c, int64_t m, int64_t n, int64_t k, 
   p.gamma = ga;
   p.delta = de;
   p.tiles_n = (int)((n + BN - 1) / BN);
-  const int64_t total = ((m + BM - 1) / BM) * p.tiles_n;
+  p.tiles1 = (int)(((m + BM - 1) / BM) * p.tiles_n);
+  p.sA = sA;
+  p.sB = sG;
+  p.sD = sD;
+  const int64_t total = (int64_t)p.tiles1 * batch;
   const int nk = (p.K + KT - 1) / KT;
   constexpr int64_t MAX_PARTS = (int64_t)(SKW_BYTES / (sizeof(zf) * BM * BN));
   int parts = c->no_split ? 1

@@ -352,7 +352,8 @@ gevp_status launch_cgemm32_filter(gevp_ctx* c, int64_t m, int64_t n, int64_t k, 
                                   int64_t lda, const void* G, int64_t ldg, const void* P,
                                   int64_t ldp, const void* R, int64_t ldr, void* D, int64_t ldd,
                                   const double* al, const double* be, const double* ga,
-                                  const double* de);
+                                  const double* de, int batch = 1, int64_t sA = 0, int64_t sG = 0,
+                                  int64_t sD = 0);
 gevp_status launch_to_c32(gevp_ctx* c, int64_t rows, int64_t cols, const zd* S, int64_t lds,
                           void* D, int64_t ldd);
 gevp_status launch_resid_start32(gevp_ctx* c, int64_t rows, int64_t cols, const zd* W,
