@@ -77,9 +77,12 @@ struct gevp_ctx {
   // false for the worker contexts of gevp_solve_batched: problems already run
   // concurrently there, so a solve keeps all its work on its own stream
   bool inner_streams = true;
-  // other work shares the GPU with this stream (batched workers, the second
-  // stream): no launch that must have all its work-groups resident at once
+  // no launch that must have all its work-groups resident at once: the second
+  // stream, whose eigensolve runs beside the main stream's work (nothing to gain,
+  // and its waiting work-groups would take compute units), and a handle where one
+  // gave up
   bool shared_gpu = false;
+  bool batch_worker = false;  // takes turns with the others for such a launch
   // panel stream of the Cholesky factorisation and its two events (on demand)
   gevp_ctx* panel = nullptr;
   hipEvent_t pev[2] = {nullptr, nullptr};

@@ -20,6 +20,8 @@
 //     FP64 matrix cores.
 #include <atomic>
 #include <cfloat>
+#include <chrono>
+#include <thread>
 
 #include "common.h"
 
@@ -1112,7 +1114,7 @@ size_t heev_work_bytes(int64_t n) {
   return b;
 }
 
-// One launch per reflector, for streams that share the GPU, under capture and
+// One launch per reflector, for a solve's second stream, under capture and
 // where the single launch gave up: the kernel boundary is the grid-wide barrier (a cooperative single launch with
 // explicit barriers measured slower, because each barrier must write back and
 // invalidate the XCD caches).  Issued one by
@@ -1180,9 +1182,17 @@ constexpr int TRD_SPINS = 1 << 18;  // some tenths of a second
 // compute units
 struct TrdTurn {
   std::atomic<bool>* busy = nullptr;
-  explicit TrdTurn(int device) {
+  TrdTurn(int device, double wait_s) {
     static std::atomic<bool> taken[64];
-    if (device >= 0 && device < 64 && !taken[device].exchange(true)) busy = &taken[device];
+    if (device < 0 || device >= 64) return;
+    const auto start = std::chrono::steady_clock::now();
+    do {
+      if (!taken[device].exchange(true)) {
+        busy = &taken[device];
+        return;
+      }
+      std::this_thread::yield();
+    } while (std::chrono::duration<double>(std::chrono::steady_clock::now() - start).count() < wait_s);
   }
   ~TrdTurn() {
     if (busy) busy->store(false);
@@ -1218,7 +1228,11 @@ gevp_status hetrd_all(gevp_ctx* c, const TrdArgs& a, TrdExchange x, bool* done) 
     return GEVP_OK;
   }
   if (per_cu * cus < groups) return GEVP_OK;
-  TrdTurn turn(c->device);
+  // a batch worker waits for its turn with its stream empty, so that the turn
+  // lasts no longer than the launch (eight problems of n = 1500 to 3000: 90 ms
+  // with a launch per reflector, 76 ms with turns)
+  if (c->batch_worker) GEVP_HIP_TRY(hipStreamSynchronize(c->stream));
+  TrdTurn turn(c->device, c->batch_worker ? 5e-3 : 0.0);
   if (!turn.busy) return GEVP_OK;
   x.ld = (n + 15) / 16 * 16;
   const int64_t words = (int64_t)n * 4 * x.ld;
@@ -1279,8 +1293,8 @@ gevp_status heev_small(gevp_ctx* c, int64_t n64, zd* H, int64_t ldh, double* the
   // Many work-groups in one launch where they can be resident together; one
   // work-group where the exchange through memory costs more than it spreads (the
   // whole eigensolver at n = 32, 64, 116: 0.25, 0.47, 0.94 ms with one, 0.28,
-  // 0.45, 0.76 with many); a launch per reflector where other streams share the
-  // GPU.  The exchange lies in the tridiagonal solver's workspace, not
+  // 0.45, 0.76 with many); a launch per reflector on the second stream of a solve,
+  // under capture and where another handle has its turn.  The exchange lies in the tridiagonal solver's workspace, not
   // in use yet (40 n^2 bytes against 32 n (n + 15): enough from n = 60).
   bool done = false;
   if (n > TRD1_MAX && n <= TRDM_MAX && !c->shared_gpu) {

@@ -1289,7 +1289,7 @@ gevp_status gevp_solve_batched(gevp_handle h, const gevp_opts* opts, int count, 
     }
     w->owns_stream = true;
     w->inner_streams = false;
-    w->shared_gpu = true;
+    w->batch_worker = true;
     h->workers.push_back(w);
   }
   // event timing of the filter launches (profiling flag 2) carries over; the
