@@ -330,6 +330,17 @@ gevp_status launch_max_offident(gevp_ctx* c, int64_t n, const zd* M, int64_t ldm
 gevp_status lanczos_bounds(gevp_ctx* c, int64_t n, const zd* M, int64_t ldm, int steps,
                            unsigned long long seed, double frac, double* out, void* work);
 size_t lanczos_work_bytes(int64_t n, int steps);
+// up to three runs (in one launch where that is possible) with two workspaces of
+// lanczos_work_bytes
+struct LanczosRun {
+  const zd* M;
+  int64_t ldm;
+  int steps;
+  unsigned long long seed;
+  double* out;
+};
+gevp_status lanczos_bounds_all(gevp_ctx* c, int64_t n, const LanczosRun* runs, int count, double frac,
+                               void* work, void* work2);
 
 // Controller (single work-group): decides convergence, the next filter
 // interval, per-column degrees, the degree-sorted column permutation and the

@@ -18,12 +18,9 @@
 //     diag(1/tau) plus the strict upper triangle of V^H V, so Z <- Z - V (T
 //     (V^H Z)) is a Gram product, a triangular solve and two products on the
 //     FP64 matrix cores.
-#include <atomic>
 #include <cfloat>
-#include <chrono>
-#include <thread>
 
-#include "common.h"
+#include "exchange.h"
 
 namespace {
 constexpr int HT = 256;  // threads per work-group
@@ -233,28 +230,6 @@ __global__ __launch_bounds__(HT) void k_hetrd_step(TrdArgs a, int s) {
 // reflector by itself, exactly as every other wave forms it (the same operations
 // in the same order).  One exchange per reflector, no other communication.
 
-// sum over the wave, the same in every lane: within rows of 16 lanes, then
-// across the rows, by lane shifts of the vector unit
-template <int CTRL, int ROWS>
-__device__ __forceinline__ double dpp_move(double v) {
-  const unsigned long long u = __double_as_longlong(v);
-  const unsigned lo = __builtin_amdgcn_update_dpp(0, (unsigned)u, CTRL, ROWS, 0xf, true);
-  const unsigned hi = __builtin_amdgcn_update_dpp(0, (unsigned)(u >> 32), CTRL, ROWS, 0xf, true);
-  return __longlong_as_double(((unsigned long long)hi << 32) | lo);
-}
-__device__ __forceinline__ double wave_total(double v) {
-  v += dpp_move<0x111, 0xf>(v);  // row_shr 1, 2, 4, 8
-  v += dpp_move<0x112, 0xf>(v);
-  v += dpp_move<0x114, 0xf>(v);
-  v += dpp_move<0x118, 0xf>(v);
-  v += dpp_move<0x142, 0xa>(v);  // lane 15 of rows 0 and 2 to the next row
-  v += dpp_move<0x143, 0xc>(v);  // lane 31 to the upper half
-  const unsigned long long u = __double_as_longlong(v);
-  const unsigned lo = __builtin_amdgcn_readlane((unsigned)u, 63);
-  const unsigned hi = __builtin_amdgcn_readlane((unsigned)(u >> 32), 63);
-  return __longlong_as_double(((unsigned long long)hi << 32) | lo);
-}
-
 struct Reflector {
   zd tau, scal, K, wps;  // K of the previous reflector and w_{s-1}(s)
   double d, beta;
@@ -375,14 +350,9 @@ __global__ __launch_bounds__(1024) void k_hetrd_one(TrdArgs a) {
 
 // 60 < n <= 2048: eight columns a work-group, a row of each in every thread (R
 // rows when there are more than threads), one launch.  The exchange
-// goes through device memory with accesses that are coherent over the XCDs by
-// themselves (agent-scope atomics of 8 bytes), every step into fresh memory that
-// was filled with a value no arithmetic produces: a reader polls the entries it
-// needs until they differ from it, so a step costs one trip from writer to reader
-// and no cache is written back or invalidated.  A work-group publishes its eight
-// p as one line of 128 bytes.  A wait that exceeds its bound raises *err and ends
-// the work-group (and with it, in time, the others); the host then takes the
-// launch per reflector.
+// goes through device memory (exchange.h).  A work-group publishes its eight p as
+// one line of 128 bytes.  When a wait gives up the host takes the launch per
+// reflector.
 // Latency bounds it: of the 4.4 us a step takes at n = 948 about half is the way
 // of p through memory, the rest three sums over the work-group and eight columns
 // of FP64 arithmetic.  Measured whole, n = 256, 512, 948: 0.71, 1.82, 4.18 ms,
@@ -390,7 +360,6 @@ __global__ __launch_bounds__(1024) void k_hetrd_one(TrdArgs a) {
 // and the reflector formed by every wave took 10 us a step at n = 948 (the reads
 // of p by 237 work-groups queue up); 256 threads instead of 512 4.9 us.
 constexpr int TRDM_MAX = 2048;
-constexpr unsigned long long HOLE = 0x7ff8a5c35a3cf00dull;  // a NaN with a payload of its own
 struct TrdExchange {
   // step t: p_t, then column t + 1, each as n real and n imaginary parts (a wave's
   // read is one contiguous piece) of ld entries
@@ -399,57 +368,6 @@ struct TrdExchange {
   int* err;
   int spin;               // polls before a wait gives up
 };
-__device__ __forceinline__ void publish(unsigned long long* dst, double v) {
-  unsigned long long u = __double_as_longlong(v);
-  u = u == HOLE ? 0x7ff8000000000000ull : u;
-  __hip_atomic_store(dst, u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ unsigned long long peek(const unsigned long long* src) {
-  return __hip_atomic_load(src, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__global__ __launch_bounds__(256) void k_trd_holes(unsigned long long* x, int64_t words, int* err) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i == 0) *err = 0;
-  for (int64_t k = i; k < words; k += (int64_t)gridDim.x * 256) x[k] = HOLE;
-}
-// Sums over the wave of 16 values a lane: the lane returns the total of value
-// 4 * (lane / 16) + (lane & 3).  The first two levels exchange halves of the
-// values as they add them, the last two rotate within rows of 16 lanes.
-__device__ __forceinline__ double2 swap_halves32(double a, double b) {
-  const unsigned long long ua = __double_as_longlong(a), ub = __double_as_longlong(b);
-  const auto lo = __builtin_amdgcn_permlane32_swap((unsigned)ua, (unsigned)ub, false, false);
-  const auto hi = __builtin_amdgcn_permlane32_swap((unsigned)(ua >> 32), (unsigned)(ub >> 32), false, false);
-  return make_double2(__longlong_as_double(((unsigned long long)hi[0] << 32) | lo[0]),
-                      __longlong_as_double(((unsigned long long)hi[1] << 32) | lo[1]));
-}
-__device__ __forceinline__ double2 swap_halves16(double a, double b) {
-  const unsigned long long ua = __double_as_longlong(a), ub = __double_as_longlong(b);
-  const auto lo = __builtin_amdgcn_permlane16_swap((unsigned)ua, (unsigned)ub, false, false);
-  const auto hi = __builtin_amdgcn_permlane16_swap((unsigned)(ua >> 32), (unsigned)(ub >> 32), false, false);
-  return make_double2(__longlong_as_double(((unsigned long long)hi[0] << 32) | lo[0]),
-                      __longlong_as_double(((unsigned long long)hi[1] << 32) | lo[1]));
-}
-__device__ __forceinline__ double wave_totals16(const double (&v)[16]) {
-  double a[8], b[4];
-#pragma unroll
-  for (int k = 0; k < 8; ++k) {
-    const double2 t = swap_halves32(v[k], v[k + 8]);
-    a[k] = t.x + t.y;
-  }
-#pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    const double2 t = swap_halves16(a[k], a[k + 4]);
-    b[k] = t.x + t.y;
-    b[k] += dpp_move<0x128, 0xf>(b[k]);  // row_ror 8, 4, 2, 1
-    b[k] += dpp_move<0x124, 0xf>(b[k]);
-    b[k] += dpp_move<0x122, 0xf>(b[k]);
-    b[k] += dpp_move<0x121, 0xf>(b[k]);
-  }
-  const int l = threadIdx.x & 3;
-  const double x = l & 1 ? b[1] : b[0], y = l & 1 ? b[3] : b[2];
-  return l & 2 ? y : x;
-}
-
 constexpr int TRD_COLS = 8;
 template <int T, int R>
 __global__ __launch_bounds__(T) void k_hetrd_all(TrdArgs a, TrdExchange e) {
@@ -1175,45 +1093,13 @@ gevp_status hetrd_launches(gevp_ctx* c, const TrdArgs& a, int G, size_t sh3) {
 }  // namespace
 
 namespace {
-constexpr int TRD_SPINS = 1 << 18;  // some tenths of a second
-
-// one single-launch tridiagonalisation at a time per device and process: two of
-// them, each with a part of its work-groups resident, would wait for the other's
-// compute units
-struct TrdTurn {
-  std::atomic<bool>* busy = nullptr;
-  TrdTurn(int device, double wait_s) {
-    static std::atomic<bool> taken[64];
-    if (device < 0 || device >= 64) return;
-    const auto start = std::chrono::steady_clock::now();
-    do {
-      if (!taken[device].exchange(true)) {
-        busy = &taken[device];
-        return;
-      }
-      std::this_thread::yield();
-    } while (std::chrono::duration<double>(std::chrono::steady_clock::now() - start).count() < wait_s);
-  }
-  ~TrdTurn() {
-    if (busy) busy->store(false);
-  }
-};
-
 // The tridiagonalisation in one launch; *done = false when it may not run, could
-// not be launched or gave up, H being unchanged.  An ordinary launch: kernels of
-// other streams end by themselves, so its work-groups, no more than fit the GPU
-// at once, all become resident.  (A cooperative launch gives the process one more
-// hardware queue for good, which slowed batches on eight streams from 94 to 139
-// ms.)  A handle whose launch gave up once (its stream may be confined to some of
-// the compute units) does not try again.
+// not be launched or gave up, H being unchanged.  A handle whose launch gave up
+// once (its stream may be confined to some of the compute units) does not try
+// again.
 gevp_status hetrd_all(gevp_ctx* c, const TrdArgs& a, TrdExchange x, bool* done) {
   *done = false;
-  // the outcome is read back, which a capture cannot hold
-  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(c->stream, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) {
-    (void)hipGetLastError();
-    return GEVP_OK;
-  }
+  if (!resident_allowed(c)) return GEVP_OK;
   const int n = a.n;
   auto* f = n <= 256    ? k_hetrd_all<256, 1>
             : n <= 512  ? k_hetrd_all<512, 1>
@@ -1221,24 +1107,15 @@ gevp_status hetrd_all(gevp_ctx* c, const TrdArgs& a, TrdExchange x, bool* done) 
             : n <= 1536 ? k_hetrd_all<512, 3>
                         : k_hetrd_all<512, 4>;
   const int threads = n <= 256 ? 256 : 512, groups = (n + TRD_COLS - 1) / TRD_COLS;
-  int per_cu = 0, cus = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, f, threads, 0) != hipSuccess ||
-      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device) != hipSuccess) {
-    (void)hipGetLastError();
-    return GEVP_OK;
-  }
-  if (per_cu * cus < groups) return GEVP_OK;
+  if (!resident_fits(c, f, threads, groups)) return GEVP_OK;
   // a batch worker waits for its turn with its stream empty, so that the turn
   // lasts no longer than the launch (eight problems of n = 1500 to 3000: 90 ms
   // with a launch per reflector, 76 ms with turns)
   if (c->batch_worker) GEVP_HIP_TRY(hipStreamSynchronize(c->stream));
-  TrdTurn turn(c->device, c->batch_worker ? 5e-3 : 0.0);
+  LaunchTurn turn(c->device, c->batch_worker ? 5e-3 : 0.0);
   if (!turn.busy) return GEVP_OK;
   x.ld = (n + 15) / 16 * 16;
-  const int64_t words = (int64_t)n * 4 * x.ld;
-  hipLaunchKernelGGL(k_trd_holes, dim3((unsigned)std::min<int64_t>((words + 255) / 256, 4096)), dim3(256), 0,
-                     c->stream, x.x, words, x.err);
-  GEVP_HIP_TRY(hipGetLastError());
+  GEVP_TRY(fill_holes(c, x.x, (int64_t)n * 4 * x.ld, x.err));
   hipLaunchKernelGGL(f, dim3((unsigned)groups), dim3((unsigned)threads), 0, c->stream, a, x);
   const hipError_t launched = hipGetLastError();
   int err = 1;
@@ -1298,7 +1175,7 @@ gevp_status heev_small(gevp_ctx* c, int64_t n64, zd* H, int64_t ldh, double* the
   // in use yet (40 n^2 bytes against 32 n (n + 15): enough from n = 60).
   bool done = false;
   if (n > TRD1_MAX && n <= TRDM_MAX && !c->shared_gpu) {
-    TrdExchange x{(unsigned long long*)tw, 0, (int*)a.pb, TRD_SPINS};
+    TrdExchange x{(unsigned long long*)tw, 0, (int*)a.pb, EXCHANGE_SPINS};
     GEVP_TRY(hetrd_all(c, a, x, &done));
   }
   if (n <= TRD1_MAX && !c->shared_gpu) {

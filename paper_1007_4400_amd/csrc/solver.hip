@@ -859,11 +859,10 @@ gevp_status gevp_solve(gevp_handle h, const gevp_opts* opts, int64_t n, const vo
     GEVP_TRY(lanczos_bounds(ax, n, C, n, lz, o.seed ^ 0xC0FFEEull, frac, bC, lanw2));
     GEVP_HIP_TRY(hipEventRecord(evs.bounds, ax->stream));
   } else {
-    GEVP_TRY(lanczos_bounds(c, n, C, n, lz, o.seed ^ 0xC0FFEEull, frac, bC, lanw));
-  }
-  if (!spec) {
-    GEVP_TRY(lanczos_bounds(c, n, Af, n, lzn, o.seed ^ 0xA11CEull, frac, bA, lanw));
-    GEVP_TRY(lanczos_bounds(c, n, Bf, n, lzn, o.seed ^ 0xB0Bull, frac, bB, lanw));
+    const LanczosRun runs[3] = {{C, n, lz, o.seed ^ 0xC0FFEEull, bC},
+                                {Af, n, lzn, o.seed ^ 0xA11CEull, bA},
+                                {Bf, n, lzn, o.seed ^ 0xB0Bull, bB}};
+    GEVP_TRY(lanczos_bounds_all(c, n, runs, 3, frac, lanw, lanw2));
     GEVP_TRY(launch_copy_real(c, 1, bA + 5, norms));
     GEVP_TRY(launch_copy_real(c, 1, bB + 5, norms + 1));
   }
