@@ -227,6 +227,7 @@ __global__ __launch_bounds__(256) void k_cgemm32_reduce(CgemmParams p, int parts
   const zf* src = p.part + e;
   const int64_t st = (int64_t)p.tiles * PER;
   float sr = 0.f, si = 0.f;
+#pragma unroll 8  // eight loads in flight
   for (int q = 0; q < parts; ++q) {
     const zf v = src[q * st];
     sr += v.x;

@@ -463,6 +463,7 @@ __global__ __launch_bounds__(256) void k_zgemm_splitk_reduce(ZgemmParams p) {
   const int row = tm * BM + rl, col = tn * BN + cl;
   if (row >= p.M || col >= p.N) return;
   double ar = 0.0, ai = 0.0;
+#pragma unroll 8  // eight loads in flight
   for (int kc = 0; kc < p.splits; ++kc) {
     const zd v = p.part[((int64_t)kc * p.tiles + tile) * per + w];
     ar += v.x;
@@ -491,13 +492,15 @@ __global__ __launch_bounds__(256) void k_zgemm_splitk_reduce(ZgemmParams p) {
 
 // K splits for T tiles of nk slices when `slots` work-groups run at once:
 // minimise rounds(T s) * ceil(nk / s) plus the reduction (about 1/100 of a
-// slice per partial tile), keeping at least 8 slices per part
+// slice per partial tile), keeping at least 2 slices per part: with few tiles it
+// is latency that counts, and a slice is about 2 us of it.  256 x 48 x 256: two
+// parts of 8 slices 20.4 + 4.6 us, eight of 2 9.4 + 3.4 us.
 int zgemm_splits(int64_t T, int nk, int64_t slots, int64_t max_parts) {
   int best = 1;
   double best_cost = (double)((T + slots - 1) / slots) * nk;
   for (int s = 2; s <= 16; ++s) {
     const int nks = (nk + s - 1) / s;
-    if (nks < 8) break;
+    if (nks < 2) break;
     const int se = (nk + nks - 1) / nks;
     if (T * se > max_parts) break;
     const double cost = (double)((T * se + slots - 1) / slots) * nks + 0.01 * (double)(T * se) + 2.0;
