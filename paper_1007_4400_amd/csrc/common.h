@@ -78,11 +78,12 @@ struct gevp_ctx {
   // concurrently there, so a solve keeps all its work on its own stream
   bool inner_streams = true;
   // no launch that must have all its work-groups resident at once: the second
-  // stream, whose eigensolve runs beside the main stream's work (nothing to gain,
-  // and its waiting work-groups would take compute units), and a handle where one
-  // gave up
+  // stream, unless the solve holds the turn for it, and a handle where one gave up
   bool shared_gpu = false;
   bool batch_worker = false;  // takes turns with the others for such a launch
+  // where set, such launches raise this flag and go on (their turn is held by the
+  // caller, which looks at the flag when it next waits for the stream)
+  int* defer_err = nullptr;
   // panel stream of the Cholesky factorisation and its two events (on demand)
   gevp_ctx* panel = nullptr;
   hipEvent_t pev[2] = {nullptr, nullptr};

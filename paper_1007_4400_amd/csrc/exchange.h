@@ -29,7 +29,7 @@ __device__ __forceinline__ unsigned long long peek(const unsigned long long* src
 }
 __global__ __launch_bounds__(256) void k_fill_holes(unsigned long long* x, int64_t words, int* err) {
   const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i == 0) *err = 0;
+  if (i == 0 && err) *err = 0;
   for (int64_t k = i; k < words; k += (int64_t)gridDim.x * 256) x[k] = HOLE;
 }
 
@@ -98,7 +98,7 @@ __device__ __forceinline__ double wave_totals16(const double (&v)[16]) {
 constexpr int EXCHANGE_SPINS = 1 << 18;  // polls before a wait gives up: some tenths of a second
 
 namespace {
-gevp_status fill_holes(gevp_ctx* c, unsigned long long* x, int64_t words, int* err) {
+inline gevp_status fill_holes(gevp_ctx* c, unsigned long long* x, int64_t words, int* err) {
   hipLaunchKernelGGL(k_fill_holes, dim3((unsigned)std::min<int64_t>((words + 255) / 256, 4096)), dim3(256), 0,
                      c->stream, x, words, err);
   GEVP_HIP_TRY(hipGetLastError());

@@ -1032,7 +1032,7 @@ size_t heev_work_bytes(int64_t n) {
   return b;
 }
 
-// One launch per reflector, for a solve's second stream, under capture and
+// One launch per reflector, under capture, where another handle has its turn and
 // where the single launch gave up: the kernel boundary is the grid-wide barrier (a cooperative single launch with
 // explicit barriers measured slower, because each barrier must write back and
 // invalidate the XCD caches).  Issued one by
@@ -1108,14 +1108,23 @@ gevp_status hetrd_all(gevp_ctx* c, const TrdArgs& a, TrdExchange x, bool* done) 
                         : k_hetrd_all<512, 4>;
   const int threads = n <= 256 ? 256 : 512, groups = (n + TRD_COLS - 1) / TRD_COLS;
   if (!resident_fits(c, f, threads, groups)) return GEVP_OK;
+  x.ld = (n + 15) / 16 * 16;
+  const int64_t words = (int64_t)n * 4 * x.ld;
+  if (c->defer_err) {
+    x.err = c->defer_err;
+    GEVP_TRY(fill_holes(c, x.x, words, nullptr));
+    hipLaunchKernelGGL(f, dim3((unsigned)groups), dim3((unsigned)threads), 0, c->stream, a, x);
+    GEVP_HIP_TRY(hipGetLastError());
+    *done = true;
+    return GEVP_OK;
+  }
   // a batch worker waits for its turn with its stream empty, so that the turn
   // lasts no longer than the launch (eight problems of n = 1500 to 3000: 90 ms
   // with a launch per reflector, 76 ms with turns)
   if (c->batch_worker) GEVP_HIP_TRY(hipStreamSynchronize(c->stream));
   LaunchTurn turn(c->device, c->batch_worker ? 5e-3 : 0.0);
   if (!turn.busy) return GEVP_OK;
-  x.ld = (n + 15) / 16 * 16;
-  GEVP_TRY(fill_holes(c, x.x, (int64_t)n * 4 * x.ld, x.err));
+  GEVP_TRY(fill_holes(c, x.x, words, x.err));
   hipLaunchKernelGGL(f, dim3((unsigned)groups), dim3((unsigned)threads), 0, c->stream, a, x);
   const hipError_t launched = hipGetLastError();
   int err = 1;
@@ -1170,8 +1179,8 @@ gevp_status heev_small(gevp_ctx* c, int64_t n64, zd* H, int64_t ldh, double* the
   // Many work-groups in one launch where they can be resident together; one
   // work-group where the exchange through memory costs more than it spreads (the
   // whole eigensolver at n = 32, 64, 116: 0.25, 0.47, 0.94 ms with one, 0.28,
-  // 0.45, 0.76 with many); a launch per reflector on the second stream of a solve,
-  // under capture and where another handle has its turn.  The exchange lies in the tridiagonal solver's workspace, not
+  // 0.45, 0.76 with many); a launch per reflector under capture and where another
+  // handle has its turn.  The exchange lies in the tridiagonal solver's workspace, not
   // in use yet (40 n^2 bytes against 32 n (n + 15): enough from n = 60).
   bool done = false;
   if (n > TRD1_MAX && n <= TRDM_MAX && !c->shared_gpu) {

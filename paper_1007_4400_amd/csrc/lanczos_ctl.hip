@@ -562,12 +562,13 @@ gevp_status lanczos_resident(gevp_ctx* c, int64_t n, const LanczosRun* runs, int
   const bool together = resident_fits(c, f, threads, (int64_t)a.groups * count);
   if (!together && !resident_fits(c, f, threads, a.groups)) return GEVP_OK;
   if (c->batch_worker) GEVP_HIP_TRY(hipStreamSynchronize(c->stream));
-  LaunchTurn turn(c->device, c->batch_worker ? 5e-3 : 0.0);
-  if (!turn.busy) return GEVP_OK;
-  a.err = (int*)((zd*)area[0] + 3 * n);
+  LaunchTurn turn(c->defer_err ? -1 : c->device, c->batch_worker ? 5e-3 : 0.0);
+  if (!turn.busy && !c->defer_err) return GEVP_OK;
+  a.err = c->defer_err ? c->defer_err : (int*)((zd*)area[0] + 3 * n);
   for (int k = 0; k < 2; ++k)
     if (used[k])
-      GEVP_TRY(fill_holes(c, (unsigned long long*)(area[k] + head), (int64_t)(used[k] / 8), a.err));
+      GEVP_TRY(fill_holes(c, (unsigned long long*)(area[k] + head), (int64_t)(used[k] / 8),
+                          c->defer_err ? nullptr : a.err));
   for (int r = 0; r < count; ++r) GEVP_TRY(launch_randn(c, n, 1, (zd*)a.job[r].v0, n, 0, runs[r].seed));
   hipError_t launched = hipSuccess;
   for (int r = 0; r < (together ? 1 : count); ++r) {
@@ -575,6 +576,11 @@ gevp_status lanczos_resident(gevp_ctx* c, int64_t n, const LanczosRun* runs, int
     hipLaunchKernelGGL(f, dim3((unsigned)(a.groups * (together ? count : 1))), dim3((unsigned)threads), 0,
                        c->stream, a);
     if (launched == hipSuccess) launched = hipGetLastError();
+  }
+  if (c->defer_err) {
+    GEVP_HIP_TRY(launched);
+    *done = true;
+    return GEVP_OK;
   }
   int err = 1;
   GEVP_HIP_TRY(hipMemcpyAsync(&err, a.err, sizeof(int), hipMemcpyDeviceToHost, c->stream));
