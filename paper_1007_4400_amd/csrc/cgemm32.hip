@@ -110,8 +110,11 @@ __global__ __launch_bounds__(NTHR, 2) void k_cgemm32_filter(CgemmParams p) {
       acc2[i][j] = f4{0, 0, 0, 0};
       acc3[i][j] = f4{0, 0, 0, 0};
     }
-  zf ra[4], rb[4];
-  auto load = [&](int k0) {
+  // PRE slices of operands in flight, in registers (n = 8192, 645 columns with the
+  // copy to FP32 3.08 -> 2.82 ms against one, n = 4096, 410 columns 0.61 -> 0.54)
+  constexpr int PRE = 4;
+  zf sa_[PRE][4], sb_[PRE][4];
+  auto load = [&](zf (&ra)[4], zf (&rb)[4], int k0) {
     const int m = tid & 63, gm = row0 + m;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -125,7 +128,7 @@ __global__ __launch_bounds__(NTHR, 2) void k_cgemm32_filter(CgemmParams p) {
       rb[i] = (gn < p.N && gk < p.K) ? p.B[gk + (int64_t)gn * p.ldb] : make_float2(0.f, 0.f);
     }
   };
-  auto store = [&](int buf) {
+  auto store = [&](const zf (&ra)[4], const zf (&rb)[4], int buf) {
     const int m = tid & 63;
 #pragma unroll
     for (int i = 0; i < 4; ++i) As[buf][(tid >> 6) + 4 * i][m] = ra[i];
@@ -135,14 +138,17 @@ __global__ __launch_bounds__(NTHR, 2) void k_cgemm32_filter(CgemmParams p) {
   };
   const int nk = (p.K + KT - 1) / KT;
   const int t0 = kc * p.nks, t1 = min(nk, t0 + p.nks);
+#pragma unroll
+  for (int q = 0; q < PRE; ++q)
+    if (t0 + q < t1) load(sa_[q], sb_[q], (t0 + q) * KT);
   if (t0 < t1) {
-    load(t0 * KT);
-    store(0);
+    store(sa_[0], sb_[0], 0);
+    if (t0 + PRE < t1) load(sa_[0], sb_[0], (t0 + PRE) * KT);
   }
   __syncthreads();
-  for (int t = t0; t < t1; ++t) {
-    const int cur = (t - t0) & 1;
-    if (t + 1 < t1) load((t + 1) * KT);
+  // slice t lies in LDS buffer t - t0 mod 2, slice t + 1 in register set t + 1 - t0 mod PRE
+  auto slice = [&](zf (&na)[4], zf (&nb)[4], int t, int cur) {
+    if (t >= t1) return;  // uniform
 #pragma unroll
     for (int ks = 0; ks < KT / 4; ++ks) {
       const int kk = ks * 4 + lg;
@@ -174,8 +180,17 @@ __global__ __launch_bounds__(NTHR, 2) void k_cgemm32_filter(CgemmParams p) {
         for (int j = 0; j < 2; ++j)
           acc3[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(sa[i], sb[j], acc3[i][j], 0, 0, 0);
     }
-    if (t + 1 < t1) store(cur ^ 1);
+    if (t + 1 < t1) {
+      store(na, nb, cur ^ 1);
+      if (t + 1 + PRE < t1) load(na, nb, (t + 1 + PRE) * KT);
+    }
     __syncthreads();
+  };
+  for (int t = t0; t < t1; t += PRE) {
+    slice(sa_[1], sb_[1], t, 0);
+    slice(sa_[2], sb_[2], t + 1, 1);
+    slice(sa_[3], sb_[3], t + 2, 0);
+    slice(sa_[0], sb_[0], t + 3, 1);
   }
   f4 accR[2][2], accI[2][2];  // the complex result of the three products
 #pragma unroll
@@ -236,19 +251,26 @@ __global__ __launch_bounds__(256) void k_cgemm32_reduce(CgemmParams p, int parts
   epilogue(p, row, col, sr, si);
 }
 
-// Parts of nk K-slices for T tiles when `slots` work-groups run at once: a
-// slice costs 1, the second kernel 3 and its reads 0.005 a partial tile; at
-// least four slices a part.  Measured at 1001 x 116 x 1001 (32 tiles, 63
-// slices): one work-group per tile 92 us, cut 14.5 + 7 us.
-inline int split32(int64_t T, int nk, int64_t slots, int64_t max_parts) {
+// K splits for T tiles of nk slices on `cus` compute units: the slices of a part
+// one after the other, at 3/4 of their time each where several work-groups share a
+// unit (one's loads run behind another's products), plus the sum of the partial
+// tiles (a hundredth of a slice each, 3 for the launch), keeping at least four
+// slices a part.  Measured at 1001 x 116 x 1001 (32 tiles, 63 slices): one
+// work-group per tile 92 us, in 8 parts 13.5 + 4.4 us, in 16 14.1 + 4.8 us; at 3000 x
+// 300 x 3000 (235 tiles) in one part 305 us, in 2 268 us.
+inline int split32(int64_t T, int nk, int64_t cus, int64_t max_parts) {
+  auto busy = [&](int64_t groups, int nks) {
+    const int64_t q = (groups + cus - 1) / cus;
+    return (q == 1 ? 1.0 : 0.75 * (double)q) * nks;
+  };
   int best = 1;
-  double cost = (double)((T + slots - 1) / slots) * nk;
+  double cost = busy(T, nk);
   for (int s = 2; s <= 16; ++s) {
     const int nks = (nk + s - 1) / s;
     if (nks < 4) break;
     const int se = (nk + nks - 1) / nks;
     if (T * se > max_parts) break;
-    const double c = (double)((T * se + slots - 1) / slots) * nks + 3.0 + 0.005 * (double)(T * se);
+    const double c = busy(T * se, nks) + 3.0 + 0.01 * (double)(T * se);
     if (c < 0.95 * cost) {
       best = se;
       cost = c;
@@ -337,7 +359,7 @@ gevp_status launch_cgemm32_filter(gevp_ctx* c, int64_t m, int64_t n, int64_t k, 
   const int nk = (p.K + KT - 1) / KT;
   constexpr int64_t MAX_PARTS = (int64_t)(SKW_BYTES / (sizeof(zf) * BM * BN));
   int parts = c->no_split ? 1
-                          : split32(total, nk, std::max<int64_t>(1, 2 * (int64_t)gevp_device_cus(c->device) /
+                          : split32(total, nk, std::max<int64_t>(1, (int64_t)gevp_device_cus(c->device) /
                                                                         std::max(1, c->cu_div)),
                                     MAX_PARTS);
   p.part = nullptr;
