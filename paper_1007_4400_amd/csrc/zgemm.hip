@@ -629,6 +629,17 @@ gevp_status launch_zgemm(gevp_ctx* c, int opA, int opB, int64_t m, int64_t n, in
     else if (n <= BN && (const zd*)D != B) skinny = 2;
   }
   const int nk = (p.K + KT - 1) / KT;
+  const int64_t slots = std::max<int64_t>(1, 2 * (int64_t)gevp_device_cus(c->device) / std::max(1, c->cu_div));
+  // ... unless the K range, one chain of about 1 us per 16 K on skinny tiles, is long
+  // enough for a cut one (2.2 us per 16 K and a second launch) to be shorter: 3000 x
+  // 64 x 960 with its launch 128 us on skinny tiles, 65 cut
+  if (skinny && !c->no_split) {
+    const int s = zgemm_splits(total, nk, slots, SPLIT_TILES_MAX), nks = (nk + s - 1) / s;
+    const int64_t groups = total * ((nk + nks - 1) / nks), tiles = 4 * total;
+    const double chain = (double)nk * (double)((tiles + slots - 1) / slots);
+    const double cut = 2.2 * (double)((groups + slots - 1) / slots * nks) + 0.022 * (double)groups + 6.5;
+    if (s > 1 && cut < 0.9 * chain) skinny = 0;
+  }
   p.upperA = upperA;
   // FP64 GEMM timing (profiling bit 4): not the FP64 filter (coef), which is
   // timed as a filter product by the caller
@@ -647,9 +658,7 @@ gevp_status launch_zgemm(gevp_ctx* c, int opA, int opB, int64_t m, int64_t n, in
   }
   int s = (c->no_split || skinny || mod)
               ? 1
-              : zgemm_splits(total, nk,
-                             std::max<int64_t>(1, 2 * (int64_t)gevp_device_cus(c->device) / std::max(1, c->cu_div)),
-                             SPLIT_TILES_MAX);
+              : zgemm_splits(total, nk, slots, SPLIT_TILES_MAX);
   p.nks = nk > 0 ? (nk + s - 1) / s : 1;
   p.splits = nk > 0 ? (nk + p.nks - 1) / p.nks : 1;
   p.part = nullptr;
