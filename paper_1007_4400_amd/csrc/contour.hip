@@ -39,8 +39,6 @@ namespace {
 constexpr int NB = 64;
 constexpr int QSTREAMS = 4;
 constexpr int64_t GRID_Y_MAX = 65535;  // column kernels put the column index in grid.y
-constexpr int CGS = 16;       // column groups of the block LU (one per wave)
-constexpr int EPT = NB / CGS; // entries per thread
 
 typedef float2 zf;
 
@@ -59,158 +57,225 @@ template <class T>
 __device__ __forceinline__ T zmul(T a, T b) {
   return Cx<T>::mk(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
 }
+
+// One 64 x 64 diagonal block (kb <= 64 rows and columns in use, the rest padded
+// with the identity): M = L U in place without row exchanges (L unit lower, stored
+// strictly below the diagonal), then inv(L) into DinvL and inv(U) into DinvU (64 x
+// 64 each, leading dimension ldi).  *info receives goff + the first failing pivot
+// (1-based); one work-group per matrix of a batch.
+//
+// A chain of 64 pivots, bound by its latency.  Wave 0 factors 16-wide panels of
+// all rows in registers (a lane holds its row's 16 entries; the pivot row comes
+// from its lane by lane reads, no barrier); the row block right of the panel and
+// the trailing update follow from the LDS, on one and on all four waves.  The
+// eight 16 x 16 diagonal blocks of the inverses take one wave each for L and for U
+// (16 lanes a block, a column each); the blocks off the diagonal are built outward,
+// X_IJ = -X_II sum L_IK X_KJ and alike for U, a wave a block.  FP32: 49 us (102 with
+// a barrier per pivot and 1024 threads, whose instructions bound it); contour solve
+// n = 1100 10.6 -> 9.6 ms.
+constexpr int PB = 16, SLD = NB + 1;  // panel width; leading dimension in the LDS
+
+__device__ __forceinline__ float lane_value(float v, int lane) {
+  return __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(v), lane));
+}
+__device__ __forceinline__ double lane_value(double v, int lane) {
+  const unsigned long long u = __double_as_longlong(v);
+  const unsigned lo = __builtin_amdgcn_readlane((unsigned)u, lane);
+  const unsigned hi = __builtin_amdgcn_readlane((unsigned)(u >> 32), lane);
+  return __longlong_as_double(((unsigned long long)hi << 32) | lo);
+}
+// a - b c, a + b c
 template <class T>
-__device__ __forceinline__ T zsub(T a, T b) {
-  return Cx<T>::mk(a.x - b.x, a.y - b.y);
+__device__ __forceinline__ T sub_mul(T a, T b, T c) {
+  return Cx<T>::mk(fma(b.y, c.y, fma(-b.x, c.x, a.x)), fma(-b.y, c.x, fma(-b.x, c.y, a.y)));
+}
+template <class T>
+__device__ __forceinline__ T add_mul(T a, T b, T c) {
+  return Cx<T>::mk(fma(-b.y, c.y, fma(b.x, c.x, a.x)), fma(b.y, c.x, fma(b.x, c.y, a.y)));
+}
+// by value: a conditional between lvalues would be a choice of addresses
+template <class T>
+__device__ __forceinline__ T pick(bool c, T a, T b) {
+  return Cx<T>::mk(c ? a.x : b.x, c ? a.y : b.y);
 }
 
-// One 64 x 64 diagonal block (kb <= 64 rows and columns in use, the rest
-// padded with the identity): M = L U in place without row exchanges (L unit
-// lower, stored strictly below the diagonal), then inv(L) into DinvL and
-// inv(U) into DinvU (64 x 64 each, leading dimension ldi).  1024 threads:
-// thread t holds row i = t % 64 at columns c = t / 64 + 16 m (m = 0..3) in
-// registers, four waves per SIMD, so the latency of one wave's dependent FP64
-// chain is hidden by the others (a quarter of the threads measured 4x slower:
-// latency-bound with one wave per SIMD).  Step
-// k reads the pivot row and column k from double-buffered LDS (one barrier
-// per step); the next step's row and column are published from inside the
-// unrolled update loop under a per-element test, so every register index is a
-// constant.  *info receives goff + the first failing pivot (1-based).
 template <class T>
-__global__ __launch_bounds__(1024) void k_getrf_block(T* M, int64_t ldm, int kb, T* DinvL, T* DinvU,
+__global__ __launch_bounds__(256) void k_getrf_block(T* M, int64_t ldm, int kb, T* DinvL, T* DinvU,
                                                      int64_t ldi, int* info, int goff, int64_t sM,
                                                      int64_t sD) {
-  M += blockIdx.x * sM;  // one work-group per matrix of a batch
+  typedef typename Cx<T>::R R;
+  __shared__ T S[NB * SLD];   // the block, then its factors, [column][row]
+  __shared__ T X[NB * SLD];   // inv(L) strictly below, inv(U) on and above the diagonal
+  __shared__ T W[4][PB * (PB + 1)];
+  M += blockIdx.x * sM;
   DinvL += blockIdx.x * sD;
   DinvU += blockIdx.x * sD;
-  typedef typename Cx<T>::R R;
-  __shared__ T rowb[2][NB], colb[2][NB], rpiv[2];
-  __shared__ T rowl[2][NB], coll[2][NB], rowu[2][NB], colu[2][NB];
-  __shared__ T dinv[NB];
-  // the column group is uniform over a wave: column tests become scalar branches
-  const int tid = threadIdx.x, i = tid & 63, cg = __builtin_amdgcn_readfirstlane(tid >> 6);
-  T a[EPT];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l16 = lane & 15, lg = lane >> 4;
+  const T zero = Cx<T>::mk(R(0), R(0)), one = Cx<T>::mk(R(1), R(0));
+  {
+    T v[NB * NB / 256];
 #pragma unroll
-  for (int m = 0; m < EPT; ++m) {
-    const int j = cg + CGS * m;
-    a[m] = (i < kb && j < kb) ? M[i + (int64_t)j * ldm] : Cx<T>::mk(i == j ? R(1) : R(0), R(0));
-    if (i == 0) rowb[0][j] = a[m];
-    if (j == 0) colb[0][i] = a[m];
-    if (i == 0 && j == 0) {
-      const R d = a[m].x * a[m].x + a[m].y * a[m].y;
-      rpiv[0] = Cx<T>::mk(a[m].x / d, -a[m].y / d);
-      if (!(d > R(0)) || !isfinite(d)) atomicMin(info, goff + 1);
+    for (int q = 0; q < NB * NB / 256; ++q) {
+      const int j = wave + 4 * q;
+      v[q] = pick(lane == j, one, zero);
+      if (lane < kb && j < kb) v[q] = M[lane + (int64_t)j * ldm];
     }
-  }
-  // factorisation; the reciprocal of the next pivot is published with its row
-  for (int k = 0; k < NB; ++k) {
-    const int b = k & 1, nb = b ^ 1;
-    __syncthreads();
-    if (i > k) {
-      const T l = zmul(colb[b][i], rpiv[b]);
-      // all LDS reads first, then a branch-free update (a zero multiplier for
-      // columns j <= k), so the reads are not serialised behind branches
-      T r[EPT];
 #pragma unroll
-      for (int m = 0; m < EPT; ++m) r[m] = rowb[b][cg + CGS * m];
-      const T zero = Cx<T>::mk(R(0), R(0));
-#pragma unroll
-      for (int m = 0; m < EPT; ++m) {
-        const int j = cg + CGS * m;
-        const T lm = (j > k) ? l : zero;
-        const T u = zsub(a[m], zmul(lm, r[m]));
-        a[m] = (j == k) ? l : u;
-      }
-#pragma unroll
-      for (int m = 0; m < EPT; ++m) {
-        const int j = cg + CGS * m;
-        if (j == k + 1) {
-          colb[nb][i] = a[m];
-          if (i == k + 1) {
-            const R d = a[m].x * a[m].x + a[m].y * a[m].y;
-            rpiv[nb] = Cx<T>::mk(a[m].x / d, -a[m].y / d);
-            if (!(d > R(0)) || !isfinite(d)) atomicMin(info, goff + k + 2);
-          }
-        }
-      }
-      if (i == k + 1) {
-#pragma unroll
-        for (int m = 0; m < EPT; ++m) rowb[nb][cg + CGS * m] = a[m];
-      }
-    }
-  }
-  // store the factors; diagonal inverses of U for the backward sweep; the
-  // first step's operands of the inverse sweeps
-  T bl[EPT], bu[EPT];
-#pragma unroll
-  for (int m = 0; m < EPT; ++m) {
-    const int j = cg + CGS * m;
-    if (i < kb && j < kb) M[i + (int64_t)j * ldm] = a[m];
-    if (j == i) {
-      const R d = a[m].x * a[m].x + a[m].y * a[m].y;
-      dinv[i] = Cx<T>::mk(a[m].x / d, -a[m].y / d);
-    }
-    const R e = (j == i) ? R(1) : R(0);
-    bl[m] = Cx<T>::mk(e, R(0));
-    bu[m] = Cx<T>::mk(e, R(0));
-    if (i == 0) rowl[0][j] = bl[m];  // row 0 of inv(L)
-    if (j == 0) coll[0][i] = a[m];   // l_i0
-    if (j == NB - 1) colu[0][i] = a[m];  // u_i,63
+    for (int q = 0; q < NB * NB / 256; ++q) S[(wave + 4 * q) * SLD + lane] = v[q];
   }
   __syncthreads();
-  if (i == NB - 1) {  // row 63 of inv(U)
-    const T di = dinv[NB - 1];
+  for (int p = 0; p < NB / PB; ++p) {
+    const int d0 = p * PB, d1 = d0 + PB;
+    if (wave == 0) {  // the panel
+      T a[PB];
 #pragma unroll
-    for (int m = 0; m < EPT; ++m) {
-      bu[m] = zmul(bu[m], di);
-      rowu[0][cg + CGS * m] = bu[m];
+      for (int c = 0; c < PB; ++c) a[c] = S[(d0 + c) * SLD + lane];
+      int bad = 0;
+#pragma unroll
+      for (int j = 0; j < PB; ++j) {
+        const R pr = lane_value(a[j].x, d0 + j), pi = lane_value(a[j].y, d0 + j);
+        const R d = pr * pr + pi * pi;
+        if (bad == 0 && (!(d > R(0)) || !isfinite(d))) bad = j + 1;
+        const T l = zmul(a[j], Cx<T>::mk(pr / d, -pi / d));
+        const bool below = lane > d0 + j;
+        a[j] = pick(below, l, a[j]);
+        const T lm = pick(below, l, zero);
+#pragma unroll
+        for (int c = j + 1; c < PB; ++c)
+          a[c] = sub_mul(a[c], lm, Cx<T>::mk(lane_value(a[c].x, d0 + j), lane_value(a[c].y, d0 + j)));
+      }
+      if (bad && lane == 0) atomicMin(info, goff + d0 + bad);
+      if (lane >= d0) {
+#pragma unroll
+        for (int c = 0; c < PB; ++c) S[(d0 + c) * SLD + lane] = a[c];
+      }
     }
-  }
-  // inverses: forward sweep for L (unit lower, step k) and backward sweep for
-  // U (row ku = 63 - k) together; bl, bu hold rows of the right-hand sides I
-  for (int k = 0; k < NB; ++k) {
-    const int b = k & 1, nb = b ^ 1, ku = NB - 1 - k;
     __syncthreads();
-    {
-      // branch-free: rows outside the update range use a zero multiplier
-      const T zero = Cx<T>::mk(R(0), R(0));
-      const T l = (i > k) ? coll[b][i] : zero;
-      const T u = (i < ku) ? colu[b][i] : zero;
-      T rl[EPT], ru[EPT];
+    if (wave == 0 && d1 + lane < NB) {  // rows of the panel right of it: a lane a column
+      T x[PB];
+      T* col = S + (d1 + lane) * SLD + d0;
 #pragma unroll
-      for (int m = 0; m < EPT; ++m) {
-        rl[m] = rowl[b][cg + CGS * m];
-        ru[m] = rowu[b][cg + CGS * m];
+      for (int r = 0; r < PB; ++r) x[r] = col[r];
+      int o = 0;
+#pragma unroll
+      for (int k = 0; k < PB - 1; ++k) {
+        // the reads' address waits for the step before: all of them at once would
+        // not fit the registers
+        if (k > 0) asm volatile("" : "+v"(o) : "v"(x[k].x));
+        const T* lk = S + (d0 + k) * SLD + d0 + o;
+#pragma unroll
+        for (int r = k + 1; r < PB; ++r) x[r] = sub_mul(x[r], x[k], lk[r]);
       }
 #pragma unroll
-      for (int m = 0; m < EPT; ++m) {
-        bl[m] = zsub(bl[m], zmul(l, rl[m]));
-        bu[m] = zsub(bu[m], zmul(u, ru[m]));
-      }
+      for (int r = 0; r < PB; ++r) col[r] = x[r];
     }
-    // next step's operands: row k+1 of inv(L) is final now; row ku-1 of
-    // inv(U) is final once divided by its pivot
-    if (k + 1 < NB) {
-      const T di = dinv[ku - 1];
+    __syncthreads();
+    const int left = NB / PB - 1 - p;  // trailing blocks a side
+    for (int t = wave; t < left * left; t += 4) {
+      const int I = p + 1 + t % left, J = p + 1 + t / left;
+      T* out = S + (J * PB + l16) * SLD + I * PB + 4 * lg;
+      T acc[4];
 #pragma unroll
-      for (int m = 0; m < EPT; ++m) {
-        const int j = cg + CGS * m;
-        if (i == k + 1) rowl[nb][j] = bl[m];
-        if (i == ku - 1) {
-          bu[m] = zmul(bu[m], di);
-          rowu[nb][j] = bu[m];
-        }
-        if (j == k + 1) coll[nb][i] = a[m];
-        if (j == ku - 1) colu[nb][i] = a[m];
+      for (int i = 0; i < 4; ++i) acc[i] = out[i];
+#pragma unroll
+      for (int k = 0; k < PB; ++k) {
+        const T u = S[(J * PB + l16) * SLD + d0 + k];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) acc[i] = sub_mul(acc[i], S[(d0 + k) * SLD + I * PB + 4 * lg + i], u);
       }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) out[i] = acc[i];
     }
+    __syncthreads();
   }
 #pragma unroll
-  for (int m = 0; m < EPT; ++m) {
-    const int j = cg + CGS * m;
-    if (i < kb) {
-      DinvL[i + (int64_t)j * ldi] = bl[m];
-      DinvU[i + (int64_t)j * ldi] = bu[m];
+  for (int q = 0; q < NB * NB / 256; ++q) {
+    const int j = wave + 4 * q;
+    if (lane < kb && j < kb) M[lane + (int64_t)j * ldm] = S[j * SLD + lane];
+  }
+  if (wave < 2) {  // diagonal blocks of inv(L) (wave 0) and inv(U): block lg, column l16
+    T x[PB];
+    const T* B = S + lg * PB * SLD + lg * PB;
+    int o = 0;
+#pragma unroll
+    for (int r = 0; r < PB; ++r) x[r] = pick(r == l16, one, zero);
+    if (wave == 0) {
+#pragma unroll
+      for (int k = 0; k < PB - 1; ++k) {
+        if (k > 0) asm volatile("" : "+v"(o) : "v"(x[k].x));
+        const T* col = B + k * SLD + o;
+#pragma unroll
+        for (int r = k + 1; r < PB; ++r) x[r] = sub_mul(x[r], x[k], col[r]);
+      }
+    } else {
+#pragma unroll
+      for (int k = PB - 1; k >= 0; --k) {
+        if (k < PB - 1) asm volatile("" : "+v"(o) : "v"(x[k].x));
+        const T* col = B + k * SLD + o;
+        const T u = col[k];
+        const R d = u.x * u.x + u.y * u.y;
+        x[k] = zmul(x[k], Cx<T>::mk(u.x / d, -u.y / d));
+#pragma unroll
+        for (int r = 0; r < k; ++r) x[r] = sub_mul(x[r], x[k], col[r]);
+      }
+    }
+    T* out = X + (lg * PB + l16) * SLD + lg * PB;
+#pragma unroll
+    for (int r = 0; r < PB; ++r)
+      if ((wave == 0) == (r > l16)) out[r] = x[r];
+  }
+  __syncthreads();
+  for (int d = 1; d < NB / PB; ++d) {
+    const int side = NB / PB - d;  // blocks of L at this distance from the diagonal, as many of U
+    for (int t = wave; t < 2 * side; t += 4) {
+      const bool low = t < side;
+      const int q = low ? t : t - side, I = low ? q + d : q, J = low ? q : q + d;
+      T acc[4] = {zero, zero, zero, zero};
+      // rows 4 lg + i, column l16
+      const int K0 = low ? J : I + 1, K1 = low ? I : J + 1;
+      for (int K = K0; K < K1; ++K) {
+#pragma unroll
+        for (int k = 0; k < PB; ++k) {
+          T x = X[(J * PB + l16) * SLD + K * PB + k];
+          if (K == J) x = low ? pick(k == l16, one, pick(k > l16, x, zero)) : pick(k <= l16, x, zero);
+#pragma unroll
+          for (int i = 0; i < 4; ++i) acc[i] = add_mul(acc[i], S[(K * PB + k) * SLD + I * PB + 4 * lg + i], x);
+        }
+      }
+      T* w = W[wave];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        w[l16 * (PB + 1) + 4 * lg + i] = acc[i];
+        acc[i] = zero;
+      }
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+#pragma unroll
+      for (int k = 0; k < PB; ++k) {
+        const T v = w[l16 * (PB + 1) + k];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int m = 4 * lg + i;
+          T x = X[(I * PB + k) * SLD + I * PB + m];
+          x = low ? pick(k == m, one, pick(k < m, x, zero)) : pick(k >= m, x, zero);
+          acc[i] = sub_mul(acc[i], x, v);
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) X[(J * PB + l16) * SLD + I * PB + 4 * lg + i] = acc[i];
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+    }
+    __syncthreads();
+  }
+#pragma unroll
+  for (int q = 0; q < NB * NB / 256; ++q) {
+    const int j = wave + 4 * q;
+    const T x = X[j * SLD + lane];
+    if (lane < kb) {
+      DinvL[lane + (int64_t)j * ldi] = pick(lane > j, x, pick(lane == j, one, zero));
+      DinvU[lane + (int64_t)j * ldi] = pick(lane <= j, x, zero);
     }
   }
 }
@@ -481,7 +546,7 @@ gevp_status lu_nopiv(gevp_ctx* c, int64_t n, zd* M, int64_t ldm, zd* DinvL, zd* 
       const int64_t sb = std::min<int64_t>(NB, pend - s0);
       const int64_t below = n - s0 - sb, pc = pend - s0 - sb;
       zd* Mss = M + s0 + s0 * ldm;
-      hipLaunchKernelGGL(k_getrf_block<zd>, dim3(1), dim3(1024), 0, c->stream, Mss, ldm, (int)sb,
+      hipLaunchKernelGGL(k_getrf_block<zd>, dim3(1), dim3(256), 0, c->stream, Mss, ldm, (int)sb,
                          DinvL + s0, DinvU + s0, ldi, info_dev, (int)s0, (int64_t)0, (int64_t)0);
       GEVP_HIP_TRY(hipGetLastError());
       zd* A21 = Mss + sb;
@@ -583,7 +648,7 @@ gevp_status lu_nopiv32(gevp_ctx* c, int nodes, int64_t n, Mats M, Mats DinvL, Ma
       const int64_t sb = std::min<int64_t>(NB, pend - s0);
       const int64_t below = n - s0 - sb, pc = pend - s0 - sb;
       const Mats A11 = M.at(s0, s0), dl = DinvL.at(s0, 0), du = DinvU.at(s0, 0);
-      hipLaunchKernelGGL(k_getrf_block<zf>, dim3((unsigned)nodes), dim3(1024), 0, c->stream, A11.p, M.ld, (int)sb,
+      hipLaunchKernelGGL(k_getrf_block<zf>, dim3((unsigned)nodes), dim3(256), 0, c->stream, A11.p, M.ld, (int)sb,
                          dl.p, du.p, dl.ld, info_dev, (int)s0, M.stride, dl.stride);
       GEVP_HIP_TRY(hipGetLastError());
       const Mats A21 = A11.at(sb, 0), A12 = A11.at(0, sb), A22 = A11.at(sb, sb);
