@@ -78,11 +78,11 @@ struct gevp_ctx {
   // concurrently there, so a solve keeps all its work on its own stream
   bool inner_streams = true;
   // no launch that must have all its work-groups resident at once: the second
-  // stream, unless the solve holds the turn for it, and a handle where one gave up
+  // stream, unless the solve holds a share for it, and a handle where one gave up
   bool shared_gpu = false;
-  bool batch_worker = false;  // takes turns with the others for such a launch
-  // where set, such launches raise this flag and go on (their turn is held by the
-  // caller, which looks at the flag when it next waits for the stream)
+  bool batch_worker = false;  // other workers' launches run beside this stream's
+  // where set, such launches raise this flag and go on (their share of the device is
+  // held by the caller, which looks at the flag when it next waits for the stream)
   int* defer_err = nullptr;
   // panel stream of the Cholesky factorisation and its two events (on demand)
   gevp_ctx* panel = nullptr;

@@ -12,7 +12,6 @@
 #define GEVP_EXCHANGE_H
 #include <algorithm>
 #include <atomic>
-#include <chrono>
 #include <thread>
 
 #include "common.h"
@@ -106,25 +105,43 @@ inline gevp_status fill_holes(gevp_ctx* c, unsigned long long* x, int64_t words,
 }
 }  // namespace
 
-// one such launch at a time per device and process: two of them, each with a part
-// of its work-groups resident, would wait for the other's compute units
-struct LaunchTurn {
-  std::atomic<bool>* busy = nullptr;
-  LaunchTurn(int device, double wait_s) {
-    static std::atomic<bool> taken[64];
-    if (device < 0 || device >= 64) return;
-    const auto start = std::chrono::steady_clock::now();
-    do {
-      if (!taken[device].exchange(true)) {
-        busy = &taken[device];
-        return;
-      }
-      std::this_thread::yield();
-    } while (std::chrono::duration<double>(std::chrono::steady_clock::now() - start).count() < wait_s);
+// The compute units of a device that such launches of this process may count on: a
+// launch takes as many as it has work-groups before it starts and gives them back
+// when it has ended, so that launches of several threads never each hold a part of
+// what the others wait for.  It waits as long as it takes: which kernel runs must
+// not depend on who else is running (the results would, in their last bits), and a
+// holder never waits for a second share.
+class LaunchTurn {
+ public:
+  LaunchTurn(gevp_ctx* c, int64_t groups) : used_(units(c->device)) {
+    int cus = 0;
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device) != hipSuccess) {
+      (void)hipGetLastError();
+      cus = 1;
+    }
+    share_ = (int)std::min<int64_t>(groups, cus);
+    if (take(cus)) return;
+    // the share is then held for no longer than the launch takes
+    (void)hipStreamSynchronize(c->stream);
+    while (!take(cus)) std::this_thread::yield();
   }
-  ~LaunchTurn() {
-    if (busy) busy->store(false);
+  ~LaunchTurn() { used_.fetch_sub(share_); }
+  LaunchTurn(const LaunchTurn&) = delete;
+  LaunchTurn& operator=(const LaunchTurn&) = delete;
+
+ private:
+  static std::atomic<int>& units(int device) {
+    static std::atomic<int> used[64];
+    return used[device >= 0 && device < 64 ? device : 0];
   }
+  bool take(int cus) {
+    int u = used_.load();
+    while (u + share_ <= cus)
+      if (used_.compare_exchange_weak(u, u + share_)) return true;
+    return false;
+  }
+  std::atomic<int>& used_;
+  int share_;
 };
 
 // whether this handle's stream may take such a launch now: not under capture (the

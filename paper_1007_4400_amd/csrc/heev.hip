@@ -1032,8 +1032,7 @@ size_t heev_work_bytes(int64_t n) {
   return b;
 }
 
-// One launch per reflector, under capture, where another handle has its turn and
-// where the single launch gave up: the kernel boundary is the grid-wide barrier (a cooperative single launch with
+// One launch per reflector, under capture and where the single launch gave up: the kernel boundary is the grid-wide barrier (a cooperative single launch with
 // explicit barriers measured slower, because each barrier must write back and
 // invalidate the XCD caches).  Issued one by
 // one, the launches cost the host about 4.4 us each at n = 948, more than the
@@ -1093,8 +1092,8 @@ gevp_status hetrd_launches(gevp_ctx* c, const TrdArgs& a, int G, size_t sh3) {
 }  // namespace
 
 namespace {
-// The tridiagonalisation in one launch; *done = false when it may not run, could
-// not be launched or gave up, H being unchanged.  A handle whose launch gave up
+// The tridiagonalisation in one launch; *done = false when it may not run or gave
+// up, H being unchanged.  A handle whose launch gave up
 // once (its stream may be confined to some of the compute units) does not try
 // again.
 gevp_status hetrd_all(gevp_ctx* c, const TrdArgs& a, TrdExchange x, bool* done) {
@@ -1118,12 +1117,11 @@ gevp_status hetrd_all(gevp_ctx* c, const TrdArgs& a, TrdExchange x, bool* done) 
     *done = true;
     return GEVP_OK;
   }
-  // a batch worker waits for its turn with its stream empty, so that the turn
-  // lasts no longer than the launch (eight problems of n = 1500 to 3000: 90 ms
-  // with a launch per reflector, 76 ms with turns)
+  // (a batch worker empties its stream first, so that its share of the device is
+  // held no longer than the launch: eight problems of n = 1500 to 3000 took 90 ms
+  // with a launch per reflector, 76 ms so)
   if (c->batch_worker) GEVP_HIP_TRY(hipStreamSynchronize(c->stream));
-  LaunchTurn turn(c->device, c->batch_worker ? 5e-3 : 0.0);
-  if (!turn.busy) return GEVP_OK;
+  LaunchTurn turn(c, groups);
   GEVP_TRY(fill_holes(c, x.x, words, x.err));
   hipLaunchKernelGGL(f, dim3((unsigned)groups), dim3((unsigned)threads), 0, c->stream, a, x);
   const hipError_t launched = hipGetLastError();
@@ -1179,8 +1177,8 @@ gevp_status heev_small(gevp_ctx* c, int64_t n64, zd* H, int64_t ldh, double* the
   // Many work-groups in one launch where they can be resident together; one
   // work-group where the exchange through memory costs more than it spreads (the
   // whole eigensolver at n = 32, 64, 116: 0.25, 0.47, 0.94 ms with one, 0.28,
-  // 0.45, 0.76 with many); a launch per reflector under capture and where another
-  // handle has its turn.  The exchange lies in the tridiagonal solver's workspace, not
+  // 0.45, 0.76 with many); a launch per reflector under capture and where a
+  // launch gave up.  The exchange lies in the tridiagonal solver's workspace, not
   // in use yet (40 n^2 bytes against 32 n (n + 15): enough from n = 60).
   bool done = false;
   if (n > TRD1_MAX && n <= TRDM_MAX && !c->shared_gpu) {

@@ -26,6 +26,7 @@
 // last iterate lands in the same buffer; columns are sorted by degree so the
 // columns still active at step j form a contiguous suffix.
 #include <cfloat>
+#include <memory>
 
 #include "exchange.h"
 
@@ -559,11 +560,12 @@ gevp_status lanczos_resident(gevp_ctx* c, int64_t n, const LanczosRun* runs, int
             : n <= 1536 ? k_lanczos_all<512, 3>
                         : k_lanczos_all<512, 4>;
   const int threads = n <= 256 ? 256 : 512;
-  const bool together = resident_fits(c, f, threads, (int64_t)a.groups * count);
+  // (on a second stream one after the other: a smaller share of the device is held)
+  const bool together = !c->defer_err && resident_fits(c, f, threads, (int64_t)a.groups * count);
   if (!together && !resident_fits(c, f, threads, a.groups)) return GEVP_OK;
   if (c->batch_worker) GEVP_HIP_TRY(hipStreamSynchronize(c->stream));
-  LaunchTurn turn(c->defer_err ? -1 : c->device, c->batch_worker ? 5e-3 : 0.0);
-  if (!turn.busy && !c->defer_err) return GEVP_OK;
+  std::unique_ptr<LaunchTurn> turn;
+  if (!c->defer_err) turn.reset(new LaunchTurn(c, a.groups * (together ? count : 1)));
   a.err = c->defer_err ? c->defer_err : (int*)((zd*)area[0] + 3 * n);
   for (int k = 0; k < 2; ++k)
     if (used[k])

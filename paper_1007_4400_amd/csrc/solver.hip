@@ -23,6 +23,7 @@
 #include <cmath>
 #include <cstdlib>
 #include <cstring>
+#include <memory>
 #include <mutex>
 #include <thread>
 #include <vector>
@@ -595,32 +596,33 @@ struct EventPair {
   }
 };
 
-// The turn for single-launch kernels on the second stream: they overlap the main
-// stream's work, so nothing waits for their outcome there; it is read with the
-// first sweep's results.  Given back then, or on any exit, after the second
-// stream's work (EventPair waits for it; declared after this).  The host had been
-// busy with some 400 small launches there while the main stream waited for it:
-// seeded solves n = 2048 14.6 -> 12.8 ms, contour n = 1100 12.0 -> 10.7 ms, n = 8192
-// 153 -> 149 ms.
+// The share of the device for single-launch kernels on the second stream: they
+// overlap the main stream's work, so nothing waits for their outcome there; it is
+// read with the first sweep's results.  Until then the main stream's own such
+// launches count on the same share (they wait for the second stream's work).  Given
+// back on any exit, after the second stream's work (EventPair waits for it; declared
+// after this).  The host had been busy with some 400 small launches there while the
+// main stream waited for it: seeded solves n = 2048 14.6 -> 12.8 ms, contour n = 1100
+// 12.0 -> 10.7 ms, n = 8192 153 -> 149 ms.
 struct SecondTurn {
-  gevp_ctx* second = nullptr;
-  LaunchTurn* turn = nullptr;
-  void take(gevp_ctx* c, gevp_ctx* ax, int* err) {
+  gevp_ctx *main = nullptr, *second = nullptr;
+  std::unique_ptr<LaunchTurn> turn;
+  // groups: of the largest of the launches, which follow one another
+  void take(gevp_ctx* c, gevp_ctx* ax, int* err, int64_t groups) {
     if (!resident_allowed(c)) return;
-    turn = new LaunchTurn(c->device, 0.0);
-    if (!turn->busy) return release();
+    turn.reset(new LaunchTurn(c, groups));
+    main = c;
     second = ax;
     ax->shared_gpu = false;
-    ax->defer_err = err;
+    ax->defer_err = c->defer_err = err;
   }
   void release() {
     if (second) {
       second->shared_gpu = true;
-      second->defer_err = nullptr;
+      second->defer_err = main->defer_err = nullptr;
       second = nullptr;
     }
-    delete turn;
-    turn = nullptr;
+    turn.reset();
   }
   ~SecondTurn() { release(); }
 };
@@ -795,7 +797,8 @@ gevp_status solve_once(gevp_handle h, const gevp_opts* opts, int64_t n, const vo
   gevp_ctx* ax = nullptr;
   if (spec) {
     GEVP_TRY(aux_ctx(c, &ax));
-    turn2.take(c, ax, flags + 4);
+    // eight rows or columns a work-group; the Lanczos runs up to order 2048
+    turn2.take(c, ax, flags + 4, ((n <= 2048 ? n : nb) + 7) / 8);
     ax->profiling = c->profiling & 4;
     ax->gev_used = 0;
     ax->gev_flops = 0.0;
@@ -1052,6 +1055,8 @@ gevp_status solve_once(gevp_handle h, const gevp_opts* opts, int64_t n, const vo
       GEVP_TRY(launch_zgemm(c, 0, 0, n, nb, n, 1.0, C, n, P1, n, 0.0, nullptr, 0, 0.0, nullptr, 0,
                             nullptr, T, n, nullptr, 0, 0, 0, nullptr, pC));
     } else {
+      // (the eigensolve below shares the second stream's part of the device)
+      if (spec && it == 0) GEVP_HIP_TRY(hipStreamWaitEvent(c->stream, evs.bounds, 0));
       GEVP_TRY(launch_zgemm(c, 0, 0, n, nb, n, 1.0, C, n, P0, n, 0.0, nullptr, 0, 0.0, nullptr, 0,
                             nullptr, W, n, nullptr, 0, 0, 0, nullptr, pC));
       GEVP_TRY(launch_zgemm(c, 1, 0, nb, nb, n, 1.0, P0, n, W, n, 0.0, nullptr, 0, 0.0, nullptr, 0,
