@@ -1,8 +1,9 @@
 // Cholesky factorisation and triangular solves, FP64 complex.
 //
-// The factorisation is right-looking in panels of 384 columns with one panel
-// of lookahead on a second stream (see chol_lower); each 64 x 64 diagonal
-// block is factored and inverted by one work-group in LDS.  The triangular solves
+// The factorisation is right-looking in outer panels of 384 to 1024 columns, each
+// in inner panels of 384, with one panel of lookahead on a second stream (see
+// chol_lower); each 64 x 64 diagonal block is factored and inverted by one
+// work-group.  The triangular solves
 // recurse: every level splits the triangle in two halves (rounded to the
 // 64-wide block), so the off-diagonal work is one large GEMM on the FP64
 // matrix cores per level, and the base case applies a diagonal block's
@@ -423,19 +424,27 @@ gevp_status copy_ct(gevp_ctx* c, int64_t m, int64_t k, const zd* in, int64_t ldi
 }
 }  // namespace
 
-// Right-looking blocked Cholesky in 384-wide panels with one panel of
-// lookahead.  A panel is factored on the panel stream, 64 columns at a time:
+// Right-looking blocked Cholesky in 384-wide panels, grouped into outer panels,
+// with one panel of lookahead.  A panel is factored on the panel stream, 64 columns at a time:
 // the diagonal block in LDS (k_potrf_block, which also writes its inverse to
 // Dinv), the rows below by an in-place product with that inverse,
 // L21 = A21 L11^{-H}, and the panel's remaining columns by a rank-64 update.
 // The panel's conjugate transpose is then copied into the upper block row
 // (space the factor does not use until it is zeroed at the end), so the
-// rank-384 trailing updates multiply both operands as stored.  The main
+// trailing updates multiply both operands as stored.  An inner panel updates the
+// rest of its outer panel; the matrix behind that is updated once per outer panel,
+// with its whole width as K: wide enough for the products in residue arithmetic,
+// whose conversions and reconstruction cost a pass over the trailing matrix each
+// time.  The main
 // stream applies the panel first to the next panel's columns, after which
 // the panel stream may factor that panel, then to the rest of the lower
 // triangle, which overlaps the factorisation.
 namespace {
 constexpr int64_t IPW = 6 * NB;
+// Measured with 384, 768 and 1024 columns (factorisation; one-sweep solve, where the
+// left solve is carried along): n = 3000 3.38, 3.45, 3.42 and 12.5, 12.1, 12.2 ms, n =
+// 5500 8.62, 8.13, 8.20 and 36.0, 33.6, 33.1 ms, n = 8192 17.9, 15.3, 15.0 and 82.6,
+// 71.2, 69.2 ms.
 inline int64_t outer_panel(int64_t n) { return n >= 6144 ? 1024 : n >= 3072 ? 768 : IPW; }
 }  // namespace
 gevp_status chol_lower(gevp_ctx* c, int64_t n, zd* M, int64_t ldm, zd* Dinv, int64_t ldi,

@@ -8,7 +8,8 @@
 //            solve W = L^{-1} A carried along panel by panel; L^H X0 for a
 //            seeded solve, then L^H copied into L's upper triangle
 //   reduce   C = W L^{-H} (the lower triangle of the right solve, mirrored)
-//   bounds   Lanczos on C (filter interval), on A and B (norm estimates)
+//   bounds   Lanczos on C (filter interval), on A and B (norm estimates), up to
+//            order 2048 in one launch
 //   seed     Y0 = [L^H X0, random], or random for a cold start; a full seed's
 //            first projection X0^H A X0 and its eigensolve run on a second
 //            stream during the factorisation and reduction

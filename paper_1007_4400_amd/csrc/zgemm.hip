@@ -39,6 +39,10 @@
 // at its own first row, and the entries below the diagonal of op(A) read as
 // zero, so only the upper triangle is ever used.  A split whose K range lies
 // entirely below a row block's diagonal contributes a zero partial tile.
+//
+// Large products go to the INT8 matrix cores in residue arithmetic (zgemm_mod.hip,
+// where the rule is); the kernels here follow them for operands that could not be
+// scaled.
 #include <atomic>
 
 #include <algorithm>
