@@ -383,6 +383,7 @@ __global__ __launch_bounds__(256) void k_bf16_splitk_reduce(BfParams p) {
   const int row = tm * BM + rl, col = tn * BN + cl;
   if (row >= p.M || col >= p.N) return;
   float ar = 0.f, ai = 0.f;
+#pragma unroll 8  // eight loads in flight
   for (int kc = 0; kc < p.splits; ++kc) {
     const zf v = p.part[((int64_t)kc * p.tiles + tile) * per + w];
     ar += v.x;
@@ -507,17 +508,20 @@ namespace {
 constexpr int PART_TILES_MAX = 1024;  // partial tiles the workspace holds
 
 // K splits for T tiles of nk slices on `cus` compute units: minimise
-// rounds(T s) * ceil(nk / s) plus the reduction's traffic (about 1/40 of a
-// slice per partial tile), keeping at least 8 slices per part
+// rounds(T s) * ceil(nk / s) plus the second kernel (4 slices' time and 1/40 of a
+// slice per partial tile), keeping at least 2 slices per part: few tiles are bound by
+// their chains of slices (filter step with the conversion, at least 8 slices before:
+// n = 500, 40 columns 55 -> 49 us, n = 1000, 100 columns 70 -> 63 us; from n = 2400 on
+// no difference).
 int choose_splits(int64_t T, int nk, int cus) {
   int best = 1;
   double best_cost = (double)((T + cus - 1) / cus) * nk;
-  for (int s = 2; s <= 8; ++s) {
+  for (int s = 2; s <= 16; ++s) {
     const int nks = (nk + s - 1) / s;
-    if (nks < 8) break;
+    if (nks < 2) break;
     const int se = (nk + nks - 1) / nks;
     if (T * se > PART_TILES_MAX) break;
-    const double cost = (double)((T * se + cus - 1) / cus) * nks + 0.025 * (double)(T * se) + 2.0;
+    const double cost = (double)((T * se + cus - 1) / cus) * nks + 0.025 * (double)(T * se) + 4.0;
     if (cost < 0.95 * best_cost) {
       best = s;
       best_cost = cost;
