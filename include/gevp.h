@@ -364,9 +364,9 @@ gevp_status gevp_backward_noalloc(gevp_handle h, int64_t n, int64_t nev, const v
  *   Cm may alias D; Cm / E may be NULL (term dropped).  gcol (device float64[n])
  *   scales the E term per column when non-NULL.  Asynchronous.
  * Large products run in residue arithmetic on the INT8 matrix cores (see
- * zgemm_mod.hip): after an exact power-of-two balancing along k, an entry's
- * error is at most about sqrt(k) 2^-57 ||op(A)(i, :)|| ||op(B)(:, j)|| and a few
- * roundings of the entry itself.  The handle keeps their scratch (up to 16 GiB,
+ * zgemm_mod.hip) where every entry is then at least as accurate, root mean square
+ * and relative to sum_k |op(A)(i, k)| |op(B)(k, j)|, as the FP64 matrix cores make
+ * it; a check on the device sends every other product to those.  The handle keeps their scratch (up to 16 GiB,
  * the largest product's); under stream capture, or where the memory is not to
  * be had, the FP64 matrix cores do every product.
  */

@@ -142,6 +142,7 @@ inline size_t ws_round(size_t b) { return (b + 255) & ~size_t(255); }
 struct ModPrepared {  // a left operand converted once for several products
   void* planes = nullptr;
   int* ex = nullptr;
+  const float* nr = nullptr;   // scaled norms of its rows
   const double* ks = nullptr;  // balancing scales for the right operands
   int* flag = nullptr;
   int64_t m = 0, k = 0;
@@ -178,13 +179,14 @@ struct ModGemmCall {
   const double *gcol, *coef;
   zd* D;
   const ModPrepared* prepared;
+  int parts;  // parts the FP64 kernels would cut k in
 };
 bool mod_gemm_pays(int opA, int opB, int64_t m, int64_t n, int64_t k, int lower, int upperA, bool prepared);
 size_t mod_gemm_bytes(int64_t m, int64_t n, int64_t k);
 size_t mod_prepared_bytes(int64_t m, int64_t k);
 gevp_status mod_prepare(gevp_ctx* c, int64_t m, int64_t k, int opA, const zd* A, int64_t lda, void* buf,
                         ModPrepared* out);
-// scratch >= mod_gemm_bytes; *flag1, *flag2 (the latter may be null): device
+// scratch >= mod_gemm_bytes; flag1[0..1], *flag2 (the latter may be null): device
 // flags, raised when the product was left to the FP64 kernels
 gevp_status launch_mod_gemm(gevp_ctx* c, const ModGemmCall& g, void* scratch, const int** flag1,
                             const int** flag2);

@@ -1208,8 +1208,9 @@ gevp_status heev_small(gevp_ctx* c, int64_t n64, zd* H, int64_t ldh, double* the
                        a.tau);
     GEVP_HIP_TRY(hipGetLastError());
     GEVP_TRY(diag_block_inverses(c, k, Lut, k, Dut, k));
+    // (V^H is upper triangular: reflector s begins at row s + 1)
     GEVP_TRY(launch_zgemm(c, 1, 0, k, n, n, 1.0, a.V, a.ldv, Z, ldz, 0.0, nullptr, 0, 0.0, nullptr, 0,
-                          nullptr, Sut, k));
+                          nullptr, Sut, k, nullptr, 0, 1));
     GEVP_TRY(trsm_left_lower_c(c, k, n, Lut, k, Dut, k, Sut, k, 0));
     GEVP_TRY(launch_zgemm(c, 0, 0, n, n, k, -1.0, a.V, a.ldv, Sut, k, 1.0, Z, ldz, 0.0, nullptr, 0,
                           nullptr, Z, ldz));

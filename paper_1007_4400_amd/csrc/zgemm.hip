@@ -41,8 +41,8 @@
 // entirely below a row block's diagonal contributes a zero partial tile.
 //
 // Large products go to the INT8 matrix cores in residue arithmetic (zgemm_mod.hip,
-// where the rule is); the kernels here follow them for operands that could not be
-// scaled.
+// where the rule is); the kernels here follow them for operands that one scale a
+// row and a column does not serve.
 #include <atomic>
 
 #include <algorithm>
@@ -89,7 +89,7 @@ struct ZgemmParams {
   const zd* A2;     // op(A) = 'N' only: rows >= M1 of op(A) are rows - M1 of A2 (same lda)
   int M1;
   // k_zgemm_after: the product was done in residue arithmetic unless one of
-  // these flags is up (flag2 may be null)
+  // these flags (two, one) is up (flag2 may be null)
   const int* flag1;
   const int* flag2;
 };
@@ -331,12 +331,13 @@ __global__ __launch_bounds__(NTHR, 2) void k_zgemm_cn(ZgemmParams p) { zgemm_til
 __global__ __launch_bounds__(NTHR, 2) void k_zgemm_cc(ZgemmParams p) { zgemm_tile<1, 1>(p); }
 
 // Behind a product in residue arithmetic (zgemm_mod.hip): the whole product
-// where an operand could not be scaled, nothing otherwise.  Kernels of their
+// where an operand could not be scaled or an entry failed the check, nothing
+// otherwise.  Kernels of their
 // own: the two flag loads ahead of every work-group's first slice cost the
 // plain ones 7 per cent at K = 256.
 template <int OPA, int OPB>
 __global__ __launch_bounds__(NTHR, 2) void k_zgemm_after(ZgemmParams p) {
-  if (*p.flag1 == 0 && (p.flag2 == nullptr || *p.flag2 == 0)) return;
+  if ((p.flag1[0] | p.flag1[1]) == 0 && (p.flag2 == nullptr || *p.flag2 == 0)) return;
   zgemm_tile<OPA, OPB>(p);
 }
 
@@ -588,6 +589,20 @@ gevp_status launch_zgemm(gevp_ctx* c, int opA, int opB, int64_t m, int64_t n, in
   if (A2 && (opA != 0 || lower || upperA || coef || m1 <= 0 || m1 >= m)) return GEVP_ERR_INVALID;
   if (m > INT32_MAX || n > INT32_MAX || k > INT32_MAX) return GEVP_ERR_INVALID;
   if (prepared && (prepared->m != m || prepared->k != k || upperA || A2)) return GEVP_ERR_INVALID;
+  // In residue arithmetic the last quarter of a triangle's rows is a product of its
+  // own: a row with few entries overlaps a column of full length too little for the
+  // check there, and the whole product would go to the FP64 kernels.
+  if (upperA && !lower && !c->no_mod) {
+    const int64_t r0 = (k - k / 4) / BM * BM;
+    if (r0 > 0 && r0 < m && mod_gemm_pays(opA, opB, r0, n, k, 0, 1, false) &&
+        mod_scratch(c, mod_gemm_bytes(r0, n, k))) {
+      auto rows = [&](const zd* M, int64_t ld, int op) { return M ? M + (op ? r0 * ld : r0) : nullptr; };
+      GEVP_TRY(launch_zgemm(c, opA, opB, r0, n, k, alpha, A, lda, B, ldb, beta, Cm, ldc, gamma, E, lde, gcol, D,
+                            ldd, coef, 0, 1));
+      return launch_zgemm(c, opA, opB, m - r0, n, k - r0, alpha, A + r0 + r0 * lda, lda, rows(B, ldb, opB), ldb,
+                          beta, rows(Cm, ldc, 0), ldc, gamma, rows(E, lde, 0), lde, gcol, D + r0, ldd, coef, 0, 1);
+    }
+  }
   ZgemmParams p;
   p.M = (int)m;
   p.N = (int)n;
@@ -654,7 +669,7 @@ gevp_status launch_zgemm(gevp_ctx* c, int opA, int opB, int64_t m, int64_t n, in
       mod_gemm_pays(opA, opB, m, n, k, lower, upperA, prepared != nullptr)) {
     if (void* sc = mod_scratch(c, mod_gemm_bytes(m, n, k))) {
       const ModGemmCall g{opA, opB, lower, upperA, m, n, k, m1, A, A2, B, Cm, E, lda, ldb, ldc, lde, ldd,
-                          alpha, beta, gamma, gcol, coef, D, prepared};
+                          alpha, beta, gamma, gcol, coef, D, prepared, zgemm_splits(total, nk, slots, SPLIT_TILES_MAX)};
       if (timed) GEVP_TRY(gev_begin(c));
       GEVP_TRY(launch_mod_gemm(c, g, sc, &p.flag1, &p.flag2));
       mod = true;

@@ -34,9 +34,23 @@
 // other operand's entries for the same k are large.  So op(A) op(B) is first
 // balanced as (op(A) T)(T^-1 op(B)), T diagonal with powers of two (exact)
 // that bring each row of op(B) below 1 (each column of op(A) when op(A) is
-// converted ahead, for several products): the error of an entry is then
-// relative to the sum of |op(A)| |op(B)| up to a factor of about sqrt(k) for
-// operands whose grading along k is systematic.
+// converted ahead, for several products); a slice that is zero in the operand
+// looked at is left out of the other one, where it contributes nothing.
+//
+// Balancing serves gradings along k that all rows share, no others.  So every
+// entry of the product is checked.  Each rounding of step 1 being uniform, an entry
+// is off by sqrt((|a|^2 + |b|^2) / 6), root mean square, in the integers' unit, a and
+// b its row and column; the FP64 kernels' error was measured at 2^-53.9 / sqrt(parts)
+// of the entry's sum of sizes S = sum_k |op(A)(i, k)| |op(B)(k, j)| for random
+// operands of any k, parts being the parts they cut k in (more where the terms have
+// one sign: 2^-51.1 to 2^-52.9 S, here 2^-54.4 S).  Where the former is not
+// the smaller, the flag is raised and the FP64 kernels do the product.  S is bounded
+// from below by an INT8 product of sizes: each entry's over its row's root mean
+// square, rounded down and cut at 127.  A coarse one with k eight times shorter
+// comes first and mostly suffices; a tile of the result where it does not takes the
+// one of all sizes, as long as a residue product.
+// In time: 8192 x 948 x 8192 2.74 ms without the check, 2.81 with it, 3001 x 768 x
+// 768 0.181 and 0.185.
 //
 // Planes: residues of 16 rows and 64 consecutive k are stored as one
 // 1 KB MFMA fragment (lane l: row l % 16, sixteen k), so that global loads,
@@ -44,6 +58,8 @@
 // fragment is free as long as both operands agree: lane group g holds
 // k = 4 q + g, q = 0..15, which keeps the conversion's loads of both storage
 // orders in runs of at least 64 bytes.
+#include <cmath>
+
 #include "common.h"
 
 typedef int i4 __attribute__((ext_vector_type(4)));
@@ -55,9 +71,15 @@ struct ic {
 
 namespace {
 constexpr int NMOD = 16, NCH = 2 * NMOD;  // moduli, residue channels
+constexpr int NPL = NCH + 1;              // planes of an operand: the residues, then the sizes
+constexpr int COARSE = 8;                 // sizes summed up in one of the coarse plane behind them
 constexpr int FR = 16, FK = 64;           // rows and k of a fragment
 constexpr int TM = 256;                   // largest output tile of a work-group (rows and columns)
 constexpr int SCALE_EXP = 58;             // row and column norms are scaled below 2^58
+constexpr float SIZE_UNIT = 48.f;         // size of a root-mean-square entry of a row of norm 2^58
+// least sum of sizes of an entry over sqrt(|a|^2 + |b|^2), in units of K and of the
+// norms' bound, against FP64 kernels in one part: 2^53.9 / 2^58 / sqrt(6)
+constexpr float MIN_SIZES = SIZE_UNIT * SIZE_UNIT * 0.0238f;
 
 typedef unsigned __int128 u128;
 
@@ -150,6 +172,7 @@ __device__ __forceinline__ zd mod_elem(const ModSrc& s, int r, int k) {
 // The balancing scales, ks0[k] = 2^-x for the operand looked at here, ks1[k] =
 // 2^x for the other one: the largest entry of its slice k is brought into
 // [1/2, 1).  Every entry counts (a sample of a slice may see only small ones).
+// Of a zero slice the other operand's entries count for nothing, however large.
 // With several chunks of rows the maxima go to part[chunk][k] first.
 constexpr int BAL_ROWS = 1024;  // rows of a chunk, k contiguous
 __device__ __forceinline__ void balance_store(int k, double m, double* ks0, double* ks1) {
@@ -157,7 +180,7 @@ __device__ __forceinline__ void balance_store(int k, double m, double* ks0, doub
   if (m > 0.0 && m < 1e300) (void)frexp(m, &x);
   x = max(-250, min(250, x));
   ks0[k] = ldexp(1.0, -x);
-  ks1[k] = ldexp(1.0, x);
+  ks1[k] = m == 0.0 ? 0.0 : ldexp(1.0, x);  // (a NaN or an infinity still raises the flag)
 }
 __global__ __launch_bounds__(1024) void k_mod_balance(ModSrc s, double* ks0, double* ks1, double* part,
                                                       int chunks) {
@@ -202,7 +225,8 @@ __global__ __launch_bounds__(256) void k_mod_balance_finish(const double* part, 
 }
 
 // Row sums of squares in at most MAXC chunks of k (part[chunk][row]; -1 for a
-// chunk without a nonzero entry), each operand in the order its storage favours.
+// chunk without a nonzero entry that counts), each operand in the order its
+// storage favours.
 constexpr int MAXC = 16;
 __device__ __forceinline__ void norm_kfast(const ModSrc& s, const double* ks, int blk, int nch, int clen,
                                            double* part) {
@@ -216,17 +240,17 @@ __device__ __forceinline__ void norm_kfast(const ModSrc& s, const double* ks, in
 #pragma unroll 8
   for (int k = c * clen + lane; k < k1; k += 64) {
     zd v = mod_elem(s, (int)r, k);
+    nz = ((v.x != 0.0 || v.y != 0.0) && ks[k] != 0.0) ? 1.0 : nz;
     v.x *= ks[k];
     v.y *= ks[k];
     ss += v.x * v.x + v.y * v.y;
-    nz = (v.x != 0.0 || v.y != 0.0) ? 1.0 : nz;
   }
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) {
     ss += __shfl_xor(ss, o, 64);
     nz = fmax(nz, __shfl_xor(nz, o, 64));
   }
-  if (lane == 0) part[(int64_t)c * s.rows + r] = (nz == 0.0) ? -1.0 : ss;
+  if (lane == 0) part[(int64_t)c * s.rows + r] = (nz == 0.0 && ss == 0.0) ? -1.0 : ss;
 }
 __device__ __forceinline__ void norm_rfast(const ModSrc& s, const double* ks, int blk, int nch, int clen,
                                            double* part) {
@@ -240,13 +264,13 @@ __device__ __forceinline__ void norm_rfast(const ModSrc& s, const double* ks, in
 #pragma unroll 8
     for (int k = c * clen + w; k < k1; k += 4) {
       zd v = mod_elem(s, r, k);
+      nz = ((v.x != 0.0 || v.y != 0.0) && ks[k] != 0.0) ? 1.0 : nz;
       v.x *= ks[k];
       v.y *= ks[k];
       ss += v.x * v.x + v.y * v.y;
-      nz = (v.x != 0.0 || v.y != 0.0) ? 1.0 : nz;
     }
   }
-  sh[w][threadIdx.x & 63] = (nz == 0.0) ? -1.0 : ss;
+  sh[w][threadIdx.x & 63] = (nz == 0.0 && ss == 0.0) ? -1.0 : ss;
   __syncthreads();
   if (w == 0 && r < s.rows) {
     double t = -1.0;
@@ -265,6 +289,7 @@ struct ConvArgs {
   const double* ks[2];     // balancing scale of each k
   double* part[2];
   int* ex[2];              // scale exponents, written by the conversion
+  float* nr[2];            // scaled norms over 2^58: in [1/2, 1), 0 for a row of zeros
   unsigned char* planes[2];
   int rg[2], kb[2];        // fragments along rows and k
   int* flag;
@@ -272,7 +297,7 @@ struct ConvArgs {
 __global__ __launch_bounds__(256) void k_mod_norms(ConvArgs p) {
   const int w = (int)blockIdx.x >= p.blk[0];
   const int b = blockIdx.x - (w ? p.blk[0] : 0);
-  if (blockIdx.x == 0 && threadIdx.x == 0) *p.flag = 0;  // raised by the conversion only
+  if (blockIdx.x == 0 && threadIdx.x < 2) p.flag[threadIdx.x] = 0;  // raised by the conversion and the check
   if (p.s[w].kfast)
     norm_kfast(p.s[w], p.ks[w], b, p.nch[w], p.clen[w], p.part[w]);
   else
@@ -300,14 +325,15 @@ __device__ __forceinline__ unsigned pack4(unsigned a, unsigned b, unsigned c, un
 // sixteen digit products (v_dot4_i32_i8, below 2^18), reduced with one FP32
 // multiply-round-subtract, which is exact at that size.  Bound by the bytes
 // written (32 per complex entry) as much as by the about 550 vector
-// instructions per entry.
+// instructions per entry.  The sizes (|entry| over its row's root mean square) go
+// out as one plane more.
 __device__ __forceinline__ void digits(double x, unsigned& lo, unsigned& hi) {
   const long long t = __double2ll_rn(x);
   const unsigned long long u = (unsigned long long)t + 0x0080808080808080ull;
   lo = (unsigned)u ^ 0x80808080u;
   hi = (unsigned)(u >> 32) ^ 0x00808080u;
 }
-__global__ __launch_bounds__(256) void k_mod_split(ConvArgs p) {
+__global__ __launch_bounds__(256, 4) void k_mod_split(ConvArgs p) {
   const int lane = threadIdx.x & 63;
   const int w = (int)blockIdx.x >= p.blk[0];
   const int64_t f = (int64_t)(blockIdx.x - (w ? p.blk[0] : 0)) * 4 + (threadIdx.x >> 6);
@@ -340,19 +366,27 @@ __global__ __launch_bounds__(256) void k_mod_split(ConvArgs p) {
   any |= __shfl_xor(any, 16, 64);
   any |= __shfl_xor(any, 32, 64);
   int e = 0;
+  float nr = 0.f;
   if (any) {
     if (ss > 1e-250 && ss < 1e250) {
       int x = 0;
-      (void)frexp(sqrt(ss), &x);
+      nr = (float)frexp(sqrt(ss), &x);
       e = SCALE_EXP - x;
     } else {
       *p.flag = 1;
     }
   }
-  if (kb == 0 && lane < 16 && r < s.rows) p.ex[w][r] = e;
+  if (kb == 0 && lane < 16 && r < s.rows) {
+    p.ex[w][r] = e;
+    p.nr[w][r] = nr;
+  }
   const double sc = ldexp(1.0, e);
+  const int64_t chs = (int64_t)rg * nkb * 1024;  // bytes per channel
+  unsigned char* out = p.planes[w] + ((int64_t)g * nkb + kb) * 1024 + lane * 16;
   unsigned alo[16], ahi[16], blo[16], bhi[16];
   {
+    const float unit = SIZE_UNIT * __builtin_amdgcn_sqrtf((float)s.K) * 0x1p-58f;
+    unsigned size[4] = {0, 0, 0, 0}, sum[2] = {0, 0}, least[2] = {127, 127};
     zd v[16];
 #pragma unroll
     for (int q = 0; q < 16; ++q) v[q] = mod_elem(s, r, k0 + 4 * q);
@@ -362,10 +396,24 @@ __global__ __launch_bounds__(256) void k_mod_split(ConvArgs p) {
       const double f = sc * (k0 + 4 * q < s.K ? p.ks[w][k0 + 4 * q] : 0.0);
       digits(v[q].x * f, alo[q], ahi[q]);
       digits((s.conj ? -v[q].y : v[q].y) * f, blo[q], bhi[q]);
+      const float x = (float)(v[q].x * f), y = (float)(v[q].y * f);
+      const unsigned z = (unsigned)fminf(unit * __builtin_amdgcn_sqrtf(x * x + y * y), 127.f);
+      size[q >> 2] |= z << (8 * (q & 3));
+      sum[q >> 3] += z;
+      least[q >> 3] = min(least[q >> 3], z);
+      if ((q & 3) == 3) __builtin_amdgcn_sched_barrier(0);
     }
+    // the coarse plane: eight of a lane's sizes in one, their mean on the left, their
+    // least on the right (the sum of the eight products is at least eight times the
+    // product of these)
+    const unsigned c8 = w == 0 ? sum[0] / 8 | sum[1] / 8 << 8 : least[0] | least[1] << 8;
+    const int nkc = (nkb + COARSE - 1) / COARSE;
+    unsigned char* oc = p.planes[w] + NPL * chs + ((int64_t)g * nkc + kb / COARSE) * 1024 + lane * 16;
+    *reinterpret_cast<unsigned short*>(oc + 2 * (kb % COARSE)) = (unsigned short)c8;
+    if (kb == nkb - 1)  // zeros to the fragment's end
+      for (int z = kb % COARSE + 1; z < COARSE; ++z) *reinterpret_cast<unsigned short*>(oc + 2 * z) = 0;
+    *reinterpret_cast<uint4*>(out + (int64_t)NCH * chs) = make_uint4(size[0], size[1], size[2], size[3]);
   }
-  const int64_t chs = (int64_t)rg * nkb * 1024;  // bytes per channel
-  unsigned char* out = p.planes[w] + ((int64_t)g * nkb + kb) * 1024 + lane * 16;
   for (int m = 0; m < NMOD; ++m) {
     const unsigned dlo = c_tab.dlo[m], dhi = c_tab.dhi[m], jlo = c_tab.jlo[m], jhi = c_tab.jhi[m];
     const int mod = c_tab.p[m];
@@ -393,7 +441,8 @@ __global__ __launch_bounds__(256) void k_mod_split(ConvArgs p) {
 }
 
 // The residue products: channel c of the result is the INT32 product of the
-// operands' channel-c planes, reduced mod p to one byte.
+// operands' channel-c planes, reduced mod p to one byte.  Beside them the check's
+// sums of sizes, which are compared and not kept.
 //
 // Eight waves (2 x 4) own a 32 MI x 64 NJ tile, each MI x NJ MFMA blocks.  The
 // largest, 256 x 256 with 128 accumulators per wave and two waves per SIMD,
@@ -411,41 +460,37 @@ struct ModGemmArgs {
   int tiles_m, tiles_n, tiles;
   int lower, tri;
   int rb, cb;            // 16 x 16 blocks of the result
-  int total;
+  int total, checks;     // work-groups of the residue products, and of the check (a multiple of 8)
   int small;             // 1: the INT32 sums stay below 2^24
+  // the check: norms of A's rows and B's columns, the least sum of sizes of an entry
+  // over the root of the sum of their squares
+  const float *nra, *nrb;
+  int M, N;
+  float least;
+  // flag[0]: an operand could not be scaled, flag[1]: raised by the check here; of
+  // an operand converted ahead the first alone
+  int* flag;
+  const int* flag2;
 };
 
+// The INT32 product of a tile: ga, gb the first fragments of A and B this wave
+// transfers, fs bytes from one fragment row to the next, stages kb0 .. kb - 1.
+// off: the transfers issued ahead are waited for and nothing is computed.
 template <int MI, int NJ>
-__global__ __launch_bounds__(512, 2) void k_mod_gemm(ModGemmArgs p) {
-  constexpr int TM = 32 * MI, TN = 64 * NJ;
-  constexpr int A_ST = (TM / FR) * 1024, ST = A_ST + (TN / FR) * 1024;
-  constexpr int TA = MI / 4, TB = NJ / 2;  // fragments of A and B this wave transfers per stage
-  __shared__ __attribute__((aligned(16))) unsigned char s0[ST], s1[ST], s2[ST], s3[ST];
+struct ModTile {
+  static constexpr int TM = 32 * MI, TN = 64 * NJ;
+  static constexpr int A_ST = (TM / FR) * 1024, ST = A_ST + (TN / FR) * 1024;
+  static constexpr int TA = MI / 4, TB = NJ / 2;  // fragments of A and B a wave transfers per stage
+};
+template <int MI, int NJ>
+__device__ __forceinline__ void mod_product(const unsigned char* ga, const unsigned char* gb, int64_t fs, int kb0,
+                                            int kb, int off, unsigned char* s0, unsigned char* s1,
+                                            unsigned char* s2, unsigned char* s3, i4 (&acc)[MI][NJ]) {
+  typedef ModTile<MI, NJ> G;
+  constexpr int A_ST = G::A_ST, TA = G::TA, TB = G::TB;
   const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // uniform: addresses in scalar registers
-  // XCD-aware order: eight consecutive work-groups go to the eight XCDs; give
-  // each XCD a contiguous range
-  int L = blockIdx.x;
-  const int per = (p.total + 7) >> 3;
-  L = (L & 7) * per + (L >> 3);
-  if (L >= p.total) return;
-  const int ch = L / p.tiles;
-  int t = L - ch * p.tiles;
-  // groups of eight row tiles, walked column by column: the tiles in flight
-  // on an XCD share few row and column panels
-  const int gsz = 8 * p.tiles_n, gi = t / gsz, gr = min(8, p.tiles_m - gi * 8);
-  t -= gi * gsz;
-  const int tn = t / gr, tm = gi * 8 + (t - tn * gr);
-  const int row0 = tm * TM, col0 = tn * TN;
-  if (p.lower && col0 > row0 + TM - 1) return;  // entirely above the diagonal
-  const int kb0 = p.tri ? min(row0 / FK, p.kb - 1) : 0;  // (rows beyond K: one stage of zeros)
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wr = wave >> 2, wc = wave & 3;
-  const int mod = c_tab.p[ch >> 1];
-
-  // this wave's transfers
-  const int64_t fs = (int64_t)p.kb * 1024;  // from one fragment row to the next
-  const unsigned char* ga = p.A + ((int64_t)ch * p.rga + row0 / FR + wave * TA) * fs;
-  const unsigned char* gb = p.B + ((int64_t)ch * p.rgb + col0 / FR + wave * TB) * fs;
   auto issue = [&](int kk, unsigned char* st) {
 #pragma unroll
     for (int i = 0; i < TA; ++i)
@@ -458,7 +503,6 @@ __global__ __launch_bounds__(512, 2) void k_mod_gemm(ModGemmArgs p) {
                                        (__attribute__((address_space(3))) void*)(st + A_ST + (wave * TB + i) * 1024),
                                        16, 0, 0);
   };
-  i4 acc[MI][NJ];
 #pragma unroll
   for (int i = 0; i < MI; ++i)
 #pragma unroll
@@ -472,11 +516,15 @@ __global__ __launch_bounds__(512, 2) void k_mod_gemm(ModGemmArgs p) {
   i4 b0[NJ], b1[NJ], a0[2], a1[2];  // B fragments of this and the next stage; two A fragments ahead
   // stages beyond the last are filled with the last one again, so that every
   // pass through the loop issues and waits alike and runs without branches
-  const int n = p.kb - kb0, last = p.kb - 1;
+  const int n = kb - kb0, last = kb - 1;
   constexpr int T = TA + TB;  // transfers a stage
   issue(kb0, s0);
   issue(min(kb0 + 1, last), s1);
   issue(min(kb0 + 2, last), s2);
+  if (off != 0) {
+    __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0), as at the end
+    return;
+  }
   __builtin_amdgcn_s_waitcnt(0x0f70 | (2 * T));  // vmcnt(2 T): stage 0 has landed
   __builtin_amdgcn_s_barrier();
 #pragma unroll
@@ -530,8 +578,97 @@ __global__ __launch_bounds__(512, 2) void k_mod_gemm(ModGemmArgs p) {
   if (u + 2 < n) body(b0, b1, s2, s3, s1, u + 2);
   // nothing may be in flight to the LDS when the work-group ends
   __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
+}
+
+template <int MI, int NJ>
+__global__ __launch_bounds__(512, 2) void k_mod_gemm(ModGemmArgs p) {
+  typedef ModTile<MI, NJ> G;
+  constexpr int TM = G::TM, TN = G::TN;
+  __shared__ __attribute__((aligned(16))) unsigned char s0[G::ST], s1[G::ST], s2[G::ST], s3[G::ST];
+  __shared__ int below;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // uniform: addresses in scalar registers
+  // The check's tiles come first: they are the short ones (and spread over the XCDs
+  // as they are).  Then XCD-aware order: eight consecutive work-groups go to the
+  // eight XCDs; give each XCD a contiguous range
+  const bool check = (int)blockIdx.x < p.checks;
+  int t = blockIdx.x, ch = 0;
+  if (!check) {
+    const int per = (p.total + 7) >> 3, q = blockIdx.x - p.checks;
+    const int L = (q & 7) * per + (q >> 3);
+    if (L >= p.total) return;
+    ch = L / p.tiles;
+    t = L - ch * p.tiles;
+  } else if (t >= p.tiles) {
+    return;
+  }
+  // groups of eight row tiles, walked column by column: the tiles in flight
+  // on an XCD share few row and column panels
+  const int gsz = 8 * p.tiles_n, gi = t / gsz, gr = min(8, p.tiles_m - gi * 8);
+  t -= gi * gsz;
+  const int tn = t / gr, tm = gi * 8 + (t - tn * gr);
+  const int row0 = tm * TM, col0 = tn * TN;
+  if (p.lower && col0 > row0 + TM - 1) return;  // entirely above the diagonal
+  const int kb0 = p.tri ? min(row0 / FK, p.kb - 1) : 0;  // (rows beyond K: one stage of zeros)
+  const int wr = wave >> 2, wc = wave & 3;
+  const int off = p.flag[0] | (p.flag2 ? *p.flag2 : 0);  // left to the FP64 kernels
+  const int64_t fs = (int64_t)p.kb * 1024;
+  const int64_t fra = row0 / FR + wave * G::TA, frb = col0 / FR + wave * G::TB;  // this wave's transfers
+  i4 acc[MI][NJ];
+
+  if (check) {
+    // the sums of sizes, compared with the norms: those of the coarse planes where
+    // they suffice for the tile, else those of the full ones
+#pragma unroll 1
+    for (int pass = 0; pass < 2; ++pass) {
+      const int kb = pass == 0 ? (p.kb + COARSE - 1) / COARSE : p.kb, planes = pass == 0 ? NPL : NCH;
+      const int64_t fp = (int64_t)kb * 1024;
+      mod_product<MI, NJ>(p.A + planes * p.rga * fs + fra * fp, p.B + planes * p.rgb * fs + frb * fp, fp,
+                          pass == 0 ? kb0 / COARSE : kb0, kb, off, s0, s1, s2, s3, acc);
+      if (off != 0) return;
+      const float least = pass == 0 ? p.least * (1.f / COARSE) : p.least;
+      // the comparison's addresses and norms belong here, not in registers across the product
+      int wr = wave >> 2, wc = wave & 3;
+      asm volatile("" : "+s"(wr), "+s"(wc));
+      bool low = false;
+#pragma unroll
+      for (int i = 0; i < MI; ++i) {
+        const int rb = row0 / FR + wr * MI + i;
+        if (rb >= p.rb) continue;
+        float na[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int row = rb * 16 + 4 * (lane >> 4) + r;
+          na[r] = row < p.M ? p.nra[row] : 0.f;
+        }
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+          const int cb = col0 / FR + wc * NJ + j, col = cb * 16 + (lane & 15);
+          if (cb >= p.cb || (p.lower && (cb >> 2) > (rb >> 2))) continue;
+          const float nb = col < p.N ? p.nrb[col] : 0.f;
+#pragma unroll
+          for (int r = 0; r < 4; ++r)  // (a row or column of zeros needs no check)
+            low |= na[r] * nb > 0.f &&
+                   (float)acc[i][j][r] < least * __builtin_amdgcn_sqrtf(na[r] * na[r] + nb * nb);
+        }
+      }
+      if (threadIdx.x == 0) below = 0;
+      __syncthreads();
+      if (low) below = 1;
+      __syncthreads();
+      const int again = below;
+      __syncthreads();
+      if (again == 0) return;
+    }
+    if (threadIdx.x == 0) p.flag[1] = 1;
+    return;
+  }
+  mod_product<MI, NJ>(p.A + ((int64_t)ch * p.rga + fra) * fs, p.B + ((int64_t)ch * p.rgb + frb) * fs, fs, kb0, p.kb,
+                      off, s0, s1, s2, s3, acc);
+  if (off != 0) return;
 
   // residues of the INT32 sums, folded at 2^16 first where they may pass 2^24
+  const int mod = c_tab.p[ch >> 1];
   const float ip = 1.0f / (float)mod;
   const int c16 = 65536 % mod > mod / 2 ? 65536 % mod - mod : 65536 % mod;
 #pragma unroll
@@ -573,7 +710,7 @@ struct CrtArgs {
   const double* coef;
 };
 __global__ __launch_bounds__(256) void k_mod_crt(CrtArgs p) {
-  if (*p.flag != 0 || (p.flag2 && *p.flag2 != 0)) return;  // the FP64 kernels take over
+  if ((p.flag[0] | p.flag[1]) != 0 || (p.flag2 && *p.flag2 != 0)) return;  // the FP64 kernels take over
   const int lane = threadIdx.x & 63;
   const int64_t blk = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
   if (blk >= (int64_t)p.rb * p.cb) return;
@@ -638,10 +775,12 @@ __global__ __launch_bounds__(256) void k_mod_crt(CrtArgs p) {
 inline int64_t up(int64_t a, int64_t b) { return (a + b - 1) / b * b; }
 // planes of a rows x k operand: rows padded to the largest tile (the padding is
 // never written: it only has to be readable), k to a fragment (zeros)
-inline int64_t plane_bytes(int64_t rows, int64_t k) { return up(rows, TM) * up(k, FK) * NCH; }
+inline int64_t plane_bytes(int64_t rows, int64_t k) {
+  return up(rows, TM) * (up(k, FK) * NPL + up(k, FK * COARSE) / COARSE);
+}
 inline int chunks(int64_t k) { return (int)std::max<int64_t>(1, std::min<int64_t>(MAXC, k / 128)); }
 inline size_t conv_bytes(int64_t rows, int64_t k) {
-  return ws_round(plane_bytes(rows, k)) + ws_round(sizeof(int) * rows) +
+  return ws_round(plane_bytes(rows, k)) + ws_round(sizeof(int) * rows) + ws_round(sizeof(float) * rows) +
          ws_round(sizeof(double) * rows * chunks(k));
 }
 
@@ -662,6 +801,7 @@ void set_operand(ConvArgs& c, int w, const ModSrc& s, Carver& m) {
   c.kb[w] = (int)(up(s.K, FK) / FK);
   c.planes[w] = (unsigned char*)m.take(plane_bytes(s.rows, s.K));
   c.ex[w] = (int*)m.take(sizeof(int) * s.rows);
+  c.nr[w] = (float*)m.take(sizeof(float) * s.rows);
   c.part[w] = (double*)m.take(sizeof(double) * s.rows * c.nch[w]);
 }
 
@@ -727,7 +867,9 @@ gevp_status launch_tiles(gevp_ctx* c, ModGemmArgs q, int64_t m, int64_t n) {
   q.tiles_n = (int)((n + 64 * NJ - 1) / (64 * NJ));
   q.tiles = q.tiles_m * q.tiles_n;
   q.total = q.tiles * NCH;
-  hipLaunchKernelGGL((k_mod_gemm<MI, NJ>), dim3((unsigned)((q.total + 7) / 8 * 8)), dim3(512), 0, c->stream, q);
+  q.checks = (q.tiles + 7) / 8 * 8;
+  hipLaunchKernelGGL((k_mod_gemm<MI, NJ>), dim3((unsigned)(q.checks + (q.total + 7) / 8 * 8)), dim3(512), 0,
+                     c->stream, q);
   GEVP_HIP_TRY(hipGetLastError());
   return GEVP_OK;
 }
@@ -741,13 +883,13 @@ size_t mod_gemm_bytes(int64_t m, int64_t n, int64_t k) {
 }
 
 // The route by estimated times.  Residues: 45 us for six launches and their
-// gaps, the conversions (64 bytes per entry: read twice, 32 written; 16 more
+// gaps, the conversions (64 bytes per entry: read twice, 33 written; 16 more
 // for the balancing), the result (residues written and read, the result read
 // and written), the INT8 products of whole 128-wide tiles; FP64: the rate of
 // the operand form at sizes where the two meet.  Measured residues / FP64, in
-// ms: NN 8192 x 8192 x 384 2.40 / 2.67, 4096 x 4096 x 384 0.71 / 0.68, 2048 x
-// 2048 x 512 0.24 / 0.23, 4096 x 474 x 1024 0.213 / 0.220, 948^3 0.116 / 0.116
-// (CN 0.121 / 0.146), 2048 x 237 x 2048 0.132 / 0.129, 512^3 0.069 / 0.036; 8192
+// ms: NN 8192 x 8192 x 384 2.39 / 2.68, 4096 x 4096 x 384 0.71 / 0.68, 2048 x
+// 2048 x 512 0.234 / 0.225, 4096 x 474 x 1024 0.211 / 0.221, 948^3 0.116 / 0.116
+// (CN 0.127 / 0.147), 2048 x 237 x 2048 0.132 / 0.129, 512^3 0.069 / 0.036; 8192
 // x 128 x 8192 1.42 / 0.86 (the conversion of a large matrix for few columns);
 // 8192 x 948 x 8192 2.8 / 6.7, 4096^3 2.4 / 6.7.
 bool mod_gemm_pays(int opA, int opB, int64_t m, int64_t n, int64_t k, int lower, int upperA, bool prepared) {
@@ -777,6 +919,7 @@ gevp_status mod_prepare(gevp_ctx* c, int64_t m, int64_t k, int opA, const zd* A,
   out->ks = p.ks[1];
   out->planes = p.planes[0];
   out->ex = p.ex[0];
+  out->nr = p.nr[0];
   out->flag = p.flag;
   out->m = m;
   out->k = k;
@@ -809,6 +952,13 @@ gevp_status launch_mod_gemm(gevp_ctx* c, const ModGemmCall& g, void* scratch, co
   q.rb = q.rga;
   q.cb = q.rgb;
   q.small = g.k <= 1024;  // 1024 * 120^2 < 2^24
+  q.nra = pa ? pa->nr : p.nr[0];
+  q.nrb = p.nr[1];
+  q.M = (int)g.m;
+  q.N = (int)g.n;
+  q.least = MIN_SIZES * (float)g.k * std::sqrt((float)g.parts);
+  q.flag = p.flag;
+  q.flag2 = pa ? pa->flag : nullptr;
   switch (mod_tile(g.m, g.n, gevp_device_cus(c->device))) {
     case 0: GEVP_TRY((launch_tiles<8, 4>(c, q, g.m, g.n))); break;
     case 1: GEVP_TRY((launch_tiles<8, 2>(c, q, g.m, g.n))); break;
