@@ -30,7 +30,10 @@
  *  - Work runs on the stream set with gevp_set_stream (default: the null
  *    stream).  gevp_solve returns after its work has completed, because its
  *    status depends on convergence; gevp_backward and the gevp_k_* kernels
- *    are asynchronous.
+ *    are asynchronous, except that a call which needs more memory than any
+ *    before allocates it, waiting for the stream where it frees the old one.
+ *    Calls queued on one stream after another use the handle's memory in
+ *    turn: the later stream waits, on the device, for the earlier call.
  *  - A handle is not thread-safe: one handle per host thread and stream.
  *  - Errors are returned as a status code and never raised across the ABI.
  */
@@ -366,8 +369,8 @@ gevp_status gevp_backward_noalloc(gevp_handle h, int64_t n, int64_t nev, const v
  * Large products run in residue arithmetic on the INT8 matrix cores (see
  * zgemm_mod.hip) where every entry is then at least as accurate, root mean square
  * and relative to sum_k |op(A)(i, k)| |op(B)(k, j)|, as the FP64 matrix cores make
- * it; a check on the device sends every other product to those.  The handle keeps their scratch (up to 16 GiB,
- * the largest product's); under stream capture, or where the memory is not to
+ * it; a check on the device sends every other product to those.  The handle
+ * keeps their scratch (up to 16 GiB, the largest product's); under stream capture, or where the memory is not to
  * be had, the FP64 matrix cores do every product.
  */
 gevp_status gevp_k_zgemm(gevp_handle h, char opA, char opB, int64_t m, int64_t n, int64_t k,

@@ -109,8 +109,12 @@ struct gevp_ctx {
   size_t mod_bytes = 0;
   bool mod_borrowed = false;  // mod points into the caller-owned workspace
   bool no_mod = false;
-  hipStream_t mod_stream = nullptr;  // stream of the last product that used mod, done at mod_done
-  hipEvent_t mod_done = nullptr;
+  // ws, skw and mod are used in turn by calls on different streams: the stream of the
+  // last asynchronous call that used them, done with them at scratch_done
+  bool scratch_used = false;  // by the call at hand
+  bool scratch_pending = false;
+  hipStream_t scratch_stream = nullptr;
+  hipEvent_t scratch_done = nullptr;
   // split-K cost models count the compute units divided by this (a batched
   // worker shares the GPU with the other streams)
   int cu_div = 1;
@@ -136,6 +140,21 @@ void ext_assign(gevp_ctx* parent, gevp_ctx* child, int slot);
 // Workspace carving.  reserve() (re)allocates when `bytes` exceeds the current
 // size; take() hands out 256-byte aligned pieces until reset().
 gevp_status ws_reserve(gevp_ctx* c, size_t bytes);
+// Before memory of the handle is used on its stream: waits (on the device) for the
+// last call's use of it on another one.
+gevp_status scratch_order(gevp_ctx* c);
+// An entry point that returns with work queued: what it used of the handle's memory
+// is marked for calls on another stream when it returns.
+class QueuedCall {
+ public:
+  explicit QueuedCall(gevp_ctx* c) : c_(c) { c->scratch_used = false; }
+  ~QueuedCall();
+  QueuedCall(const QueuedCall&) = delete;
+  QueuedCall& operator=(const QueuedCall&) = delete;
+
+ private:
+  gevp_ctx* c_;
+};
 void* ws_take(gevp_ctx* c, size_t bytes);
 inline size_t ws_round(size_t b) { return (b + 255) & ~size_t(255); }
 

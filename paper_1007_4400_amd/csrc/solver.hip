@@ -65,7 +65,40 @@ int gevp_log_enabled() {
   return v;
 }
 
+namespace {
+// (an event recorded or waited for under capture would belong to the graph)
+bool capturing(gevp_ctx* c) {
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(c->stream, &cap) != hipSuccess) {
+    (void)hipGetLastError();
+    return true;
+  }
+  return cap != hipStreamCaptureStatusNone;
+}
+}  // namespace
+
+gevp_status scratch_order(gevp_ctx* c) {
+  c->scratch_used = true;
+  if (!c->scratch_pending || c->scratch_stream == c->stream || capturing(c)) return GEVP_OK;
+  GEVP_HIP_TRY(hipStreamWaitEvent(c->stream, c->scratch_done, 0));
+  c->scratch_stream = c->stream;
+  return GEVP_OK;
+}
+
+QueuedCall::~QueuedCall() {
+  if (!c_->scratch_used || capturing(c_)) return;
+  if ((c_->scratch_done || hipEventCreateWithFlags(&c_->scratch_done, hipEventDisableTiming) == hipSuccess) &&
+      hipEventRecord(c_->scratch_done, c_->stream) == hipSuccess) {
+    c_->scratch_stream = c_->stream;
+    c_->scratch_pending = true;
+  } else {
+    (void)hipGetLastError();
+    (void)hipStreamSynchronize(c_->stream);
+  }
+}
+
 gevp_status ws_reserve(gevp_ctx* c, size_t bytes) {
+  GEVP_TRY(scratch_order(c));
   c->ws_used = 0;
   if (bytes <= c->ws_bytes) return GEVP_OK;
   if (c->ext) return GEVP_ERR_WORKSPACE;  // the caller's buffer is too small
@@ -467,7 +500,7 @@ void gevp_destroy(gevp_handle h) {
   if (h->ws && !h->ext) (void)hipFree(h->ws);
   if (h->skw && !h->ext) (void)hipFree(h->skw);
   if (h->mod && !h->mod_borrowed) (void)hipFree(h->mod);
-  if (h->mod_done) (void)hipEventDestroy(h->mod_done);
+  if (h->scratch_done) (void)hipEventDestroy(h->scratch_done);
   for (int i = 0; i < h->fev_cap; ++i) (void)hipEventDestroy(h->fev[i]);
   delete[] h->fev;
   for (int i = 0; i < h->gev_cap; ++i) (void)hipEventDestroy(h->gev[i]);
@@ -524,6 +557,7 @@ gevp_status gevp_set_workspace(gevp_handle h, void* dev_ptr, size_t bytes) {
     return GEVP_ERR_INVALID;
   GEVP_HIP_TRY(hipSetDevice(h->device));
   GEVP_HIP_TRY(hipStreamSynchronize(h->stream));
+  if (h->scratch_pending) GEVP_HIP_TRY(hipEventSynchronize(h->scratch_done));
   std::vector<gevp_ctx*> subs = {h->aux, h->panel};
   for (gevp_ctx* q : h->qctx) subs.push_back(q);
   for (gevp_ctx* w : h->workers) subs.push_back(w);
@@ -1274,6 +1308,7 @@ gevp_status gevp_backward(gevp_handle h, int64_t n, int64_t nev, const void* X_,
   if (dA_ && ldda < n) return GEVP_ERR_INVALID;
   if (dB_ && (lddb < n || !lambda)) return GEVP_ERR_INVALID;
   GEVP_HIP_TRY(hipSetDevice(h->device));
+  QueuedCall queued(h);
   gevp_ctx* c = h;
   const zd* X = (const zd*)X_;
   const size_t need = ws_round(sizeof(zd) * n * nev) + ws_round(sizeof(double) * nev);
@@ -1513,6 +1548,7 @@ gevp_status gevp_k_zgemm(gevp_handle h, char opA, char opB, int64_t m, int64_t n
   if (k > 0 && ldb < (ob ? n : k)) return GEVP_ERR_INVALID;
   if (ldd < m || (Cm && ldc < m) || (E && lde < m)) return GEVP_ERR_INVALID;
   GEVP_HIP_TRY(hipSetDevice(h->device));
+  QueuedCall queued(h);
   return launch_zgemm(h, oa, ob, m, n, k, alpha, (const zd*)A, lda, (const zd*)B, ldb, beta,
                       (const zd*)Cm, ldc, gamma, (const zd*)E, lde, gcol, (zd*)D, ldd);
 }
@@ -1532,6 +1568,7 @@ gevp_status gevp_k_zgemm_tri(gevp_handle h, char opA, char opB, int64_t m, int64
   if (k > 0 && ldb < (ob ? n : k)) return GEVP_ERR_INVALID;
   if (ldd < m || (Cm && ldc < m)) return GEVP_ERR_INVALID;
   GEVP_HIP_TRY(hipSetDevice(h->device));
+  QueuedCall queued(h);
   return launch_zgemm(h, oa, ob, m, n, k, alpha, (const zd*)A, lda, (const zd*)B, ldb, beta,
                       (const zd*)Cm, ldc, 0.0, nullptr, 0, nullptr, (zd*)D, ldd, nullptr, lower,
                       upperA);
@@ -1547,6 +1584,7 @@ gevp_status gevp_k_filter_gemm(gevp_handle h, int precision, int64_t n, int64_t 
     return GEVP_ERR_INVALID;
   if (precision != GEVP_FP32 && precision != GEVP_BF16X3) return GEVP_ERR_INVALID;
   GEVP_HIP_TRY(hipSetDevice(h->device));
+  QueuedCall queued(h);
   const bool bf = precision == GEVP_BF16X3;
   const size_t bytes = bf ? bf16_planes_bytes(n) : (size_t)8 * n * n;
   const size_t wbytes = bf ? bf16_filter_work_bytes(n, m) : 0;
@@ -1566,6 +1604,7 @@ gevp_status gevp_k_filter_gemm(gevp_handle h, int precision, int64_t n, int64_t 
 gevp_status gevp_k_hemv(gevp_handle h, int64_t n, const void* M, int64_t ldm, const void* x, void* y) {
   if (!h || n < 1 || !M || ldm < n || !x || !y) return GEVP_ERR_INVALID;
   GEVP_HIP_TRY(hipSetDevice(h->device));
+  QueuedCall queued(h);
   GEVP_TRY(ws_reserve(h, hemv_work_bytes(n) + 256));
   void* w = ws_take(h, hemv_work_bytes(n));
   return launch_hemv(h, n, (const zd*)M, ldm, (const zd*)x, (zd*)y, w);
@@ -1597,6 +1636,7 @@ gevp_status gevp_k_trsm(gevp_handle h, char side, char trans, int64_t n, int64_t
   if (!left && !conj) return GEVP_ERR_INVALID;
   if (ldr < (left ? n : m)) return GEVP_ERR_INVALID;
   GEVP_HIP_TRY(hipSetDevice(h->device));
+  QueuedCall queued(h);
   // the diagonal-block inverses come from re-factoring a copy of L L^H's
   // diagonal blocks: L's own diagonal blocks are inverted directly instead
   GEVP_TRY(ws_reserve(h, ws_round(sizeof(zd) * n * 64) + ws_round(sizeof(zd) * n * n) + 256));

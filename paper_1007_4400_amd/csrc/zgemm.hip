@@ -525,6 +525,7 @@ int zgemm_splits(int64_t T, int nk, int64_t slots, int64_t max_parts) {
 }  // namespace
 
 gevp_status splitk_buffer(gevp_ctx* c, size_t need, void** out) {
+  GEVP_TRY(scratch_order(c));
   if (need > c->skw_bytes) {
     if (c->ext) return GEVP_ERR_WORKSPACE;  // caller-owned memory is never reallocated
     if (c->skw) {
@@ -551,11 +552,7 @@ void* mod_scratch(gevp_ctx* c, size_t bytes) {
     (void)hipGetLastError();
     return nullptr;
   }
-  // a caller that moves the handle to another stream: that stream's first
-  // product waits for the last one that used this scratch
-  if (c->mod_done && c->mod_stream != c->stream &&
-      hipStreamWaitEvent(c->stream, c->mod_done, 0) != hipSuccess)
-    return nullptr;
+  if (scratch_order(c) != GEVP_OK) return nullptr;
   if (c->ext && !c->mod_borrowed) {  // what the caller's workspace has left
     const size_t used = ws_round(c->ws_used);
     return (c->ws && used + bytes <= c->ws_bytes) ? c->ws + used : nullptr;
@@ -743,11 +740,6 @@ gevp_status launch_zgemm(gevp_ctx* c, int opA, int opB, int64_t m, int64_t n, in
     hipLaunchKernelGGL(k_zgemm_splitk_reduce, dim3((unsigned)((elems + 255) / 256)), dim3(256), 0,
                        c->stream, p);
     GEVP_HIP_TRY(hipGetLastError());
-  }
-  if (mod) {
-    if (!c->mod_done) GEVP_HIP_TRY(hipEventCreateWithFlags(&c->mod_done, hipEventDisableTiming));
-    GEVP_HIP_TRY(hipEventRecord(c->mod_done, c->stream));
-    c->mod_stream = c->stream;
   }
   if (timed) {
     // algorithmic flops: 8 per complex multiply-add of the product as
