@@ -358,10 +358,10 @@ gevp_status launch_cgemm32_filter(gevp_ctx* c, int64_t m, int64_t n, int64_t k, 
   const int64_t total = (int64_t)p.tiles1 * batch;
   const int nk = (p.K + KT - 1) / KT;
   constexpr int64_t MAX_PARTS = (int64_t)(SKW_BYTES / (sizeof(zf) * BM * BN));
-  int parts = c->no_split ? 1
-                          : split32(total, nk, std::max<int64_t>(1, (int64_t)gevp_device_cus(c->device) /
-                                                                        std::max(1, c->cu_div)),
-                                    MAX_PARTS);
+  int parts = 1;
+  if (splitk_possible(c))
+    parts = split32(total, nk,
+                    std::max<int64_t>(1, (int64_t)gevp_device_cus(c->device) / std::max(1, c->cu_div)), MAX_PARTS);
   p.part = nullptr;
   if (parts > 1) {
     void* buf = nullptr;

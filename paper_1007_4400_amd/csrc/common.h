@@ -140,6 +140,9 @@ void ext_assign(gevp_ctx* parent, gevp_ctx* child, int slot);
 // Workspace carving.  reserve() (re)allocates when `bytes` exceeds the current
 // size; take() hands out 256-byte aligned pieces until reset().
 gevp_status ws_reserve(gevp_ctx* c, size_t bytes);
+// whether c's stream is being captured (also where that cannot be told): nothing may
+// then be allocated, and no event recorded or waited for that is not the graph's own
+bool stream_capturing(gevp_ctx* c);
 // Before memory of the handle is used on its stream: waits (on the device) for the
 // last call's use of it on another one.
 gevp_status scratch_order(gevp_ctx* c);
@@ -209,7 +212,9 @@ gevp_status mod_prepare(gevp_ctx* c, int64_t m, int64_t k, int opA, const zd* A,
 // flags, raised when the product was left to the FP64 kernels
 gevp_status launch_mod_gemm(gevp_ctx* c, const ModGemmCall& g, void* scratch, const int** flag1,
                             const int** flag2);
-// the stream's split-K buffer (SKW_BYTES, allocated on first use)
+// the stream's split-K buffer (SKW_BYTES, allocated on first use), and whether it is
+// there or can be allocated now: where not, k is not split
+bool splitk_possible(gevp_ctx* c);
 gevp_status splitk_buffer(gevp_ctx* c, size_t need, void** out);
 // scratch of at least `bytes` for the next product on c's stream, or null
 void* mod_scratch(gevp_ctx* c, size_t bytes);

@@ -147,13 +147,7 @@ class LaunchTurn {
 // whether this handle's stream may take such a launch now: not under capture (the
 // outcome is read back), not where one gave up or other work is meant to run beside
 inline bool resident_allowed(gevp_ctx* c) {
-  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  if (c->shared_gpu) return false;
-  if (hipStreamIsCapturing(c->stream, &cap) != hipSuccess) {
-    (void)hipGetLastError();
-    return false;
-  }
-  return cap == hipStreamCaptureStatusNone;
+  return !c->shared_gpu && !stream_capturing(c);
 }
 
 // whether all work-groups of a launch fit the device at once. An ordinary launch

@@ -65,9 +65,7 @@ int gevp_log_enabled() {
   return v;
 }
 
-namespace {
-// (an event recorded or waited for under capture would belong to the graph)
-bool capturing(gevp_ctx* c) {
+bool stream_capturing(gevp_ctx* c) {
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(c->stream, &cap) != hipSuccess) {
     (void)hipGetLastError();
@@ -75,18 +73,17 @@ bool capturing(gevp_ctx* c) {
   }
   return cap != hipStreamCaptureStatusNone;
 }
-}  // namespace
 
 gevp_status scratch_order(gevp_ctx* c) {
   c->scratch_used = true;
-  if (!c->scratch_pending || c->scratch_stream == c->stream || capturing(c)) return GEVP_OK;
+  if (!c->scratch_pending || c->scratch_stream == c->stream || stream_capturing(c)) return GEVP_OK;
   GEVP_HIP_TRY(hipStreamWaitEvent(c->stream, c->scratch_done, 0));
   c->scratch_stream = c->stream;
   return GEVP_OK;
 }
 
 QueuedCall::~QueuedCall() {
-  if (!c_->scratch_used || capturing(c_)) return;
+  if (!c_->scratch_used || stream_capturing(c_)) return;
   if ((c_->scratch_done || hipEventCreateWithFlags(&c_->scratch_done, hipEventDisableTiming) == hipSuccess) &&
       hipEventRecord(c_->scratch_done, c_->stream) == hipSuccess) {
     c_->scratch_stream = c_->stream;

@@ -524,6 +524,10 @@ int zgemm_splits(int64_t T, int nk, int64_t slots, int64_t max_parts) {
 }
 }  // namespace
 
+bool splitk_possible(gevp_ctx* c) {
+  return !c->no_split && (c->skw_bytes > 0 || (!c->ext && !stream_capturing(c)));
+}
+
 gevp_status splitk_buffer(gevp_ctx* c, size_t need, void** out) {
   GEVP_TRY(scratch_order(c));
   if (need > c->skw_bytes) {
@@ -545,13 +549,7 @@ gevp_status splitk_buffer(gevp_ctx* c, size_t need, void** out) {
 }
 
 void* mod_scratch(gevp_ctx* c, size_t bytes) {
-  // under capture nothing may be allocated and no event of this handle may be
-  // tied to the graph: the FP64 kernels alone
-  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(c->stream, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) {
-    (void)hipGetLastError();
-    return nullptr;
-  }
+  if (stream_capturing(c)) return nullptr;  // the FP64 kernels alone
   if (scratch_order(c) != GEVP_OK) return nullptr;
   if (c->ext && !c->mod_borrowed) {  // what the caller's workspace has left
     const size_t used = ws_round(c->ws_used);
@@ -649,7 +647,8 @@ gevp_status launch_zgemm(gevp_ctx* c, int opA, int opB, int64_t m, int64_t n, in
   // ... unless the K range, one chain of about 1 us per 16 K on skinny tiles, is long
   // enough for a cut one (2.2 us per 16 K and a second launch) to be shorter: 3000 x
   // 64 x 960 with its launch 128 us on skinny tiles, 65 cut
-  if (skinny && !c->no_split) {
+  const bool can_split = splitk_possible(c);
+  if (skinny && can_split) {
     const int s = zgemm_splits(total, nk, slots, SPLIT_TILES_MAX), nks = (nk + s - 1) / s;
     const int64_t groups = total * ((nk + nks - 1) / nks), tiles = 4 * total;
     const double chain = (double)nk * (double)((tiles + slots - 1) / slots);
@@ -672,7 +671,7 @@ gevp_status launch_zgemm(gevp_ctx* c, int opA, int opB, int64_t m, int64_t n, in
       mod = true;
     }
   }
-  int s = (c->no_split || skinny || mod)
+  int s = (!can_split || skinny || mod)
               ? 1
               : zgemm_splits(total, nk, slots, SPLIT_TILES_MAX);
   p.nks = nk > 0 ? (nk + s - 1) / s : 1;
