@@ -367,6 +367,7 @@ gevp_status launch_cgemm32_filter(gevp_ctx* c, int64_t m, int64_t n, int64_t k, 
     void* buf = nullptr;
     GEVP_TRY(splitk_buffer(c, (size_t)parts * total * BM * BN * sizeof(zf), &buf));
     p.part = (zf*)buf;
+    if (!buf) parts = 1;
   }
   p.tiles = (int)total;
   p.nks = nk > 0 ? (nk + parts - 1) / parts : 1;

@@ -369,6 +369,7 @@ gevp_status panel_ctx(gevp_ctx* c, gevp_ctx** out) {
       return GEVP_ERR_HIP;
     }
     w->owns_stream = true;
+    w->parent = c;
     c->panel = w;
     ext_assign(c, w, SLOT_PANEL);
   }

@@ -87,8 +87,10 @@ struct gevp_ctx {
   // panel stream of the Cholesky factorisation and its two events (on demand)
   gevp_ctx* panel = nullptr;
   hipEvent_t pev[2] = {nullptr, nullptr};
-  // per-stream sub-contexts of gevp_solve_batched (own stream and workspace)
+  // per-stream sub-contexts of gevp_solve_batched (own stream and workspace), and
+  // theirs and the other sub-contexts' way back
   std::vector<gevp_ctx*> workers;
+  gevp_ctx* parent = nullptr;
   // streams of the contour filter's independent quadrature nodes (on demand)
   std::vector<gevp_ctx*> qctx;
   bool owns_stream = false;
@@ -103,12 +105,14 @@ struct gevp_ctx {
   bool no_split = false;
   // scratch of the residue-arithmetic products (zgemm_mod.hip): library-owned,
   // grown on demand and freed by destroy; in a caller-owned workspace the part
-  // of ws beyond ws_used serves instead.  no_mod: keep to the FP64 kernels
-  // (calls that must not allocate, and after a failed allocation).
+  // of ws beyond ws_used serves instead.  It is given back where other memory of the
+  // handle cannot be had otherwise.  no_mod: keep to the FP64 kernels (calls that
+  // must not allocate).  mod_failed: as much could not be had in this call.
   char* mod = nullptr;
   size_t mod_bytes = 0;
   bool mod_borrowed = false;  // mod points into the caller-owned workspace
   bool no_mod = false;
+  size_t mod_failed = SIZE_MAX;
   // ws, skw and mod are used in turn by calls on different streams: the stream of the
   // last asynchronous call that used them, done with them at scratch_done
   bool scratch_used = false;  // by the call at hand
@@ -140,17 +144,25 @@ void ext_assign(gevp_ctx* parent, gevp_ctx* child, int slot);
 // Workspace carving.  reserve() (re)allocates when `bytes` exceeds the current
 // size; take() hands out 256-byte aligned pieces until reset().
 gevp_status ws_reserve(gevp_ctx* c, size_t bytes);
+// hipMalloc, where need be after the scratch that the handle can do without (the
+// residue products') has been given back; null where that does not help
+void* device_alloc(gevp_ctx* c, size_t bytes);
 // whether c's stream is being captured (also where that cannot be told): nothing may
 // then be allocated, and no event recorded or waited for that is not the graph's own
 bool stream_capturing(gevp_ctx* c);
 // Before memory of the handle is used on its stream: waits (on the device) for the
 // last call's use of it on another one.
 gevp_status scratch_order(gevp_ctx* c);
+// A new call: what could not be allocated before is tried again.
+void scratch_retry(gevp_ctx* c);
 // An entry point that returns with work queued: what it used of the handle's memory
 // is marked for calls on another stream when it returns.
 class QueuedCall {
  public:
-  explicit QueuedCall(gevp_ctx* c) : c_(c) { c->scratch_used = false; }
+  explicit QueuedCall(gevp_ctx* c) : c_(c) {
+    c->scratch_used = false;
+    scratch_retry(c);
+  }
   ~QueuedCall();
   QueuedCall(const QueuedCall&) = delete;
   QueuedCall& operator=(const QueuedCall&) = delete;
@@ -212,8 +224,9 @@ gevp_status mod_prepare(gevp_ctx* c, int64_t m, int64_t k, int opA, const zd* A,
 // flags, raised when the product was left to the FP64 kernels
 gevp_status launch_mod_gemm(gevp_ctx* c, const ModGemmCall& g, void* scratch, const int** flag1,
                             const int** flag2);
-// the stream's split-K buffer (SKW_BYTES, allocated on first use), and whether it is
-// there or can be allocated now: where not, k is not split
+// the stream's split-K buffer (SKW_BYTES, allocated on first use; null where there is
+// no memory for it), and whether it is there or may be allocated now: where not, k
+// is not split
 bool splitk_possible(gevp_ctx* c);
 gevp_status splitk_buffer(gevp_ctx* c, size_t need, void** out);
 // scratch of at least `bytes` for the next product on c's stream, or null

@@ -442,6 +442,7 @@ gevp_status quad_ctx(gevp_ctx* c, int i, gevp_ctx** out) {
     }
     w->owns_stream = true;
     w->inner_streams = false;
+    w->parent = c;
     c->qctx.push_back(w);
     ext_assign(c, w, SLOT_QUAD0 + (int)c->qctx.size() - 1);
   }

@@ -94,8 +94,16 @@ QueuedCall::~QueuedCall() {
   }
 }
 
+void scratch_retry(gevp_ctx* c) {
+  c->mod_failed = SIZE_MAX;
+  if (c->aux) c->aux->mod_failed = SIZE_MAX;
+  if (c->panel) c->panel->mod_failed = SIZE_MAX;
+  for (gevp_ctx* q : c->qctx) q->mod_failed = SIZE_MAX;
+}
+
 gevp_status ws_reserve(gevp_ctx* c, size_t bytes) {
   GEVP_TRY(scratch_order(c));
+  scratch_retry(c);
   c->ws_used = 0;
   if (bytes <= c->ws_bytes) return GEVP_OK;
   if (c->ext) return GEVP_ERR_WORKSPACE;  // the caller's buffer is too small
@@ -105,13 +113,46 @@ gevp_status ws_reserve(gevp_ctx* c, size_t bytes) {
     c->ws = nullptr;
     c->ws_bytes = 0;
   }
-  if (hipMalloc((void**)&c->ws, bytes) != hipSuccess) {
-    c->ws = nullptr;
-    (void)hipGetLastError();
-    return GEVP_ERR_ALLOC;
-  }
+  c->ws = (char*)device_alloc(c, bytes);
+  if (!c->ws) return GEVP_ERR_ALLOC;
   c->ws_bytes = bytes;
   return GEVP_OK;
+}
+
+namespace {
+bool drop_mod(gevp_ctx* c) {
+  if (!c || !c->mod || c->mod_borrowed) return false;
+  (void)hipStreamSynchronize(c->stream);  // earlier launches may still read it
+  if (c->scratch_pending) (void)hipEventSynchronize(c->scratch_done);
+  (void)hipFree(c->mod);
+  c->mod = nullptr;
+  c->mod_bytes = 0;
+  return true;
+}
+std::mutex g_drop_mu;  // batch workers that share a parent
+}  // namespace
+
+void* device_alloc(gevp_ctx* c, size_t bytes) {
+  void* p = nullptr;
+  if (hipMalloc(&p, bytes) == hipSuccess) return p;
+  (void)hipGetLastError();
+  // A batch worker takes its own and its handle's (idle meanwhile, but for its
+  // workers, which are at work); any other context everything of its handle's.
+  gevp_ctx* h = c->parent ? c->parent : c;
+  bool freed = drop_mod(c);
+  for (gevp_ctx* x : c->qctx) freed |= drop_mod(x);
+  {
+    std::lock_guard<std::mutex> lock(g_drop_mu);
+    for (gevp_ctx* x : {h, h->aux, h->panel}) freed |= drop_mod(x);
+    for (gevp_ctx* x : h->qctx) freed |= drop_mod(x);
+  }
+  if (!c->batch_worker)
+    for (gevp_ctx* x : h->workers) freed |= drop_mod(x);
+  if (gevp_log_enabled())
+    fprintf(stderr, "[gevp] no %zu bytes of device memory%s\n", bytes, freed ? ": scratch given back" : "");
+  if (freed && hipMalloc(&p, bytes) == hipSuccess) return p;
+  (void)hipGetLastError();
+  return nullptr;
 }
 
 void ext_assign(gevp_ctx* parent, gevp_ctx* child, int slot) {
@@ -569,7 +610,7 @@ gevp_status gevp_set_workspace(gevp_handle h, void* dev_ptr, size_t bytes) {
     if (c->mod && !c->mod_borrowed) (void)hipFree(c->mod);
     c->mod = nullptr;
     c->mod_bytes = 0;
-    c->mod_borrowed = c->no_mod = false;
+    c->mod_borrowed = false;
     c->ws = nullptr;
     c->ws_bytes = 0;
     c->ws_used = 0;
@@ -607,6 +648,7 @@ gevp_status aux_ctx(gevp_ctx* c, gevp_ctx** out) {
     }
     w->owns_stream = true;
     w->shared_gpu = true;
+    w->parent = c;
     c->aux = w;
     ext_assign(c, w, SLOT_AUX);
   }
@@ -718,7 +760,6 @@ gevp_status solve_once(gevp_handle h, const gevp_opts* opts, int64_t n, const vo
   const bool full_seed = seeded && k0 >= nb;
   const bool spec = full_seed && c->inner_streams;
   ModBytes mb = solve_mod_bytes(n, nb, spec);
-  if (c->no_mod) mb = ModBytes();
   if (c->ext) {  // whatever the caller's buffer has beyond the solve's own needs
     GEVP_TRY(ws_reserve(c, need));
     size_t left = c->ws_bytes - need;
@@ -734,7 +775,8 @@ gevp_status solve_once(gevp_handle h, const gevp_opts* opts, int64_t n, const vo
       rs = ws_reserve(c, need);
     }
     GEVP_TRY(rs);
-    if (mb.main) (void)mod_scratch(c, mb.main);  // one allocation for all products
+    // one allocation for all products; without it the FP64 kernels do them
+    if (mb.main && !mod_scratch(c, mb.main)) mb = ModBytes();
   }
   zd* Af = (zd*)ws_take(c, sizeof(zd) * nn);
   zd* Bf = (zd*)ws_take(c, sizeof(zd) * nn);
@@ -1383,6 +1425,7 @@ gevp_status gevp_solve_batched(gevp_handle h, const gevp_opts* opts, int count, 
     w->owns_stream = true;
     w->inner_streams = false;
     w->batch_worker = true;
+    w->parent = h;
     h->workers.push_back(w);
   }
   // event timing of the filter launches (profiling flag 2) carries over; the

@@ -538,11 +538,9 @@ gevp_status splitk_buffer(gevp_ctx* c, size_t need, void** out) {
       c->skw = nullptr;
       c->skw_bytes = 0;
     }
-    if (need > SKW_BYTES || hipMalloc(&c->skw, SKW_BYTES) != hipSuccess) {
-      c->skw = nullptr;
-      return GEVP_ERR_ALLOC;
-    }
-    c->skw_bytes = SKW_BYTES;
+    if (need > SKW_BYTES) return GEVP_ERR_ALLOC;
+    c->skw = device_alloc(c, SKW_BYTES);
+    if (c->skw) c->skw_bytes = SKW_BYTES;
   }
   *out = c->skw;
   return GEVP_OK;
@@ -556,7 +554,7 @@ void* mod_scratch(gevp_ctx* c, size_t bytes) {
     return (c->ws && used + bytes <= c->ws_bytes) ? c->ws + used : nullptr;
   }
   if (bytes <= c->mod_bytes) return c->mod;
-  if (c->ext || bytes > ((size_t)16 << 30)) return nullptr;
+  if (c->ext || bytes > ((size_t)16 << 30) || bytes >= c->mod_failed) return nullptr;
   if (c->mod) {
     if (hipStreamSynchronize(c->stream) != hipSuccess) return nullptr;  // earlier launches may still read it
     (void)hipFree(c->mod);
@@ -565,8 +563,9 @@ void* mod_scratch(gevp_ctx* c, size_t bytes) {
   }
   if (hipMalloc((void**)&c->mod, bytes) != hipSuccess) {
     c->mod = nullptr;
-    c->no_mod = true;  // no memory to spare: stay with the FP64 kernels
+    c->mod_failed = bytes;  // no memory to spare: the FP64 kernels
     (void)hipGetLastError();
+    if (gevp_log_enabled()) fprintf(stderr, "[gevp] no %zu bytes of scratch for residue products\n", bytes);
     return nullptr;
   }
   c->mod_bytes = bytes;
@@ -681,6 +680,10 @@ gevp_status launch_zgemm(gevp_ctx* c, int opA, int opB, int64_t m, int64_t n, in
     void* buf = nullptr;
     GEVP_TRY(splitk_buffer(c, (size_t)p.splits * total * BM * BN * sizeof(zd), &buf));
     p.part = (zd*)buf;
+    if (!buf) {
+      p.nks = nk;
+      p.splits = 1;
+    }
   }
   const int64_t blocks = total * p.splits;
   p.total = (int)blocks;
