@@ -81,9 +81,11 @@ struct gevp_ctx {
   // stream, unless the solve holds a share for it, and a handle where one gave up
   bool shared_gpu = false;
   bool batch_worker = false;  // other workers' launches run beside this stream's
-  // where set, such launches raise this flag and go on (their share of the device is
-  // held by the caller, which looks at the flag when it next waits for the stream)
+  // where set, such launches raise this flag, record the event and go on (their share
+  // of the device is held by the caller, which looks at the flag when it next waits
+  // for the stream)
   int* defer_err = nullptr;
+  hipEvent_t defer_done = nullptr;
   // panel stream of the Cholesky factorisation and its two events (on demand)
   gevp_ctx* panel = nullptr;
   hipEvent_t pev[2] = {nullptr, nullptr};
@@ -299,6 +301,7 @@ gevp_status contour_apply32(gevp_ctx* c, int64_t n, int64_t m, const zd* Q, int6
 // Small Hermitian eigensolver (n <= 2048): H (full storage, overwritten),
 // theta ascending, Z (n x n) unitary.  work >= heev_work_bytes(n).
 size_t heev_work_bytes(int64_t n);
+constexpr int TRD1_MAX = 60;  // largest order whose tridiagonalisation takes one work-group
 // Eigen-decomposition of the real symmetric tridiagonal T (diagonal d[n],
 // off-diagonal e[n-1]): theta ascending by Sturm-count multisection, the
 // orthonormal eigenvectors by inverse iteration, Zt[i * n + j] = component i

@@ -11,8 +11,8 @@
 #ifndef GEVP_EXCHANGE_H
 #define GEVP_EXCHANGE_H
 #include <algorithm>
-#include <atomic>
-#include <thread>
+#include <condition_variable>
+#include <mutex>
 
 #include "common.h"
 
@@ -108,39 +108,47 @@ inline gevp_status fill_holes(gevp_ctx* c, unsigned long long* x, int64_t words,
 // The compute units of a device that such launches of this process may count on: a
 // launch takes as many as it has work-groups before it starts and gives them back
 // when it has ended, so that launches of several threads never each hold a part of
-// what the others wait for.  It waits as long as it takes: which kernel runs must
-// not depend on who else is running (the results would, in their last bits), and a
-// holder never waits for a second share.
+// what the others wait for.  It waits in turn, asleep, and for no longer than the
+// launches before it run: a share is taken only when the stream has nothing else
+// left to do, and a holder never waits for a second one.  (It is not left to chance
+// which kernel runs: the results would then depend, in their last bits, on who else
+// is running.)
 class LaunchTurn {
  public:
-  LaunchTurn(gevp_ctx* c, int64_t groups) : used_(units(c->device)) {
-    int cus = 0;
-    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device) != hipSuccess) {
-      (void)hipGetLastError();
-      cus = 1;
-    }
-    share_ = (int)std::min<int64_t>(groups, cus);
-    if (take(cus)) return;
-    // the share is then held for no longer than the launch takes
+  LaunchTurn(gevp_ctx* c, int64_t groups) : d_(device(c->device)) {
     (void)hipStreamSynchronize(c->stream);
-    while (!take(cus)) std::this_thread::yield();
+    const int cus = gevp_device_cus(c->device);
+    share_ = (int)std::min<int64_t>(groups, cus);
+    std::unique_lock<std::mutex> lock(d_.mu);
+    const unsigned long long ticket = d_.next++;
+    d_.cv.wait(lock, [&] { return ticket == d_.serving && d_.used + share_ <= cus; });
+    d_.used += share_;
+    ++d_.serving;
+    lock.unlock();
+    d_.cv.notify_all();
   }
-  ~LaunchTurn() { used_.fetch_sub(share_); }
+  ~LaunchTurn() {
+    {
+      std::lock_guard<std::mutex> lock(d_.mu);
+      d_.used -= share_;
+    }
+    d_.cv.notify_all();
+  }
   LaunchTurn(const LaunchTurn&) = delete;
   LaunchTurn& operator=(const LaunchTurn&) = delete;
 
  private:
-  static std::atomic<int>& units(int device) {
-    static std::atomic<int> used[64];
-    return used[device >= 0 && device < 64 ? device : 0];
+  struct Device {
+    std::mutex mu;
+    std::condition_variable cv;
+    int used = 0;
+    unsigned long long next = 0, serving = 0;
+  };
+  static Device& device(int i) {
+    static Device all[64];
+    return all[i >= 0 && i < 64 ? i : 0];
   }
-  bool take(int cus) {
-    int u = used_.load();
-    while (u + share_ <= cus)
-      if (used_.compare_exchange_weak(u, u + share_)) return true;
-    return false;
-  }
-  std::atomic<int>& used_;
+  Device& d_;
   int share_;
 };
 

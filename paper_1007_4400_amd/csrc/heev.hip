@@ -300,7 +300,6 @@ __device__ __forceinline__ zd column_step(int s, int j, const Reflector& f, cons
 
 // n <= 60: one work-group of 16 waves, up to four columns a wave, the exchange
 // through the LDS and one barrier per reflector.
-constexpr int TRD1_MAX = 60;
 __global__ __launch_bounds__(1024) void k_hetrd_one(TrdArgs a) {
   __shared__ zd P[2][64], C[2][64], V[2][64];
   const int n = a.n, lane = threadIdx.x & 63;
@@ -1114,15 +1113,14 @@ gevp_status hetrd_all(gevp_ctx* c, const TrdArgs& a, TrdExchange x, bool* done) 
     GEVP_TRY(fill_holes(c, x.x, words, nullptr));
     hipLaunchKernelGGL(f, dim3((unsigned)groups), dim3((unsigned)threads), 0, c->stream, a, x);
     GEVP_HIP_TRY(hipGetLastError());
+    GEVP_HIP_TRY(hipEventRecord(c->defer_done, c->stream));
     *done = true;
     return GEVP_OK;
   }
-  // (a batch worker empties its stream first, so that its share of the device is
-  // held no longer than the launch: eight problems of n = 1500 to 3000 took 90 ms
-  // with a launch per reflector, 76 ms so)
-  if (c->batch_worker) GEVP_HIP_TRY(hipStreamSynchronize(c->stream));
-  LaunchTurn turn(c, groups);
+  // (eight problems of n = 1500 to 3000 at a time took 90 ms with a launch per
+  // reflector, 76 ms with shares of the device)
   GEVP_TRY(fill_holes(c, x.x, words, x.err));
+  LaunchTurn turn(c, groups);
   hipLaunchKernelGGL(f, dim3((unsigned)groups), dim3((unsigned)threads), 0, c->stream, a, x);
   const hipError_t launched = hipGetLastError();
   int err = 1;
@@ -1185,7 +1183,7 @@ gevp_status heev_small(gevp_ctx* c, int64_t n64, zd* H, int64_t ldh, double* the
     TrdExchange x{(unsigned long long*)tw, 0, (int*)a.pb, EXCHANGE_SPINS};
     GEVP_TRY(hetrd_all(c, a, x, &done));
   }
-  if (n <= TRD1_MAX && !c->shared_gpu) {
+  if (n <= TRD1_MAX) {
     hipLaunchKernelGGL(k_hetrd_one, dim3(1), dim3(1024), 0, c->stream, a);
     GEVP_HIP_TRY(hipGetLastError());
     done = true;

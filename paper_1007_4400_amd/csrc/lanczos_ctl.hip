@@ -563,15 +563,14 @@ gevp_status lanczos_resident(gevp_ctx* c, int64_t n, const LanczosRun* runs, int
   // (on a second stream one after the other: a smaller share of the device is held)
   const bool together = !c->defer_err && resident_fits(c, f, threads, (int64_t)a.groups * count);
   if (!together && !resident_fits(c, f, threads, a.groups)) return GEVP_OK;
-  if (c->batch_worker) GEVP_HIP_TRY(hipStreamSynchronize(c->stream));
-  std::unique_ptr<LaunchTurn> turn;
-  if (!c->defer_err) turn.reset(new LaunchTurn(c, a.groups * (together ? count : 1)));
   a.err = c->defer_err ? c->defer_err : (int*)((zd*)area[0] + 3 * n);
   for (int k = 0; k < 2; ++k)
     if (used[k])
       GEVP_TRY(fill_holes(c, (unsigned long long*)(area[k] + head), (int64_t)(used[k] / 8),
                           c->defer_err ? nullptr : a.err));
   for (int r = 0; r < count; ++r) GEVP_TRY(launch_randn(c, n, 1, (zd*)a.job[r].v0, n, 0, runs[r].seed));
+  std::unique_ptr<LaunchTurn> turn;
+  if (!c->defer_err) turn.reset(new LaunchTurn(c, a.groups * (together ? count : 1)));
   hipError_t launched = hipSuccess;
   for (int r = 0; r < (together ? 1 : count); ++r) {
     if (!together) a.job[0] = a.job[r];
@@ -581,6 +580,7 @@ gevp_status lanczos_resident(gevp_ctx* c, int64_t n, const LanczosRun* runs, int
   }
   if (c->defer_err) {
     GEVP_HIP_TRY(launched);
+    GEVP_HIP_TRY(hipEventRecord(c->defer_done, c->stream));
     *done = true;
     return GEVP_OK;
   }

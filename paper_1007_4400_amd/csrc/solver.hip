@@ -670,35 +670,49 @@ struct EventPair {
   }
 };
 
-// The share of the device for single-launch kernels on the second stream: they
-// overlap the main stream's work, so nothing waits for their outcome there; it is
-// read with the first sweep's results.  Until then the main stream's own such
-// launches count on the same share (they wait for the second stream's work).  Given
-// back on any exit, after the second stream's work (EventPair waits for it; declared
-// after this).  The host had been busy with some 400 small launches there while the
-// main stream waited for it: seeded solves n = 2048 14.6 -> 12.8 ms, contour n = 1100
-// 12.0 -> 10.7 ms, n = 8192 153 -> 149 ms.
+// The share of the device for a single-launch kernel on the second stream, which
+// overlaps the main stream's work: the host waits for the stream to come to it, takes
+// the share, queues the launch and what follows it, and gives the share back when
+// the launch has ended, before it waits for anything else.  The kernel's outcome is
+// read with the first sweep's results.  On any other exit the second stream's work is
+// waited for first (EventPair, declared after this).  The host had been busy with
+// some 400 small launches there while the main stream waited for it: seeded solves
+// n = 2048 14.6 -> 12.8 ms, contour n = 1100 12.0 -> 10.7 ms, n = 8192 153 -> 149 ms.
 struct SecondTurn {
-  gevp_ctx *main = nullptr, *second = nullptr;
+  gevp_ctx* second = nullptr;
+  int* err = nullptr;  // null: no such launches there
+  hipEvent_t done = nullptr;
   std::unique_ptr<LaunchTurn> turn;
-  // groups: of the largest of the launches, which follow one another
-  void take(gevp_ctx* c, gevp_ctx* ax, int* err, int64_t groups) {
-    if (!resident_allowed(c)) return;
-    turn.reset(new LaunchTurn(c, groups));
-    main = c;
+  gevp_status open(gevp_ctx* c, gevp_ctx* ax, int* flag) {
+    if (!resident_allowed(c)) return GEVP_OK;
+    GEVP_HIP_TRY(hipEventCreateWithFlags(&done, hipEventDisableTiming));
     second = ax;
-    ax->shared_gpu = false;
-    ax->defer_err = c->defer_err = err;
+    err = flag;
+    return GEVP_OK;
   }
-  void release() {
-    if (second) {
-      second->shared_gpu = true;
-      second->defer_err = main->defer_err = nullptr;
-      second = nullptr;
-    }
+  void take(int64_t groups) {
+    turn.reset(new LaunchTurn(second, groups));
+    second->shared_gpu = false;
+    second->defer_err = err;
+    second->defer_done = done;
+  }
+  gevp_status give() {
+    if (!turn) return GEVP_OK;
+    GEVP_HIP_TRY(hipEventSynchronize(done));
+    drop();
+    return GEVP_OK;
+  }
+  void drop() {
+    if (!turn) return;
+    second->shared_gpu = true;
+    second->defer_err = nullptr;
+    second->defer_done = nullptr;
     turn.reset();
   }
-  ~SecondTurn() { release(); }
+  ~SecondTurn() {
+    drop();
+    if (done) (void)hipEventDestroy(done);
+  }
 };
 
 gevp_status solve_once(gevp_handle h, const gevp_opts* opts, int64_t n, const void* A_,
@@ -869,10 +883,18 @@ gevp_status solve_once(gevp_handle h, const gevp_opts* opts, int64_t n, const vo
   SecondTurn turn2;
   EventPair evs;
   gevp_ctx* ax = nullptr;
+  // eight rows or columns a work-group
+  const bool lan_resident = n >= 64 && n <= 2048;
+  const int64_t lan_groups = (n + 7) / 8, heev_groups = (nb + 7) / 8;
+  auto norms2 = [&]() -> gevp_status {
+    const LanczosRun runs[2] = {{Af, n, lzn, o.seed ^ 0xA11CEull, bA}, {Bf, n, lzn, o.seed ^ 0xB0Bull, bB}};
+    GEVP_TRY(lanczos_bounds_all(ax, n, runs, 2, frac, lanw, lanw2));
+    GEVP_TRY(launch_copy_real(ax, 1, bA + 5, norms));
+    return launch_copy_real(ax, 1, bB + 5, norms + 1);
+  };
   if (spec) {
     GEVP_TRY(aux_ctx(c, &ax));
-    // eight rows or columns a work-group; the Lanczos runs up to order 2048
-    turn2.take(c, ax, flags + 4, ((n <= 2048 ? n : nb) + 7) / 8);
+    GEVP_TRY(turn2.open(c, ax, flags + 4));
     ax->profiling = c->profiling & 4;
     ax->gev_used = 0;
     ax->gev_flops = 0.0;
@@ -891,13 +913,7 @@ gevp_status solve_once(gevp_handle h, const gevp_opts* opts, int64_t n, const vo
     GEVP_HIP_TRY(hipEventRecord(evs.fork, c->stream));
     GEVP_HIP_TRY(hipStreamWaitEvent(ax->stream, evs.fork, 0));
     evs.second = ax->stream;
-    auto norms2 = [&]() -> gevp_status {
-      const LanczosRun runs[2] = {{Af, n, lzn, o.seed ^ 0xA11CEull, bA}, {Bf, n, lzn, o.seed ^ 0xB0Bull, bB}};
-      GEVP_TRY(lanczos_bounds_all(ax, n, runs, 2, frac, lanw, lanw2));
-      GEVP_TRY(launch_copy_real(ax, 1, bA + 5, norms));
-      return launch_copy_real(ax, 1, bB + 5, norms + 1);
-    };
-    GEVP_TRY(norms2());
+    if (!turn2.err || !lan_resident) GEVP_TRY(norms2());
   }
 
   // ---------------- Cholesky of B
@@ -909,16 +925,22 @@ gevp_status solve_once(gevp_handle h, const gevp_opts* opts, int64_t n, const vo
   GEVP_TRY(chol_lower(c, n, L, n, Dinv, n, flags + 1, spec ? evs.mid : nullptr, C, n, n));
   tm.stop(info, GEVP_STAGE_CHOL);
   if (spec) {  // second stream, from the Cholesky's midpoint on
+    if (turn2.err && lan_resident) {  // the norms, the Cholesky's launches being queued
+      turn2.take(lan_groups);
+      GEVP_TRY(norms2());
+      GEVP_TRY(turn2.give());
+    }
     GEVP_HIP_TRY(hipStreamWaitEvent(ax->stream, evs.mid, 0));
     auto second = [&]() -> gevp_status {
       GEVP_TRY(launch_zgemm(ax, 0, 0, n, nb, n, 1.0, Af, n, X0, ldx0, 0.0, nullptr, 0, 0.0, nullptr,
                             0, nullptr, T, n));
       GEVP_TRY(launch_zgemm(ax, 1, 0, nb, nb, n, 1.0, X0, ldx0, T, n, 0.0, nullptr, 0, 0.0, nullptr,
                             0, nullptr, Hs, nb, nullptr, 1));
-      GEVP_TRY(launch_mirror_lower(ax, nb, Hs, nb, Hs, nb, nullptr));
-      return heev_small(ax, nb, Hs, nb, theta, Zs, nb, heevw);
+      return launch_mirror_lower(ax, nb, Hs, nb, Hs, nb, nullptr);
     };
-    const gevp_status sst = second();
+    GEVP_TRY(second());
+    if (turn2.err && nb > TRD1_MAX) turn2.take(heev_groups);  // (given back with the reduction queued)
+    const gevp_status sst = heev_small(ax, nb, Hs, nb, theta, Zs, nb, heevw);
     GEVP_HIP_TRY(hipEventRecord(evs.join, ax->stream));
     GEVP_TRY(sst);
   }
@@ -959,15 +981,22 @@ gevp_status solve_once(gevp_handle h, const gevp_opts* opts, int64_t n, const vo
 
   // ---------------- bounds
   tm.start();
-  if (spec) {
-    // the bound of C (bandwidth-bound) goes to the second stream, after its
-    // seed eigensolve, and overlaps the first rotation and C P (GEMM-bound);
-    // the main stream waits for it just before the first controller call
-    GEVP_HIP_TRY(hipEventRecord(evs.reduced, c->stream));
-    GEVP_HIP_TRY(hipStreamWaitEvent(ax->stream, evs.reduced, 0));
+  // the bound of C (bandwidth-bound) goes to the second stream, after its seed
+  // eigensolve, and overlaps the first rotation and C P (GEMM-bound); the main
+  // stream waits for it just before the first controller call.  In one launch it is
+  // queued only then, when the rotation and C P are.
+  auto bound_c = [&]() -> gevp_status {
     const LanczosRun run{C, n, lz, o.seed ^ 0xC0FFEEull, bC};
     GEVP_TRY(lanczos_bounds_all(ax, n, &run, 1, frac, lanw, lanw2));
     GEVP_HIP_TRY(hipEventRecord(evs.bounds, ax->stream));
+    return GEVP_OK;
+  };
+  const bool bound_late = turn2.err && lan_resident;
+  if (spec) {
+    GEVP_HIP_TRY(hipEventRecord(evs.reduced, c->stream));
+    GEVP_TRY(turn2.give());
+    GEVP_HIP_TRY(hipStreamWaitEvent(ax->stream, evs.reduced, 0));
+    if (!bound_late) GEVP_TRY(bound_c());
   } else {
     const LanczosRun runs[3] = {{C, n, lz, o.seed ^ 0xC0FFEEull, bC},
                                 {Af, n, lzn, o.seed ^ 0xA11CEull, bA},
@@ -1129,8 +1158,6 @@ gevp_status solve_once(gevp_handle h, const gevp_opts* opts, int64_t n, const vo
       GEVP_TRY(launch_zgemm(c, 0, 0, n, nb, n, 1.0, C, n, P1, n, 0.0, nullptr, 0, 0.0, nullptr, 0,
                             nullptr, T, n, nullptr, 0, 0, 0, nullptr, pC));
     } else {
-      // (the eigensolve below shares the second stream's part of the device)
-      if (spec && it == 0) GEVP_HIP_TRY(hipStreamWaitEvent(c->stream, evs.bounds, 0));
       GEVP_TRY(launch_zgemm(c, 0, 0, n, nb, n, 1.0, C, n, P0, n, 0.0, nullptr, 0, 0.0, nullptr, 0,
                             nullptr, W, n, nullptr, 0, 0, 0, nullptr, pC));
       GEVP_TRY(launch_zgemm(c, 1, 0, nb, nb, n, 1.0, P0, n, W, n, 0.0, nullptr, 0, 0.0, nullptr, 0,
@@ -1155,16 +1182,22 @@ gevp_status solve_once(gevp_handle h, const gevp_opts* opts, int64_t n, const vo
     }
     tm.stop(info, GEVP_STAGE_RR);
     info->outer_iters = it + 1;
-    if (spec && it == 0) GEVP_HIP_TRY(hipStreamWaitEvent(c->stream, evs.bounds, 0));
+    if (spec && it == 0) {
+      if (bound_late) {
+        turn2.take(lan_groups);
+        GEVP_TRY(bound_c());
+      }
+      GEVP_HIP_TRY(hipStreamWaitEvent(c->stream, evs.bounds, 0));
+    }
     GEVP_TRY(launch_control(c, cp, theta, rres, bC, norms, tol, st_i, st_d, perm, coefs, rho0,
                             coef2));
     GEVP_HIP_TRY(hipMemcpyAsync(hst.data(), st_i, sizeof(int) * hst.size(), hipMemcpyDeviceToHost, c->stream));
     GEVP_HIP_TRY(hipMemcpyAsync(hsd.data(), st_d, sizeof(double) * hsd.size(), hipMemcpyDeviceToHost, c->stream));
     int gave_up = 0;
-    if (turn2.second)
+    if (turn2.err && it == 0)
       GEVP_HIP_TRY(hipMemcpyAsync(&gave_up, flags + 4, sizeof(int), hipMemcpyDeviceToHost, c->stream));
+    GEVP_TRY(turn2.give());
     GEVP_HIP_TRY(hipStreamSynchronize(c->stream));
-    turn2.release();
     if (gave_up) {  // nothing has been written for the caller yet
       c->shared_gpu = true;
       *again = true;
