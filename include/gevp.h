@@ -193,6 +193,14 @@ gevp_status gevp_set_stream(gevp_handle h, void* hip_stream);
  * gevp_info.gemm_kernel_ms with their flops. */
 gevp_status gevp_set_profiling(gevp_handle h, int flags);
 
+/* Polls before a wait inside a single-launch kernel (the tridiagonalisation and
+ * the Lanczos steps exchange vectors between work-groups that have to be on the
+ * device together) gives up; the kernel then ends, the call goes on with one
+ * launch per step, and the handle stays with those until this is called again.
+ * polls < 0: the default, some tenths of a second.  0 makes every such launch
+ * give up, which is what the tests use it for. */
+gevp_status gevp_set_poll_limit(gevp_handle h, int polls);
+
 /* Free the workspace and the handle. */
 void gevp_destroy(gevp_handle h);
 

@@ -80,6 +80,7 @@ struct gevp_ctx {
   // no launch that must have all its work-groups resident at once: the second
   // stream, unless the solve holds a share for it, and a handle where one gave up
   bool shared_gpu = false;
+  int polls = -1;  // before a wait in such a launch gives up (the handle's; < 0: EXCHANGE_SPINS)
   bool batch_worker = false;  // other workers' launches run beside this stream's
   // where set, such launches raise this flag, record the event and go on (their share
   // of the device is held by the caller, which looks at the flag when it next waits

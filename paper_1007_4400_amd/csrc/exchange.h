@@ -152,8 +152,14 @@ class LaunchTurn {
   int share_;
 };
 
-// whether this handle's stream may take such a launch now: not under capture (the
-// outcome is read back), not where one gave up or other work is meant to run beside
+inline int exchange_spins(const gevp_ctx* c) {
+  const int n = (c->parent ? c->parent : c)->polls;
+  return n < 0 ? EXCHANGE_SPINS : n;
+}
+
+// whether this handle's stream may take such a launch now: not where one gave up or
+// other work is meant to run beside (nor under capture, which a call that waits for
+// its outcome ends in any case)
 inline bool resident_allowed(gevp_ctx* c) {
   return !c->shared_gpu && !stream_capturing(c);
 }

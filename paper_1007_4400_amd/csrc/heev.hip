@@ -2,8 +2,8 @@
 // thousand), all on the GPU in FP64:
 //
 //  1. Householder tridiagonalisation H = U T U^H, whole in one launch that
-//     keeps H in registers, or one fused kernel per reflector.  Step s finishes the rank-2 update of reflector s-1 on the
-//     columns it owns, forms reflector s from column s (which every
+//     keeps H in registers, or one fused kernel per reflector.  Step s
+//     finishes the rank-2 update of reflector s-1 on the columns it owns, forms reflector s from column s (which every
 //     work-group reconstructs redundantly from the old column and the
 //     previous reflector, so no extra grid-wide barrier is needed), and
 //     accumulates p = tau H v for reflector s on its columns.  Hermitian
@@ -619,7 +619,7 @@ __device__ int sturm(const double* d, const double* e2, int n, double x, double 
   cnt += q < 0.0;
   for (int i = 1; i < n; ++i) {
     q = fma(-e2[i - 1], recip(q), d[i] - x);
-  if (fabs(q) < pivmin) q = -pivmin;
+    if (fabs(q) < pivmin) q = -pivmin;
     cnt += q < 0.0;
   }
   return cnt;
@@ -958,7 +958,8 @@ __global__ __launch_bounds__(HT) void k_tri_start(const double* d, const double*
 inline int trd_groups(int64_t n) { return (int)(n - 1 < HT ? (n > 1 ? n - 1 : 1) : HT); }
 
 size_t tridiag_eig_work_bytes(int64_t n) {
-  return 5 * ws_round(sizeof(double) * n * n) + ws_round(sizeof(double) * 8);  // U, Vv, Lm, and the tridiagonalisation's exchange; norm
+  // U, Vv, Lm, and the tridiagonalisation's exchange; norm
+  return 5 * ws_round(sizeof(double) * n * n) + ws_round(sizeof(double) * 8);
 }
 
 gevp_status tridiag_eig(gevp_ctx* c, int64_t n64, const double* d, const double* e, double* theta,
@@ -1031,11 +1032,12 @@ size_t heev_work_bytes(int64_t n) {
   return b;
 }
 
-// One launch per reflector, under capture and where the single launch gave up: the kernel boundary is the grid-wide barrier (a cooperative single launch with
+// One launch per reflector, where the single launch may not run or gave up: the
+// kernel boundary is the grid-wide barrier (a cooperative single launch with
 // explicit barriers measured slower, because each barrier must write back and
-// invalidate the XCD caches).  Issued one by
-// one, the launches cost the host about 4.4 us each at n = 948, more than the
-// later, shorter steps take on the GPU; so the sequence is captured once per
+// invalidate the XCD caches).  Issued one by one, the launches cost the host
+// about 4.4 us each at n = 948, more than the later, shorter steps take on the
+// GPU; so the sequence is captured once per
 // argument set into a graph and replayed (the first call also pays the
 // capture).  Any failure of the graph calls falls back to direct launches.
 namespace {
@@ -1092,9 +1094,8 @@ gevp_status hetrd_launches(gevp_ctx* c, const TrdArgs& a, int G, size_t sh3) {
 
 namespace {
 // The tridiagonalisation in one launch; *done = false when it may not run or gave
-// up, H being unchanged.  A handle whose launch gave up
-// once (its stream may be confined to some of the compute units) does not try
-// again.
+// up, H being unchanged.  A handle whose launch gave up once (its stream may be
+// confined to some of the compute units) does not try again.
 gevp_status hetrd_all(gevp_ctx* c, const TrdArgs& a, TrdExchange x, bool* done) {
   *done = false;
   if (!resident_allowed(c)) return GEVP_OK;
@@ -1128,7 +1129,10 @@ gevp_status hetrd_all(gevp_ctx* c, const TrdArgs& a, TrdExchange x, bool* done) 
   GEVP_HIP_TRY(hipStreamSynchronize(c->stream));
   GEVP_HIP_TRY(launched);
   *done = err == 0;
-  if (err) c->shared_gpu = true;
+  if (err) {
+    if (gevp_log_enabled()) fprintf(stderr, "[gevp] the single-launch tridiagonalisation gave up (n %d)\n", n);
+    c->shared_gpu = true;
+  }
   return GEVP_OK;
 }
 }  // namespace
@@ -1175,12 +1179,12 @@ gevp_status heev_small(gevp_ctx* c, int64_t n64, zd* H, int64_t ldh, double* the
   // Many work-groups in one launch where they can be resident together; one
   // work-group where the exchange through memory costs more than it spreads (the
   // whole eigensolver at n = 32, 64, 116: 0.25, 0.47, 0.94 ms with one, 0.28,
-  // 0.45, 0.76 with many); a launch per reflector under capture and where a
-  // launch gave up.  The exchange lies in the tridiagonal solver's workspace, not
-  // in use yet (40 n^2 bytes against 32 n (n + 15): enough from n = 60).
+  // 0.45, 0.76 with many); a launch per reflector where that one gave up.  The
+  // exchange lies in the tridiagonal solver's workspace, not in use yet (40 n^2 bytes
+  // against 32 n (n + 15): enough from n = 60).
   bool done = false;
   if (n > TRD1_MAX && n <= TRDM_MAX && !c->shared_gpu) {
-    TrdExchange x{(unsigned long long*)tw, 0, (int*)a.pb, EXCHANGE_SPINS};
+    TrdExchange x{(unsigned long long*)tw, 0, (int*)a.pb, exchange_spins(c)};
     GEVP_TRY(hetrd_all(c, a, x, &done));
   }
   if (n <= TRD1_MAX) {

@@ -532,7 +532,7 @@ gevp_status lanczos_resident(gevp_ctx* c, int64_t n, const LanczosRun* runs, int
   a.n = n;
   a.ld = (n + 15) / 16 * 16;
   a.groups = (int)((n + 7) / 8);
-  a.spin = EXCHANGE_SPINS;
+  a.spin = exchange_spins(c);
   char* area[2] = {(char*)work, (char*)work2};
   const size_t vecs = ws_round(sizeof(zd) * n * 4);
   const size_t head = vecs + ws_round(sizeof(double) * 64) + ws_round(sizeof(double) * 64 * 64);
@@ -589,6 +589,7 @@ gevp_status lanczos_resident(gevp_ctx* c, int64_t n, const LanczosRun* runs, int
   GEVP_HIP_TRY(hipStreamSynchronize(c->stream));
   GEVP_HIP_TRY(launched);
   if (err) {
+    if (gevp_log_enabled()) fprintf(stderr, "[gevp] the single-launch Lanczos steps gave up (n %lld)\n", (long long)n);
     c->shared_gpu = true;
     return GEVP_OK;
   }

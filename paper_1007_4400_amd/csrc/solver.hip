@@ -511,6 +511,14 @@ gevp_status gevp_set_stream(gevp_handle h, void* s) {
   return GEVP_OK;
 }
 
+gevp_status gevp_set_poll_limit(gevp_handle h, int polls) {
+  if (!h) return GEVP_ERR_INVALID;
+  h->polls = polls;
+  h->shared_gpu = false;
+  for (gevp_ctx* w : h->workers) w->shared_gpu = false;
+  return GEVP_OK;
+}
+
 gevp_status gevp_set_profiling(gevp_handle h, int on) {
   if (!h) return GEVP_ERR_INVALID;
   h->profiling = on;
@@ -1199,6 +1207,7 @@ gevp_status solve_once(gevp_handle h, const gevp_opts* opts, int64_t n, const vo
     GEVP_TRY(turn2.give());
     GEVP_HIP_TRY(hipStreamSynchronize(c->stream));
     if (gave_up) {  // nothing has been written for the caller yet
+      if (gevp_log_enabled()) fprintf(stderr, "[gevp] a single-launch kernel on the second stream gave up\n");
       c->shared_gpu = true;
       *again = true;
       return GEVP_OK;

@@ -112,6 +112,8 @@ def load():
     lib.gevp_set_stream.restype = I
     lib.gevp_set_profiling.argtypes = [P, I]
     lib.gevp_set_profiling.restype = I
+    lib.gevp_set_poll_limit.argtypes = [P, I]
+    lib.gevp_set_poll_limit.restype = I
     lib.gevp_destroy.argtypes = [P]
     lib.gevp_destroy.restype = None
     lib.gevp_block_size.argtypes = [ctypes.POINTER(Opts), L, L]
@@ -302,6 +304,10 @@ class Handle:
 
     def set_profiling(self, flags: int):
         self.lib.gevp_set_profiling(self.h, int(flags))
+
+    def set_poll_limit(self, polls: int):
+        """Polls before a wait inside a single-launch kernel gives up (< 0: the default)."""
+        self.lib.gevp_set_poll_limit(self.h, int(polls))
 
     def close(self):
         if getattr(self, "h", None):
