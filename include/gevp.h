@@ -372,7 +372,9 @@ gevp_status gevp_backward_noalloc(gevp_handle h, int64_t n, int64_t nev, const v
 /*
  * D = alpha op(A) op(B) + beta Cm + gamma diag-scaled E on the matrix cores, complex128.
  *   opA, opB: 'N' or 'C' (conjugate transpose).  op(A) is m x k, op(B) k x n.
- *   Cm may alias D; Cm / E may be NULL (term dropped).  gcol (device float64[n])
+ *   Cm may alias D; A and B may overlap D (an operand of which more than one
+ *   64-wide tile would be overwritten is copied to the workspace first);
+ *   Cm / E may be NULL (term dropped).  gcol (device float64[n])
  *   scales the E term per column when non-NULL.  Asynchronous.
  * Large products run in residue arithmetic on the INT8 matrix cores (see
  * zgemm_mod.hip) where every entry is then at least as accurate, root mean square

@@ -1617,6 +1617,47 @@ gevp_status gevp_autotune_batched(gevp_handle h, const gevp_opts* opts, int coun
 
 // ---- kernel-level entry points
 
+namespace {
+// whether the ra x ca matrix at A and the rd x cd matrix at D share an entry (where
+// their leading dimensions differ, whether their address ranges meet)
+bool share_entry(const zd* A, int64_t ra, int64_t ca, int64_t lda, const zd* D, int64_t rd, int64_t cd,
+                 int64_t ldd) {
+  if (ra <= 0 || ca <= 0 || rd <= 0 || cd <= 0) return false;
+  const intptr_t a = (intptr_t)A, d = (intptr_t)D, sz = (intptr_t)sizeof(zd);
+  if (a + ((ca - 1) * lda + ra) * sz <= d || d + ((cd - 1) * ldd + rd) * sz <= a) return false;
+  if (lda != ldd || (d - a) % sz != 0) return true;
+  const int64_t off = (d - a) / sz;
+  const int64_t dc = (off >= 0 ? off : off - lda + 1) / lda, dr = off - dc * lda;  // 0 <= dr < lda
+  auto meet = [](int64_t x, int64_t nx, int64_t ny) { return x < ny && x + nx > 0; };
+  return (meet(dr, rd, ra) && meet(dc, cd, ca)) || (meet(dr - lda, rd, ra) && meet(dc + 1, cd, ca));
+}
+
+// A product written over an operand: the kernels read an operand's tile again after
+// another work-group has written its tile of the result, unless one tile spans the
+// operand's side.  Otherwise the operand is copied first, into the workspace.
+gevp_status copy_overwritten(gevp_ctx* c, int opA, int opB, int64_t m, int64_t n, int64_t k, const zd** A,
+                             int64_t* lda, const zd** B, int64_t* ldb, const zd* D, int64_t ldd) {
+  const int64_t ra = opA ? k : m, ca = opA ? m : k, rb = opB ? n : k, cb = opB ? k : n;
+  const bool a = share_entry(*A, ra, ca, *lda, D, m, n, ldd) && !(!opA && *A == D && *lda == ldd && n <= 64);
+  const bool b = share_entry(*B, rb, cb, *ldb, D, m, n, ldd) && !(!opB && *B == D && *ldb == ldd && m <= 64);
+  if (!a && !b) return GEVP_OK;
+  const size_t sa = a ? sizeof(zd) * ra * ca : 0, sb = b ? sizeof(zd) * rb * cb : 0;
+  GEVP_TRY(ws_reserve(c, ws_round(sa) + ws_round(sb)));
+  auto copy = [&](const zd** M, int64_t* ld, int64_t rows, int64_t cols, size_t bytes) -> gevp_status {
+    zd* T = (zd*)ws_take(c, bytes);
+    constexpr int64_t STEP = 32768;  // columns a launch
+    for (int64_t j = 0; j < cols; j += STEP)
+      GEVP_TRY(launch_copy2d(c, rows, std::min(STEP, cols - j), *M + j * *ld, *ld, T + j * rows, rows));
+    *M = T;
+    *ld = rows;
+    return GEVP_OK;
+  };
+  if (a) GEVP_TRY(copy(A, lda, ra, ca, sa));
+  if (b) GEVP_TRY(copy(B, ldb, rb, cb, sb));
+  return GEVP_OK;
+}
+}  // namespace
+
 gevp_status gevp_k_zgemm(gevp_handle h, char opA, char opB, int64_t m, int64_t n, int64_t k,
                          double alpha, const void* A, int64_t lda, const void* B, int64_t ldb,
                          double beta, const void* Cm, int64_t ldc, double gamma, const void* E,
@@ -1631,8 +1672,10 @@ gevp_status gevp_k_zgemm(gevp_handle h, char opA, char opB, int64_t m, int64_t n
   if (ldd < m || (Cm && ldc < m) || (E && lde < m)) return GEVP_ERR_INVALID;
   GEVP_HIP_TRY(hipSetDevice(h->device));
   QueuedCall queued(h);
-  return launch_zgemm(h, oa, ob, m, n, k, alpha, (const zd*)A, lda, (const zd*)B, ldb, beta,
-                      (const zd*)Cm, ldc, gamma, (const zd*)E, lde, gcol, (zd*)D, ldd);
+  const zd *Az = (const zd*)A, *Bz = (const zd*)B;
+  GEVP_TRY(copy_overwritten(h, oa, ob, m, n, k, &Az, &lda, &Bz, &ldb, (const zd*)D, ldd));
+  return launch_zgemm(h, oa, ob, m, n, k, alpha, Az, lda, Bz, ldb, beta, (const zd*)Cm, ldc, gamma,
+                      (const zd*)E, lde, gcol, (zd*)D, ldd);
 }
 
 gevp_status gevp_k_zgemm_tri(gevp_handle h, char opA, char opB, int64_t m, int64_t n, int64_t k,
@@ -1651,8 +1694,9 @@ gevp_status gevp_k_zgemm_tri(gevp_handle h, char opA, char opB, int64_t m, int64
   if (ldd < m || (Cm && ldc < m)) return GEVP_ERR_INVALID;
   GEVP_HIP_TRY(hipSetDevice(h->device));
   QueuedCall queued(h);
-  return launch_zgemm(h, oa, ob, m, n, k, alpha, (const zd*)A, lda, (const zd*)B, ldb, beta,
-                      (const zd*)Cm, ldc, 0.0, nullptr, 0, nullptr, (zd*)D, ldd, nullptr, lower,
+  const zd *Az = (const zd*)A, *Bz = (const zd*)B;
+  GEVP_TRY(copy_overwritten(h, oa, ob, m, n, k, &Az, &lda, &Bz, &ldb, (const zd*)D, ldd));
+  return launch_zgemm(h, oa, ob, m, n, k, alpha, Az, lda, Bz, ldb, beta, (const zd*)Cm, ldc, 0.0, nullptr, 0, nullptr, (zd*)D, ldd, nullptr, lower,
                       upperA);
 }
 
