@@ -193,6 +193,12 @@ gevp_status gevp_set_stream(gevp_handle h, void* hip_stream);
  * gevp_info.gemm_kernel_ms with their flops. */
 gevp_status gevp_set_profiling(gevp_handle h, int flags);
 
+/* Profiling flag 4: the part of the last gevp_solve's gemm_kernel_ms, gemm_flops
+ * and gemm_launches that took the residue route (gevp_k_zgemm below), conversions
+ * and reconstruction included; of the last batch, all its problems' together.
+ * Each of those flops is eight INT8 operations.  Any pointer may be NULL. */
+gevp_status gevp_residue_profile(gevp_handle h, double* ms, double* flops, int64_t* launches);
+
 /* Polls before a wait inside a single-launch kernel (the tridiagonalisation and
  * the Lanczos steps exchange vectors between work-groups that have to be on the
  * device together) gives up; the kernel then ends, the call goes on with one

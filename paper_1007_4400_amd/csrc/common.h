@@ -39,7 +39,7 @@ gevp_status fev_mark(gevp_ctx* c);
 // the launch's algorithmic flops to the context's tally
 gevp_status gev_begin(gevp_ctx* c);
 // shape = {form (opA * 2 + opB), m, n, k, split-K factor, work-groups}
-gevp_status gev_end(gevp_ctx* c, double flops, const int64_t* shape = nullptr);
+gevp_status gev_end(gevp_ctx* c, double flops, const int64_t* shape = nullptr, bool residue = false);
 int gevp_device_cus(int device);  // compute units of a device (cached)
 
 struct gevp_ctx {
@@ -59,6 +59,9 @@ struct gevp_ctx {
   int gev_cap = 0;
   int gev_used = 0;
   double gev_flops = 0.0;
+  std::vector<double> gev_residue;  // per timed launch: its flops if it took the residue route, else 0
+  double res_ms = 0.0, res_flops = 0.0;  // of the last solve, once its events are read
+  int64_t res_launches = 0;
   std::vector<double> gev_shape;  // GEVP_LOG=2: 7 values per timed launch (shape, flops)
   // replayable launch sequences (the tridiagonalisation's one launch per
   // reflector, heev.hip): executable graphs keyed by their kernel arguments,

@@ -199,9 +199,11 @@ gevp_status gev_begin(gevp_ctx* c) {
   return ev_record(c, c->gev, c->gev_cap, c->gev_used);
 }
 
-gevp_status gev_end(gevp_ctx* c, double flops, const int64_t* shape) {
+gevp_status gev_end(gevp_ctx* c, double flops, const int64_t* shape, bool residue) {
   if (!(c->profiling & 4)) return GEVP_OK;
   c->gev_flops += flops;
+  c->gev_residue.resize(c->gev_used / 2, 0.0);
+  c->gev_residue.push_back(residue ? flops : 0.0);
   if (shape && gevp_log_enabled() >= 2) {
     for (int i = 0; i < 6; ++i) c->gev_shape.push_back((double)shape[i]);
     c->gev_shape.push_back(flops);
@@ -437,10 +439,17 @@ gevp_status fev_collect(gevp_ctx* c, gevp_info* info) {
 gevp_status gev_collect(gevp_ctx* c, gevp_info* info) {
   if (!c || !(c->profiling & 4)) return GEVP_OK;
   double tot = 0.0;
+  gevp_ctx* root = c->parent && !c->batch_worker ? c->parent : c;
   for (int i = 0; i + 1 < c->gev_used; i += 2) {
     float ms = 0.f;
     GEVP_HIP_TRY(hipEventElapsedTime(&ms, c->gev[i], c->gev[i + 1]));
     tot += ms;
+    const double fr = (size_t)(i / 2) < c->gev_residue.size() ? c->gev_residue[i / 2] : 0.0;
+    if (fr > 0.0) {
+      root->res_ms += ms;
+      root->res_flops += fr;
+      ++root->res_launches;
+    }
     const size_t r = (size_t)(i / 2) * 7;
     if (r + 7 <= c->gev_shape.size()) {
       const double* g = c->gev_shape.data() + r;
@@ -451,6 +460,7 @@ gevp_status gev_collect(gevp_ctx* c, gevp_info* info) {
     }
   }
   c->gev_shape.clear();
+  c->gev_residue.clear();
   info->gemm_kernel_ms += tot;
   info->gemm_launches += c->gev_used / 2;
   info->gemm_flops += c->gev_flops;
@@ -508,6 +518,14 @@ gevp_status gevp_create(gevp_handle* h, int device) {
 gevp_status gevp_set_stream(gevp_handle h, void* s) {
   if (!h) return GEVP_ERR_INVALID;
   h->stream = (hipStream_t)s;
+  return GEVP_OK;
+}
+
+gevp_status gevp_residue_profile(gevp_handle h, double* ms, double* flops, int64_t* launches) {
+  if (!h) return GEVP_ERR_INVALID;
+  if (ms) *ms = h->res_ms;
+  if (flops) *flops = h->res_flops;
+  if (launches) *launches = h->res_launches;
   return GEVP_OK;
 }
 
@@ -767,6 +785,11 @@ gevp_status solve_once(gevp_handle h, const gevp_opts* opts, int64_t n, const vo
   c->fev_used = 0;
   c->gev_used = 0;
   c->gev_flops = 0.0;
+  c->gev_residue.clear();
+  if (!c->batch_worker) {
+    c->res_ms = c->res_flops = 0.0;
+    c->res_launches = 0;
+  }
   info->block = (int)nb;
 
   const zd* A = (const zd*)A_;
@@ -906,6 +929,7 @@ gevp_status solve_once(gevp_handle h, const gevp_opts* opts, int64_t n, const vo
     ax->profiling = c->profiling & 4;
     ax->gev_used = 0;
     ax->gev_flops = 0.0;
+    ax->gev_residue.clear();
     if (c->ext) {
       ax->mod = (char*)mod_second;
       ax->mod_bytes = mod_second ? mb.second : 0;
@@ -1475,6 +1499,8 @@ gevp_status gevp_solve_batched(gevp_handle h, const gevp_opts* opts, int count, 
   for (int w = 0; w < streams; ++w) {
     gevp_ctx* c = h->workers[w];
     c->profiling = h->profiling & 6;
+    c->res_ms = c->res_flops = 0.0;
+    c->res_launches = 0;
     c->no_split = h->tune_split == 2;
     c->cu_div = h->tune_split == 1 ? streams : 1;
   }
@@ -1522,6 +1548,13 @@ gevp_status gevp_solve_batched(gevp_handle h, const gevp_opts* opts, int count, 
   for (int w = 1; w < streams; ++w) pool.emplace_back(work, w);
   work(0);
   for (auto& t : pool) t.join();
+  h->res_ms = h->res_flops = 0.0;
+  h->res_launches = 0;
+  for (int w = 0; w < streams; ++w) {
+    h->res_ms += h->workers[w]->res_ms;
+    h->res_flops += h->workers[w]->res_flops;
+    h->res_launches += h->workers[w]->res_launches;
+  }
   (void)hipEventDestroy(ready);
   gevp_status worst = GEVP_OK;
   for (int i = 0; i < count; ++i) {

@@ -755,7 +755,7 @@ gevp_status launch_zgemm(gevp_ctx* c, int opA, int opB, int64_t m, int64_t n, in
       fl = 8.0 * nd * (rows * kd - rows * (rows - 1.0) * 0.5);
     }
     const int64_t shape[6] = {opA * 2 + opB, m, n, p.K, p.splits, blocks};
-    GEVP_TRY(gev_end(c, fl, shape));
+    GEVP_TRY(gev_end(c, fl, shape, mod));
   }
   return GEVP_OK;
 }

@@ -112,6 +112,8 @@ def load():
     lib.gevp_set_stream.restype = I
     lib.gevp_set_profiling.argtypes = [P, I]
     lib.gevp_set_profiling.restype = I
+    lib.gevp_residue_profile.argtypes = [P, ctypes.POINTER(D), ctypes.POINTER(D), ctypes.POINTER(L)]
+    lib.gevp_residue_profile.restype = I
     lib.gevp_set_poll_limit.argtypes = [P, I]
     lib.gevp_set_poll_limit.restype = I
     lib.gevp_destroy.argtypes = [P]
@@ -304,6 +306,13 @@ class Handle:
 
     def set_profiling(self, flags: int):
         self.lib.gevp_set_profiling(self.h, int(flags))
+
+    def residue_profile(self) -> dict:
+        """Profiling flag 4: what of the last solve's (or batch's) gemm_* took the
+        residue route."""
+        ms, fl, n = ctypes.c_double(), ctypes.c_double(), ctypes.c_int64()
+        self.lib.gevp_residue_profile(self.h, ctypes.byref(ms), ctypes.byref(fl), ctypes.byref(n))
+        return {"residue_ms": ms.value, "residue_flops": fl.value, "residue_launches": n.value}
 
     def set_poll_limit(self, polls: int):
         """Polls before a wait inside a single-launch kernel gives up (< 0: the default)."""
