@@ -24,6 +24,14 @@
 
 namespace {
 constexpr int HT = 256;  // threads per work-group
+// Columns whose squares sum to less than 2^-900 (their entries' own may have lost
+// digits or be zero) are taken times 2^600 to form their reflector: a rank-deficient
+// matrix whose rounding errors are alike in every column, the matrix of ones say,
+// shrinks by 2^-50 from step to step, and a reflector from lost digits is not unitary.
+constexpr double SMALL_COL = 0x1p-900, COL_UP = 0x1p600;
+__device__ __forceinline__ bool small_column(zd a, double sig) {
+  return __builtin_expect(a.x * a.x + a.y * a.y + sig < SMALL_COL, 0);
+}
 
 __device__ __forceinline__ double wsum(double v) {
 #pragma unroll
@@ -142,7 +150,20 @@ __device__ void hetrd_body(const TrdArgs& a, int s, zd* sm, double* sh, zd* bc) 
     if (wg == 0 && tid == 0) a.d[s] = bc[3].x;
     return;
   }
-  const zd alpha = bc[2];
+  zd alpha = bc[2];
+  double up = 1.0;
+  if (small_column(alpha, sig)) {
+    up = COL_UP;
+    alpha = make_double2(alpha.x * up, alpha.y * up);
+    sig = 0.0;
+#pragma unroll
+    for (int q = 0; q < QMAX; ++q) {
+      const int i = s + tid + q * HT;
+      hc[q] = make_double2(hc[q].x * up, hc[q].y * up);
+      if (i >= s + 2 && i < n) sig += hc[q].x * hc[q].x + hc[q].y * hc[q].y;
+    }
+    sig = bsum(sig, sh);
+  }
   zd tau = make_double2(0.0, 0.0), scal = make_double2(0.0, 0.0);
   double beta;
   if (sig == 0.0 && alpha.y == 0.0) {
@@ -171,7 +192,7 @@ __device__ void hetrd_body(const TrdArgs& a, int s, zd* sm, double* sh, zd* bc) 
     for (int i = tid; i < n; i += HT) vcol[i] = (i > s) ? vs[i] : make_double2(0.0, 0.0);
     if (tid == 0) {
       a.tau[s] = tau;
-      a.e[s] = beta;
+      a.e[s] = beta / up;
       a.d[s] = bc[3].x;
     }
   }
@@ -268,7 +289,13 @@ __device__ __forceinline__ Reflector reflect(int s, int n, const zd* C, const zd
     }
   }
   f.d = cs.x;
-  const double sig = wave_total(lane >= s + 2 ? c.x * c.x + c.y * c.y : 0.0);
+  double sig = wave_total(lane >= s + 2 ? c.x * c.x + c.y * c.y : 0.0), up = 1.0;
+  if (small_column(ca, sig)) {
+    up = COL_UP;
+    ca = make_double2(ca.x * up, ca.y * up);
+    c = make_double2(c.x * up, c.y * up);
+    sig = wave_total(lane >= s + 2 ? c.x * c.x + c.y * c.y : 0.0);
+  }
   f.tau = f.scal = zero;
   if (sig == 0.0 && ca.y == 0.0) {
     f.beta = ca.x;
@@ -280,6 +307,7 @@ __device__ __forceinline__ Reflector reflect(int s, int n, const zd* C, const zd
     const double dd = den.x * den.x + den.y * den.y;
     f.scal = make_double2(den.x / dd, -den.y / dd);
   }
+  f.beta /= up;
   const zd x = cmul(c, f.scal);
   c = make_double2(lane == s + 1 ? 1.0 : lane > s + 1 ? x.x : 0.0, lane > s + 1 ? x.y : 0.0);
   return f;
@@ -495,6 +523,24 @@ __global__ __launch_bounds__(T) void k_hetrd_all(TrdArgs a, TrdExchange e) {
     sig = 0.0;
 #pragma unroll
     for (int u = 0; u < W; ++u) sig += sigs[u];
+    double up = 1.0;
+    if (small_column(ca, sig)) {  // alike in every thread of every work-group
+      up = COL_UP;
+      ca = make_double2(ca.x * up, ca.y * up);
+      sig = 0.0;
+#pragma unroll
+      for (int q = 0; q < R; ++q) {
+        c[q] = make_double2(c[q].x * up, c[q].y * up);
+        if (tid + T * q >= s + 2) sig += c[q].x * c[q].x + c[q].y * c[q].y;
+      }
+      sig = wave_total(sig);
+      __syncthreads();
+      if (lane == 0) sigs[wave] = sig;
+      __syncthreads();
+      sig = 0.0;
+#pragma unroll
+      for (int u = 0; u < W; ++u) sig += sigs[u];
+    }
     zd tau = zero, scal = zero;
     double beta = ca.x;
     if (sig != 0.0 || ca.y != 0.0) {
@@ -517,7 +563,7 @@ __global__ __launch_bounds__(T) void k_hetrd_all(TrdArgs a, TrdExchange e) {
         a.d[s] = cs.x;
         if (s < n - 1) {
           a.tau[s] = tau;
-          a.e[s] = beta;
+          a.e[s] = beta / up;
         }
       }
       if (s < n - 1) {
@@ -636,11 +682,12 @@ __device__ double bmax(double v, double* sh) {
   return fmax(fmax(sh[0], sh[1]), fmax(sh[2], sh[3]));
 }
 
-// One wave per eigenvalue k: every round the 64 lanes evaluate Sturm counts
+// One wave per row k, whose block of T between zero couplings has rows [b0, b1):
+// the block's eigenvalue k - b0.  Every round the 64 lanes evaluate Sturm counts
 // at 64 interior points of [lo, hi] and the bracket shrinks to the
-// sub-interval where the count passes k (65x per round).
+// sub-interval where the count passes it (65x per round).
 __global__ __launch_bounds__(HT) void k_tri_bisect(const double* d, const double* e, int n,
-                                                   double* theta) {
+                                                   double* theta, int2* block) {
   extern __shared__ double sm[];
   double* sd = sm;
   double* se2 = sm + n;
@@ -667,12 +714,28 @@ __global__ __launch_bounds__(HT) void k_tri_bisect(const double* d, const double
   double lo = gl - 2.0 * DBL_EPSILON * tnorm * n - 1e-300;
   double hi = gu + 2.0 * DBL_EPSILON * tnorm * n + 1e-300;
   const double pivmin = DBL_MIN * fmax(1.0, emax);
+  int b0 = 0, b1 = n;
+  for (int i = k - lane;; i -= 64) {  // 64 rows at a time, the nearest in lane 0
+    const unsigned long long m = __ballot(i <= 0 || se2[i - 1] == 0.0);
+    if (m != 0ull) {
+      b0 = max(0, __builtin_amdgcn_readlane(i, __ffsll((long long)m) - 1));
+      break;
+    }
+  }
+  for (int i = k + lane;; i += 64) {
+    const unsigned long long m = __ballot(i >= n - 1 || se2[i] == 0.0);
+    if (m != 0ull) {
+      b1 = min(n, __builtin_amdgcn_readlane(i, __ffsll((long long)m) - 1) + 1);
+      break;
+    }
+  }
   for (int round = 0; round < 40; ++round) {
     if (hi - lo <= 2.0 * DBL_EPSILON * fmax(fabs(lo), fabs(hi)) + 4.0 * pivmin) break;
     const double w = (hi - lo) / 65.0;
     const double x = lo + w * (lane + 1);
-    const int cnt = sturm(sd, se2, n, x, pivmin);
-    const unsigned long long m = __ballot(cnt > k);
+    // (a call of its own for all of T: from row b0 on the loop takes twice as long)
+    const int cnt = b1 - b0 == n ? sturm(sd, se2, n, x, pivmin) : sturm(sd + b0, se2 + b0, b1 - b0, x, pivmin);
+    const unsigned long long m = __ballot(cnt > k - b0);
     const double xs = x;
     if (m == 0ull) {
       lo = __shfl(xs, 63, 64);
@@ -684,7 +747,10 @@ __global__ __launch_bounds__(HT) void k_tri_bisect(const double* d, const double
       lo = nl;
     }
   }
-  if (lane == 0) theta[k] = 0.5 * (lo + hi);
+  if (lane == 0) {
+    theta[k] = 0.5 * (lo + hi);
+    block[k] = make_int2(b0, b1);
+  }
 }
 
 __device__ __forceinline__ uint64_t hmix(uint64_t z) {
@@ -707,8 +773,9 @@ __device__ __forceinline__ uint64_t hmix(uint64_t z) {
 // waited for (and five work arrays, start vectors formed here),
 // now 510 us.
 __global__ __launch_bounds__(64) void k_tri_invit(const double* dg, const double* eg, int n,
-                                                  const double* theta, double* U, double* Vv,
-                                                  double* Lm, double* Zt, const double* tnorm_dev) {
+                                                  const double* raw, const int2* block, double* theta,
+                                                  double* U, double* Vv, double* Lm, double* Zt,
+                                                  const double* tnorm_dev) {
   constexpr int IB = 16;
   const double tnorm = *tnorm_dev;
   extern __shared__ double sm[];
@@ -723,9 +790,28 @@ __global__ __launch_bounds__(64) void k_tri_invit(const double* dg, const double
   const int j = blockIdx.x * 64 + threadIdx.x;
   if (j >= n) return;
   swaps += threadIdx.x;
-  const double lam = theta[j];
-  const double tiny = fmax(DBL_EPSILON * tnorm, DBL_MIN);
+  const double lam = raw[j];
+  // The start vector is zero outside its block, and so is the result: another block's
+  // rows would outweigh this one's where they come closer to the eigenvalue (a row
+  // of zeros to 1e-71, its own block to a rounding error of its norm).
+  const int b0 = block[j].x, b1 = block[j].y;
+  int col = j;  // the eigenvalue's place among all, by value and then by row
+  if (b0 > 0 || b1 < n) {
+    const auto key = [](double x) { return x == x ? x : DBL_MAX * 2.0; };
+    const double mine = key(lam);
+    col = 0;
+    for (int i = 0; i < n; ++i) {
+      const double other = key(raw[i]);
+      col += other < mine || (other == mine && i < j);
+    }
+  }
+  theta[col] = lam;
+  const double tiny = fmax(0x1p-300 * tnorm, 0x1p-960);  // stands for a smaller pivot
+  // entry k of thread j's column of a work array, and of its vector
   auto at = [&](double* A, int k) -> double& { return A[(int64_t)k * n + j]; };
+  auto zt = [&](int k) -> double& { return Zt[(int64_t)k * n + col]; };
+  for (int k = 0; k < b0; ++k) zt(k) = 0.0;
+  for (int k = b1; k < n; ++k) zt(k) = 0.0;
   const int nb = (n + IB - 1) / IB;  // blocks of IB steps
   // working row k: (al, be) on columns (k, k+1); the last step is its pivot alone
   double al = d[0] - lam, be = e[0];
@@ -745,7 +831,7 @@ __global__ __launch_bounds__(64) void k_tri_invit(const double* dg, const double
       const double ck = ev[q], an = dv[q], bn = ev[q + 1];
       const bool sw = fabs(al) < fabs(ck);  // pivot on the next original row (ck, an, bn)
       double piv = sw ? ck : al;
-      if (fabs(piv) < DBL_MIN) piv = copysign(piv == 0.0 ? tiny : DBL_MIN, piv);
+      if (fabs(piv) < tiny) piv = copysign(tiny, piv);
       const double rp = recip(piv), l = (sw ? al : ck) * rp;
       if (k < n) {
         at(U, k) = rp;
@@ -777,10 +863,10 @@ __global__ __launch_bounds__(64) void k_tri_invit(const double* dg, const double
       for (int q = 0; q < IB; ++q) {
         const int k = min(blk * IB + q, n - 1);
         f.l[q] = at(Lm, k);
-        f.a[q] = at(Zt, min(k + 1, n - 1));
+        f.a[q] = zt(min(k + 1, n - 1));
       }
     };
-    double c = at(Zt, 0) * sc;
+    double c = zt(0) * sc;
     auto pass_f = [&](const Fwd& f, int blk) {
       const unsigned bits = swaps[64 * blk];
 #pragma unroll
@@ -789,7 +875,7 @@ __global__ __launch_bounds__(64) void k_tri_invit(const double* dg, const double
         const double a = f.a[q] * sc;
         const bool sw = (bits >> q) & 1;
         if (k < n - 1) {
-          at(Zt, k) = sw ? a : c;
+          zt(k) = sw ? a : c;
           c = fma(-f.l[q], sw ? a : c, sw ? c : a);
         }
       }
@@ -806,7 +892,7 @@ __global__ __launch_bounds__(64) void k_tri_invit(const double* dg, const double
       if (blk + 1 < nb) pass_f(f1, blk + 1);
       __builtin_amdgcn_sched_barrier(0);
     }
-    at(Zt, n - 1) = c;
+    zt(n - 1) = c;
     // backward: U x = y with U upper triangular, bandwidth 3
     double x1 = 0.0, x2 = 0.0;
     mx = 0.0;
@@ -815,7 +901,7 @@ __global__ __launch_bounds__(64) void k_tri_invit(const double* dg, const double
 #pragma unroll
       for (int q = 0; q < IB; ++q) {
         const int k = min(max(blk * IB + q, 0), n - 1);
-        f.y[q] = at(Zt, k);
+        f.y[q] = zt(k);
         f.v[q] = at(Vv, k);
         f.u[q] = at(U, k);
       }
@@ -828,7 +914,7 @@ __global__ __launch_bounds__(64) void k_tri_invit(const double* dg, const double
         if (k < n) {
           const double w = (bits >> q) & 1 ? e[k + 1] : 0.0;
           const double x = fma(-f.v[q], x1, fma(-w, x2, f.y[q])) * f.u[q];
-          at(Zt, k) = x;
+          zt(k) = x;
           x2 = x1;
           x1 = x;
           mx = fmax(mx, fabs(x));
@@ -864,7 +950,7 @@ __global__ __launch_bounds__(64) void k_tri_invit(const double* dg, const double
       double zv[NB];
 #pragma unroll
       for (int q = 0; q < NB; ++q)
-        if (k0 + q < n) zv[q] = at(Zt, k0 + q);
+        if (k0 + q < n) zv[q] = zt(k0 + q);
 #pragma unroll
       for (int q = 0; q < NB; ++q)
         if (k0 + q < n) nrm += (zv[q] * sc) * (zv[q] * sc);
@@ -875,10 +961,10 @@ __global__ __launch_bounds__(64) void k_tri_invit(const double* dg, const double
     double zv[NB];
 #pragma unroll
     for (int q = 0; q < NB; ++q)
-      if (k0 + q < n) zv[q] = at(Zt, k0 + q);
+      if (k0 + q < n) zv[q] = zt(k0 + q);
 #pragma unroll
     for (int q = 0; q < NB; ++q)
-      if (k0 + q < n) at(Zt, k0 + q) = zv[q] * inv;
+      if (k0 + q < n) zt(k0 + q) = zv[q] * inv;
   }
 }
 
@@ -931,9 +1017,17 @@ __global__ __launch_bounds__(256) void k_zt_to_complex(const double* Zt, int n, 
   }
 }
 
-// Group 0: the norm of T; the others: the start vectors of the inverse iteration
+// Group 0: the norm of T, and its couplings without those that T is as well without:
+//  - up to 16 rounding errors of the larger of the two entries beside them, and not
+//    above what moves the smaller one by as many of its own.  Parts of T that differ
+//    in size by the rounding error or more (a matrix of low rank) are blocks of their
+//    own then: an eigenvalue that is zero but for rounding would, by inverse
+//    iteration in both, give the smaller part's vector a second time;
+//  - below the square of the rounding error of T (a vector's entries on both sides of
+//    one could differ by more than the range of numbers), or whose square is none.
+// The others: the start vectors of the inverse iteration
 __global__ __launch_bounds__(HT) void k_tri_start(const double* d, const double* e, int n, double* out,
-                                                  double* Zt) {
+                                                  double* ec, double* Zt) {
   if (blockIdx.x > 0) {
     for (int64_t k = (int64_t)(blockIdx.x - 1) * HT + threadIdx.x; k < (int64_t)n * n;
          k += (int64_t)(gridDim.x - 1) * HT) {
@@ -949,6 +1043,11 @@ __global__ __launch_bounds__(HT) void k_tri_start(const double* d, const double*
     m = fmax(m, fabs(d[i]) + (i > 0 ? fabs(e[i - 1]) : 0.0) + (i < n - 1 ? fabs(e[i]) : 0.0));
   m = bmax(m, sh);
   if (threadIdx.x == 0) out[0] = m;
+  for (int i = threadIdx.x; i < n - 1; i += HT) {
+    const double x = fabs(e[i]), a = fabs(d[i]), b = fabs(d[i + 1]), eps = 16.0 * DBL_EPSILON;
+    const bool none = (x <= eps * fmax(a, b) && x * x <= eps * a * b) || x < 0x1p-106 * m || x * x == 0.0;
+    ec[i] = none ? 0.0 : e[i];
+  }
 }
 }  // namespace
 
@@ -959,8 +1058,10 @@ __global__ __launch_bounds__(HT) void k_tri_start(const double* d, const double*
 inline int trd_groups(int64_t n) { return (int)(n - 1 < HT ? (n > 1 ? n - 1 : 1) : HT); }
 
 size_t tridiag_eig_work_bytes(int64_t n) {
-  // U, Vv, Lm, and the tridiagonalisation's exchange; norm
-  return 5 * ws_round(sizeof(double) * n * n) + ws_round(sizeof(double) * 8);
+  // U, Vv, Lm and four vectors, or the tridiagonalisation's exchange
+  return std::max(5 * ws_round(sizeof(double) * n * n), 3 * ws_round(sizeof(double) * n * n) +
+                                                            3 * ws_round(sizeof(double) * n)) +
+         ws_round(sizeof(double) * 8);
 }
 
 gevp_status tridiag_eig(gevp_ctx* c, int64_t n64, const double* d, const double* e, double* theta,
@@ -976,16 +1077,19 @@ gevp_status tridiag_eig(gevp_ctx* c, int64_t n64, const double* d, const double*
   double* U = (double*)take(sizeof(double) * n * n);
   double* Vv = (double*)take(sizeof(double) * n * n);
   double* Lm = (double*)take(sizeof(double) * n * n);
+  double* ec = (double*)take(sizeof(double) * n);
+  double* raw = (double*)take(sizeof(double) * n);  // eigenvalues by block and their blocks
+  int2* block = (int2*)take(sizeof(int2) * n);
   double* tn = (double*)take(sizeof(double) * 8);
   hipLaunchKernelGGL(k_tri_start, dim3(1 + (unsigned)std::min<int64_t>(((int64_t)n * n + HT - 1) / HT, 512)),
-                     dim3(HT), 0, c->stream, d, e, n, tn, Zt);
+                     dim3(HT), 0, c->stream, d, e, n, tn, ec, Zt);
   GEVP_HIP_TRY(hipGetLastError());
   hipLaunchKernelGGL(k_tri_bisect, dim3((n + 3) / 4), dim3(HT), sizeof(double) * 2 * n, c->stream,
-                     d, e, n, theta);
+                     d, ec, n, raw, block);
   GEVP_HIP_TRY(hipGetLastError());
   const size_t shi = sizeof(double) * 2 * (n + 17) + 2 * 64 * (size_t)((n + 15) / 16);
   hipLaunchKernelGGL(k_tri_invit, dim3((n + 63) / 64), dim3(64), shi, c->stream,
-                     d, e, n, theta, U, Vv, Lm, Zt, tn);
+                     d, ec, n, raw, block, theta, U, Vv, Lm, Zt, tn);
   GEVP_HIP_TRY(hipGetLastError());
   hipLaunchKernelGGL(k_tri_cluster_mgs, dim3(n), dim3(HT), 0, c->stream, theta, n, Zt, tn);
   GEVP_HIP_TRY(hipGetLastError());
