@@ -153,6 +153,10 @@ gevp_status ws_reserve(gevp_ctx* c, size_t bytes);
 // hipMalloc, where need be after the scratch that the handle can do without (the
 // residue products') has been given back; null where that does not help
 void* device_alloc(gevp_ctx* c, size_t bytes);
+// The same for memory a call can do without (scratch of residue products, split-K
+// buffers): nullptr also where it would leave the device without room for what the
+// runtime itself takes late (a kernel's code at its first launch, its stack).
+void* device_alloc_spare(size_t bytes);
 // whether c's stream is being captured (also where that cannot be told): nothing may
 // then be allocated, and no event recorded or waited for that is not the graph's own
 bool stream_capturing(gevp_ctx* c);

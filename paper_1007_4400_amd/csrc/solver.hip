@@ -155,6 +155,17 @@ void* device_alloc(gevp_ctx* c, size_t bytes) {
   return nullptr;
 }
 
+void* device_alloc_spare(size_t bytes) {
+  constexpr size_t LEFT = (size_t)512 << 20;
+  size_t free_bytes = 0, total = 0;
+  void* p = nullptr;
+  if (hipMemGetInfo(&free_bytes, &total) == hipSuccess && free_bytes >= bytes + LEFT &&
+      hipMalloc(&p, bytes) == hipSuccess)
+    return p;
+  (void)hipGetLastError();
+  return nullptr;
+}
+
 void ext_assign(gevp_ctx* parent, gevp_ctx* child, int slot) {
   if (!parent->ext || !child) return;
   if (child->skw && !child->ext) {

@@ -539,7 +539,7 @@ gevp_status splitk_buffer(gevp_ctx* c, size_t need, void** out) {
       c->skw_bytes = 0;
     }
     if (need > SKW_BYTES) return GEVP_ERR_ALLOC;
-    c->skw = device_alloc(c, SKW_BYTES);
+    c->skw = device_alloc_spare(SKW_BYTES);
     if (c->skw) c->skw_bytes = SKW_BYTES;
   }
   *out = c->skw;
@@ -561,10 +561,9 @@ void* mod_scratch(gevp_ctx* c, size_t bytes) {
     c->mod = nullptr;
     c->mod_bytes = 0;
   }
-  if (hipMalloc((void**)&c->mod, bytes) != hipSuccess) {
-    c->mod = nullptr;
+  c->mod = (char*)device_alloc_spare(bytes);
+  if (!c->mod) {
     c->mod_failed = bytes;  // no memory to spare: the FP64 kernels
-    (void)hipGetLastError();
     if (gevp_log_enabled()) fprintf(stderr, "[gevp] no %zu bytes of scratch for residue products\n", bytes);
     return nullptr;
   }

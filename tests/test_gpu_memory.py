@@ -71,3 +71,19 @@ def test_a_shortage_ends_with_the_call(setup):
     again = h.zgemm("N", "N", A, B, out=out)
     assert 0 < short <= 1e-10
     assert torch.equal(again, first)
+
+
+@pytest.mark.parametrize("quarters", [4, 6, 8, 10, 12])
+def test_scratch_leaves_room_for_the_runtime(setup, quarters):
+    """What a call can do without never takes the device's last bytes: a kernel's code
+    is loaded at its first launch, which fails where nothing is left."""
+    gevp, h, A, B, out = setup
+    block = _leave(quarters * GIB // 4)
+    before = torch.cuda.mem_get_info()[0]
+    h.zgemm("N", "N", A, B, out=out)
+    h.zgemm("C", "N", A[:, :64], B[:, :64])  # a cut k
+    torch.cuda.synchronize()
+    left = torch.cuda.mem_get_info()[0]
+    del block
+    print(f"free {before / GIB:.2f} GiB, left {left / GIB:.2f} GiB", flush=True)
+    assert left >= min(before, GIB // 2) - GIB // 16
