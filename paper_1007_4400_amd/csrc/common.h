@@ -119,11 +119,11 @@ struct gevp_ctx {
   bool mod_borrowed = false;  // mod points into the caller-owned workspace
   bool no_mod = false;
   size_t mod_failed = SIZE_MAX;
-  // ws, skw and mod are used in turn by calls on different streams: the stream of the
-  // last asynchronous call that used them, done with them at scratch_done
-  bool scratch_used = false;  // by the call at hand
+  // ws, skw and mod are used in turn by calls on different streams: whether they were
+  // since the handle came to its stream, and whether the next use has to wait for
+  // the stream before (done with them at scratch_done)
+  bool scratch_used = false;
   bool scratch_pending = false;
-  hipStream_t scratch_stream = nullptr;
   hipEvent_t scratch_done = nullptr;
   // split-K cost models count the compute units divided by this (a batched
   // worker shares the GPU with the other streams)
@@ -160,26 +160,11 @@ void* device_alloc_spare(size_t bytes);
 // whether c's stream is being captured (also where that cannot be told): nothing may
 // then be allocated, and no event recorded or waited for that is not the graph's own
 bool stream_capturing(gevp_ctx* c);
-// Before memory of the handle is used on its stream: waits (on the device) for the
-// last call's use of it on another one.
+// Before memory of the handle is used on its stream: waits (on the device) for what
+// the handle queued on the stream before.
 gevp_status scratch_order(gevp_ctx* c);
 // A new call: what could not be allocated before is tried again.
 void scratch_retry(gevp_ctx* c);
-// An entry point that returns with work queued: what it used of the handle's memory
-// is marked for calls on another stream when it returns.
-class QueuedCall {
- public:
-  explicit QueuedCall(gevp_ctx* c) : c_(c) {
-    c->scratch_used = false;
-    scratch_retry(c);
-  }
-  ~QueuedCall();
-  QueuedCall(const QueuedCall&) = delete;
-  QueuedCall& operator=(const QueuedCall&) = delete;
-
- private:
-  gevp_ctx* c_;
-};
 void* ws_take(gevp_ctx* c, size_t bytes);
 inline size_t ws_round(size_t b) { return (b + 255) & ~size_t(255); }
 

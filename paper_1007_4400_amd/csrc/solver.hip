@@ -76,22 +76,10 @@ bool stream_capturing(gevp_ctx* c) {
 
 gevp_status scratch_order(gevp_ctx* c) {
   c->scratch_used = true;
-  if (!c->scratch_pending || c->scratch_stream == c->stream || stream_capturing(c)) return GEVP_OK;
+  if (!c->scratch_pending || stream_capturing(c)) return GEVP_OK;
   GEVP_HIP_TRY(hipStreamWaitEvent(c->stream, c->scratch_done, 0));
-  c->scratch_stream = c->stream;
+  c->scratch_pending = false;
   return GEVP_OK;
-}
-
-QueuedCall::~QueuedCall() {
-  if (!c_->scratch_used || stream_capturing(c_)) return;
-  if ((c_->scratch_done || hipEventCreateWithFlags(&c_->scratch_done, hipEventDisableTiming) == hipSuccess) &&
-      hipEventRecord(c_->scratch_done, c_->stream) == hipSuccess) {
-    c_->scratch_stream = c_->stream;
-    c_->scratch_pending = true;
-  } else {
-    (void)hipGetLastError();
-    (void)hipStreamSynchronize(c_->stream);
-  }
 }
 
 void scratch_retry(gevp_ctx* c) {
@@ -528,6 +516,20 @@ gevp_status gevp_create(gevp_handle* h, int device) {
 
 gevp_status gevp_set_stream(gevp_handle h, void* s) {
   if (!h) return GEVP_ERR_INVALID;
+  if ((hipStream_t)s == h->stream) return GEVP_OK;
+  // what was queued with the handle's memory comes first there (recorded here, not by
+  // every call: 2 to 5 us each; a capture's work is the graph's)
+  if (h->scratch_used && !stream_capturing(h)) {
+    (void)hipSetDevice(h->device);
+    if ((h->scratch_done || hipEventCreateWithFlags(&h->scratch_done, hipEventDisableTiming) == hipSuccess) &&
+        hipEventRecord(h->scratch_done, h->stream) == hipSuccess) {
+      h->scratch_pending = true;
+    } else {
+      (void)hipGetLastError();
+      (void)hipStreamSynchronize(h->stream);
+    }
+  }
+  h->scratch_used = false;
   h->stream = (hipStream_t)s;
   return GEVP_OK;
 }
@@ -568,6 +570,7 @@ void gevp_destroy(gevp_handle h) {
   for (hipEvent_t& e : h->pev)
     if (e) (void)hipEventDestroy(e);
   (void)hipStreamSynchronize(h->stream);
+  if (h->scratch_pending) (void)hipEventSynchronize(h->scratch_done);
   for (gevp_ctx::GraphEntry& g : h->graphs) (void)hipGraphExecDestroy(g.exec);
   h->graphs.clear();
   if (h->cap_stream) (void)hipStreamDestroy(h->cap_stream);
@@ -1424,7 +1427,6 @@ gevp_status gevp_backward(gevp_handle h, int64_t n, int64_t nev, const void* X_,
   if (dA_ && ldda < n) return GEVP_ERR_INVALID;
   if (dB_ && (lddb < n || !lambda)) return GEVP_ERR_INVALID;
   GEVP_HIP_TRY(hipSetDevice(h->device));
-  QueuedCall queued(h);
   gevp_ctx* c = h;
   const zd* X = (const zd*)X_;
   const size_t need = ws_round(sizeof(zd) * n * nev) + ws_round(sizeof(double) * nev);
@@ -1715,7 +1717,7 @@ gevp_status gevp_k_zgemm(gevp_handle h, char opA, char opB, int64_t m, int64_t n
   if (k > 0 && ldb < (ob ? n : k)) return GEVP_ERR_INVALID;
   if (ldd < m || (Cm && ldc < m) || (E && lde < m)) return GEVP_ERR_INVALID;
   GEVP_HIP_TRY(hipSetDevice(h->device));
-  QueuedCall queued(h);
+  scratch_retry(h);
   const zd *Az = (const zd*)A, *Bz = (const zd*)B;
   GEVP_TRY(copy_overwritten(h, oa, ob, m, n, k, &Az, &lda, &Bz, &ldb, (const zd*)D, ldd));
   return launch_zgemm(h, oa, ob, m, n, k, alpha, Az, lda, Bz, ldb, beta, (const zd*)Cm, ldc, gamma,
@@ -1737,7 +1739,7 @@ gevp_status gevp_k_zgemm_tri(gevp_handle h, char opA, char opB, int64_t m, int64
   if (k > 0 && ldb < (ob ? n : k)) return GEVP_ERR_INVALID;
   if (ldd < m || (Cm && ldc < m)) return GEVP_ERR_INVALID;
   GEVP_HIP_TRY(hipSetDevice(h->device));
-  QueuedCall queued(h);
+  scratch_retry(h);
   const zd *Az = (const zd*)A, *Bz = (const zd*)B;
   GEVP_TRY(copy_overwritten(h, oa, ob, m, n, k, &Az, &lda, &Bz, &ldb, (const zd*)D, ldd));
   return launch_zgemm(h, oa, ob, m, n, k, alpha, Az, lda, Bz, ldb, beta, (const zd*)Cm, ldc, 0.0, nullptr, 0, nullptr, (zd*)D, ldd, nullptr, lower,
@@ -1754,7 +1756,6 @@ gevp_status gevp_k_filter_gemm(gevp_handle h, int precision, int64_t n, int64_t 
     return GEVP_ERR_INVALID;
   if (precision != GEVP_FP32 && precision != GEVP_BF16X3) return GEVP_ERR_INVALID;
   GEVP_HIP_TRY(hipSetDevice(h->device));
-  QueuedCall queued(h);
   const bool bf = precision == GEVP_BF16X3;
   const size_t bytes = bf ? bf16_planes_bytes(n) : (size_t)8 * n * n;
   const size_t wbytes = bf ? bf16_filter_work_bytes(n, m) : 0;
@@ -1774,7 +1775,6 @@ gevp_status gevp_k_filter_gemm(gevp_handle h, int precision, int64_t n, int64_t 
 gevp_status gevp_k_hemv(gevp_handle h, int64_t n, const void* M, int64_t ldm, const void* x, void* y) {
   if (!h || n < 1 || !M || ldm < n || !x || !y) return GEVP_ERR_INVALID;
   GEVP_HIP_TRY(hipSetDevice(h->device));
-  QueuedCall queued(h);
   GEVP_TRY(ws_reserve(h, hemv_work_bytes(n) + 256));
   void* w = ws_take(h, hemv_work_bytes(n));
   return launch_hemv(h, n, (const zd*)M, ldm, (const zd*)x, (zd*)y, w);
@@ -1806,7 +1806,6 @@ gevp_status gevp_k_trsm(gevp_handle h, char side, char trans, int64_t n, int64_t
   if (!left && !conj) return GEVP_ERR_INVALID;
   if (ldr < (left ? n : m)) return GEVP_ERR_INVALID;
   GEVP_HIP_TRY(hipSetDevice(h->device));
-  QueuedCall queued(h);
   // the diagonal-block inverses come from re-factoring a copy of L L^H's
   // diagonal blocks: L's own diagonal blocks are inverted directly instead
   GEVP_TRY(ws_reserve(h, ws_round(sizeof(zd) * n * 64) + ws_round(sizeof(zd) * n * n) + 256));

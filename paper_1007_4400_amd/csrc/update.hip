@@ -379,7 +379,6 @@ gevp_status gevp_update_thresholded(gevp_handle h, int64_t n, void* A_, int64_t 
   if (mask && (ldmask < words || ((uintptr_t)mask & 3))) return GEVP_ERR_INVALID;
   if (tiles > INT32_MAX || n > INT32_MAX) return GEVP_ERR_INVALID;
   GEVP_HIP_TRY(hipSetDevice(h->device));
-  QueuedCall queued(h);
   const size_t need = 2 * ws_round(sizeof(double) * tiles) + 4 * ws_round(sizeof(int) * tiles) +
                       ws_round(sizeof(uint16_t) * UT * UT * (size_t)tiles) +
                       ws_round(sizeof(double) * 4) + ws_round(sizeof(int) * 4) +
