@@ -167,6 +167,18 @@ gevp_status scratch_order(gevp_ctx* c);
 void scratch_retry(gevp_ctx* c);
 void* ws_take(gevp_ctx* c, size_t bytes);
 inline size_t ws_round(size_t b) { return (b + 255) & ~size_t(255); }
+// For as long as it lives, c's products keep to the FP64 kernels.
+class Fp64Products {
+ public:
+  explicit Fp64Products(gevp_ctx* c) : c_(c), before_(c->no_mod) { c->no_mod = true; }
+  ~Fp64Products() { c_->no_mod = before_; }
+  Fp64Products(const Fp64Products&) = delete;
+  Fp64Products& operator=(const Fp64Products&) = delete;
+
+ private:
+  gevp_ctx* c_;
+  bool before_;
+};
 
 struct ModPrepared {  // a left operand converted once for several products
   void* planes = nullptr;

@@ -523,14 +523,14 @@ __global__ __launch_bounds__(T) void k_hetrd_all(TrdArgs a, TrdExchange e) {
     sig = 0.0;
 #pragma unroll
     for (int u = 0; u < W; ++u) sig += sigs[u];
-    double up = 1.0;
-    if (small_column(ca, sig)) {  // alike in every thread of every work-group
-      up = COL_UP;
-      ca = make_double2(ca.x * up, ca.y * up);
+    // (alike in every thread of every work-group)
+    const int small = __builtin_amdgcn_readfirstlane(small_column(ca, sig) ? 1 : 0);
+    if (__builtin_expect(small, 0)) {
+      ca = make_double2(ca.x * COL_UP, ca.y * COL_UP);
       sig = 0.0;
 #pragma unroll
       for (int q = 0; q < R; ++q) {
-        c[q] = make_double2(c[q].x * up, c[q].y * up);
+        c[q] = make_double2(c[q].x * COL_UP, c[q].y * COL_UP);
         if (tid + T * q >= s + 2) sig += c[q].x * c[q].x + c[q].y * c[q].y;
       }
       sig = wave_total(sig);
@@ -563,7 +563,7 @@ __global__ __launch_bounds__(T) void k_hetrd_all(TrdArgs a, TrdExchange e) {
         a.d[s] = cs.x;
         if (s < n - 1) {
           a.tau[s] = tau;
-          a.e[s] = beta / up;
+          a.e[s] = small ? beta / COL_UP : beta;
         }
       }
       if (s < n - 1) {
@@ -1309,6 +1309,10 @@ gevp_status heev_small(gevp_ctx* c, int64_t n64, zd* H, int64_t ldh, double* the
     const int k = n - 1;
     hipLaunchKernelGGL(k_ut_clear, dim3((unsigned)k), dim3(256), 0, c->stream, n, k, a.V, a.ldv, a.tau);
     GEVP_HIP_TRY(hipGetLastError());
+    // FP64 products: short reflectors and eigenvectors of T that decay along it have
+    // entries that residues never hold well enough (all four products of 1300 <= n <=
+    // 2048 were done again: 24.4 ms a call at 2048, 22.7 with these alone)
+    const Fp64Products fp64(c);
     GEVP_TRY(launch_zgemm(c, 1, 0, k, k, n, 1.0, a.V, a.ldv, a.V, a.ldv, 0.0, nullptr, 0, 0.0, nullptr,
                           0, nullptr, Lut, k, nullptr, 1));  // lower triangle of V^H V
     hipLaunchKernelGGL(k_ut_diag, dim3((unsigned)((k + 255) / 256)), dim3(256), 0, c->stream, k, Lut, k,

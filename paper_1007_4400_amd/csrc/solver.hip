@@ -1461,10 +1461,10 @@ gevp_status gevp_backward_noalloc(gevp_handle h, int64_t n, int64_t nev, const v
   const zd* X = (const zd*)X_;
   zd* Xw = (zd*)sp;  // n x nev scaled columns, in the scratch array
   // no split-K buffer and no profiling events for the duration of the call
-  const bool ns = c->no_split, nm = c->no_mod;
+  const bool ns = c->no_split;
   const int prof = c->profiling;
+  const Fp64Products fp64(c);
   c->no_split = true;
-  c->no_mod = true;
   c->profiling = 0;
   gevp_status st = GEVP_OK;
   if (dA_) {
@@ -1477,7 +1477,6 @@ gevp_status gevp_backward_noalloc(gevp_handle h, int64_t n, int64_t nev, const v
     if (st == GEVP_OK) st = weighted_projector(c, n, nev, -1.0, Xw, X, ldx, (zd*)dB_, lddb);
   }
   c->no_split = ns;
-  c->no_mod = nm;
   c->profiling = prof;
   return st;
 }
