@@ -181,7 +181,9 @@ typedef enum {
 /* Create a handle on HIP device `device`.  The workspace is allocated lazily. */
 gevp_status gevp_create(gevp_handle* h, int device);
 
-/* Run subsequent work on `hip_stream` (a hipStream_t; NULL = null stream). */
+/* Run subsequent work on `hip_stream` (a hipStream_t; NULL = null stream).  Where the
+ * handle's memory was used on the stream it leaves, an event is recorded there; the
+ * first use on the new stream waits for it on the device. */
 gevp_status gevp_set_stream(gevp_handle h, void* hip_stream);
 
 /* Profiling bits: 1 = per-stage HIP event times into gevp_info.ms (adds a
@@ -358,7 +360,9 @@ gevp_status gevp_backward(gevp_handle h, int64_t n, int64_t nev, const void* X, 
 /*
  * gevp_backward for callers that cannot allocate (code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc): the same
- * arguments, results and asynchronous behaviour, but the n x nev scaled copy
+ * arguments and asynchronous behaviour, the same results to rounding (every product
+ * on the FP64 matrix cores with k uncut, so not as fast where the other one takes the
+ * INT8 matrix cores), but the n x nev scaled copy
  * of X lives in a fixed 32 MiB device array of the library (one per device,
  * held until the process ends; its device address is taken once per device
  * by gevp_create) and no call here allocates or frees memory, creates events
@@ -385,9 +389,10 @@ gevp_status gevp_backward_noalloc(gevp_handle h, int64_t n, int64_t nev, const v
  * Large products run in residue arithmetic on the INT8 matrix cores (see
  * zgemm_mod.hip) where every entry is then at least as accurate, root mean square
  * and relative to sum_k |op(A)(i, k)| |op(B)(k, j)|, as the FP64 matrix cores make
- * it; a check on the device sends every other product to those.  The handle
- * keeps their scratch (up to 16 GiB, the largest product's); under stream capture, or where the memory is not to
- * be had, the FP64 matrix cores do every product.
+ * it; a check on the device sends every other product to those.  The handle keeps
+ * their scratch (up to 16 GiB, the largest product's, given back where other memory
+ * of the handle cannot be had); under stream capture, or where the memory would not
+ * leave the device 512 MiB, the FP64 matrix cores do every product.
  */
 gevp_status gevp_k_zgemm(gevp_handle h, char opA, char opB, int64_t m, int64_t n, int64_t k,
                          double alpha, const void* A, int64_t lda, const void* B, int64_t ldb,
