@@ -12,7 +12,7 @@ def _matrix(kind, n):
     i = np.arange(n)
     if kind == "ones":
         return np.ones((n, n), complex)
-    if kind == "checker":
+    if kind == "alternating":
         return ((-1.0) ** (i[:, None] + i)).astype(complex)
     if kind == "phases":  # entries 1, i, -1, -i
         u = 1j ** (i % 4)
@@ -32,7 +32,7 @@ def _matrix(kind, n):
 
 
 @pytest.mark.parametrize("route", ["one launch", "launches per reflector"])
-@pytest.mark.parametrize("kind", ["ones", "checker", "phases", "two blocks", "tiny column", "rank 2"])
+@pytest.mark.parametrize("kind", ["ones", "alternating", "phases", "two blocks", "tiny column", "rank 2"])
 def test_orthogonal(kind, route):
     from paper_1007_4400_amd import gevp
 
